@@ -53,6 +53,9 @@ struct csrk_matrix {
     void *d_u_vals = nullptr;
     csrk::dev::SrRec *d_srec_u = nullptr;
     int64_t nu = 0;
+    // window walk of a regular A' (csrk::dev::WinArrays); null when it does not qualify
+    csrk::dev::WinRec *d_wrec = nullptr;
+    uint16_t *d_wcols = nullptr, *d_wrend = nullptr;
 };
 
 struct csrk_batch_s {
@@ -63,6 +66,7 @@ struct csrk_batch_s {
     int2 *d_items = nullptr;
     csrk::dev::SrRec *d_brec = nullptr;  // per item, brec_stride super-row records of its SSR
     csrk::dev::SrRec *d_brec_u = nullptr;  // the same slots' union-pattern records (matrices that have one)
+    csrk::dev::WinRec *d_bwrec = nullptr;  // the same slots' window records, when every matrix has them
     int32_t brec_stride = 1;
     // Descriptor tables on the device (forward, adjoint) and the host copies
     // they were written from; a call re-uploads only when its pointers change.
@@ -126,8 +130,11 @@ void free_device(csrk_matrix *h) {
                     (void *)h->d_perm, (void *)h->d_t_row_ptr, (void *)h->d_t_col, (void *)h->d_t_src, h->d_vals,
                     h->d_vals_t == h->d_vals ? nullptr : h->d_vals_t, (void *)h->d_long, (void *)h->d_t_long,
                     (void *)h->d_srec, (void *)h->d_srec_t, (void *)h->d_u_col, (void *)h->d_u_src,
-                    (void *)h->d_erow_ptr, h->d_u_vals, (void *)h->d_srec_u})
+                    (void *)h->d_erow_ptr, h->d_u_vals, (void *)h->d_srec_u, (void *)h->d_wrec, (void *)h->d_wcols,
+                    (void *)h->d_wrend})
         if (p) (void)hipFree(p);
+    h->d_wrec = nullptr;
+    h->d_wcols = h->d_wrend = nullptr;
     h->d_u_col = h->d_u_src = h->d_erow_ptr = nullptr;
     h->d_u_vals = nullptr;
     h->d_srec_u = nullptr;
@@ -257,6 +264,9 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     a.erow_ptr = h->d_erow_ptr;
     a.srec_u = h->d_srec_u;
     a.nu = h->nu;
+    a.win.rec = h->d_wrec;
+    a.win.cols = h->d_wcols;
+    a.win.rend = h->d_wrend;
     return a;
 }
 
@@ -299,6 +309,43 @@ std::vector<int32_t> long_rows_of(const std::vector<int32_t> &rp) {
     for (size_t i = 0; i + 1 < rp.size(); ++i)
         if (rp[i + 1] - rp[i] > csrk::dev::kLongRow) out.push_back(static_cast<int32_t>(i));
     return out;
+}
+
+// Whether the window walk can take the matrix, by its rows and entries (see
+// csrk::dev::kWinRows): the longest row must fit kWinMaxBatches batches of the
+// lanes that the fullest super-row leaves to each row.
+bool window_fits(const csrk_matrix *h) {
+    using namespace csrk::dev;
+    if (h->nnz == 0) return false;
+    int32_t rows = 1;
+    for (size_t s = 0; s + 1 < h->sr_ptr.size(); ++s) rows = std::max(rows, h->sr_ptr[s + 1] - h->sr_ptr[s]);
+    if (rows > kWinRows || h->max_sr_nnz > kWinEntries) return false;
+    int32_t lanes = 1;
+    while (lanes < kWinMaxLanes && rows * lanes * 2 <= kWinRows) lanes *= 2;
+    return h->max_row_any <= kWinMaxBatches * 8 * lanes;
+}
+
+// Builds the window layout on the device from the uploaded arrays (upload
+// calls it last; the launch stream is the default one).
+void upload_window(csrk_matrix *h) {
+    using namespace csrk::dev;
+    if (!window_fits(h)) return;
+    const size_t slots = (h->ssr_ptr.size() - 1) * size_t(h->srec_stride);
+    hip_check(hipMalloc(&h->d_wrec, slots * sizeof(WinRec)), "window records");
+    hip_check(hipMalloc(&h->d_wcols, (size_t(h->nnz) + 8) * sizeof(uint16_t)), "window columns");
+    hip_check(hipMalloc(&h->d_wrend, size_t(h->n) * sizeof(uint16_t)), "window row ends");
+    int32_t *wide = upload_array(std::vector<int32_t>(1, 0), "window flag");
+    int32_t is_wide = 1;
+    hipError_t e = window_layout(h->d_srec, int64_t(slots), h->d_col_idx, h->d_row_ptr, h->d_wrec, h->d_wcols,
+                                 h->d_wrend, wide, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(&is_wide, wide, sizeof(is_wide), hipMemcpyDeviceToHost);
+    (void)hipFree(wide);
+    hip_check(e, "window layout");
+    if (is_wide) {  // some super-row's columns span more than 16 bits
+        for (void *p : {(void *)h->d_wrec, (void *)h->d_wcols, (void *)h->d_wrend}) (void)hipFree(p);
+        h->d_wrec = nullptr;
+        h->d_wcols = h->d_wrend = nullptr;
+    }
 }
 
 void need_device(const csrk_matrix *h) {
@@ -549,6 +596,7 @@ csrk_status csrk_upload(csrk_handle h, csrk_dtype store) {
                 hip_check(e, "value conversion");
                 hip_check(e2, "value conversion");
             }
+            upload_window(h);
         } catch (...) {
             h->on_device = true;
             free_device(h);
@@ -995,6 +1043,23 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
                 }
             }
             bt->d_brec_u = upload_array(brec, "batch union super-row records");
+            if (std::all_of(handles, handles + count, [](csrk_handle h) { return h->d_wrec || h->ssr_ptr.size() == 1; })) {
+                // each matrix's slots in item order, empty where its super-super-rows have fewer than the batch's
+                const size_t row = size_t(bt->brec_stride) * sizeof(csrk::dev::WinRec);
+                hip_check(hipMalloc(&bt->d_bwrec, std::max<size_t>(1, items.size()) * row), "batch window records");
+                hip_check(hipMemset(bt->d_bwrec, 0, items.size() * row), "batch window records");
+                size_t at = 0;
+                for (int32_t b = 0; b < count; ++b) {
+                    const csrk_matrix *h = handles[b];
+                    const size_t nssr = h->ssr_ptr.size() - 1, width = size_t(h->srec_stride) * sizeof(csrk::dev::WinRec);
+                    if (nssr)
+                        hip_check(hipMemcpy2D(bt->d_bwrec + at * size_t(bt->brec_stride), row, h->d_wrec, width, width,
+                                              nssr, hipMemcpyDeviceToDevice),
+                                  "batch window records");
+                    at += nssr;
+                }
+                hip_check(hipStreamSynchronize(nullptr), "batch window records");  // before any stream reads them
+            }
             for (int k = 0; k < 2; ++k)
                 hip_check(hipMalloc(&bt->d_descs[k], sizeof(csrk::dev::MatDesc) * size_t(count)), "batch descriptors");
             // Batch-wide kernel shape: the first handle's lanes/waves, which
@@ -1007,6 +1072,7 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
             if (bt->d_items) (void)hipFree(bt->d_items);
             if (bt->d_brec) (void)hipFree(bt->d_brec);
             if (bt->d_brec_u) (void)hipFree(bt->d_brec_u);
+            if (bt->d_bwrec) (void)hipFree(bt->d_bwrec);
             for (auto *p : bt->d_descs)
                 if (p) (void)hipFree(p);
             delete bt;
@@ -1045,6 +1111,8 @@ csrk::dev::MatDesc *upload_descs(csrk_batch b, int which, const void *const *val
         m.n = h->n;
         m.nssr = static_cast<int32_t>(h->ssr_ptr.size()) - 1;
         m.sym = h->trans.symmetric ? 1 : 0;
+        m.wcols = h->d_wcols;
+        m.wrend = h->d_wrend;
         if (which == 1 && h->d_srec_u) {
             m.uni = 1;
             m.u_col = a.u_col;
@@ -1094,7 +1162,7 @@ bool all_aligned16(std::initializer_list<const void *const *> arrays, size_t cou
 int batch_grid(csrk_batch b, int nrhs, bool adj, bool ind, bool vec, bool both) {
     if (b->blocks_per_cu == 0) return std::max(1, b->nitems);
     const int per_cu = std::max(b->blocks_per_cu, csrk::dev::batch_occupancy(b->store, nrhs, b->shape, adj, ind, vec,
-                                                                              b->all_sym, both));
+                                                                              b->all_sym, both, b->d_bwrec != nullptr));
     const int64_t g = int64_t(b->cus) * per_cu;
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(g, b->nitems)));
 }
@@ -1114,8 +1182,8 @@ csrk_status csrk_batch_spmv(csrk_batch b, const void *const *vals, const void *c
         hipStream_t st = static_cast<hipStream_t>(stream);
         csrk::dev::MatDesc *descs = upload_descs(b, 0, vals, x, y, nullptr, nullptr, nullptr, st);
         const bool vec = all_aligned16({x, reinterpret_cast<const void *const *>(y)}, b->handles.size());
-        hip_check(csrk::dev::batch_forward(descs, b->d_items, b->d_brec, b->brec_stride, b->nitems, b->store, nrhs,
-                                           b->shape,
+        hip_check(csrk::dev::batch_forward(descs, b->d_items, b->d_brec, b->d_bwrec, b->brec_stride, b->nitems,
+                                           b->store, nrhs, b->shape,
                                            batch_grid(b, nrhs, false, false, vec, false), vec, st),
                   "csrk_batch_spmv launch");
         return CSRK_OK;
@@ -1187,6 +1255,7 @@ csrk_status csrk_batch_destroy(csrk_batch b) {
         if (b->d_items) (void)hipFree(b->d_items);
         if (b->d_brec) (void)hipFree(b->d_brec);
         if (b->d_brec_u) (void)hipFree(b->d_brec_u);
+        if (b->d_bwrec) (void)hipFree(b->d_bwrec);
         for (auto *p : b->d_descs)
             if (p) (void)hipFree(p);
         delete b;

@@ -1,6 +1,6 @@
 // Batched kernels: one launch over a work list of (matrix, super-super-row)
 // items for many matrices, forward and adjoint; with their launchers.
-#include "common.hpp"
+#include "window.hpp"
 
 namespace csrk {
 namespace dev {
@@ -44,6 +44,34 @@ __global__ void __launch_bounds__(1024) k_batch_forward(const MatDesc *__restric
             else
                 sr_forward_mrhs_rec<VT, L, VX, false>(rec, row_ptr, col_idx, nullptr, vals, x, y, d.nnz, nrhs, lds,
                                                       lane);
+        }
+    }
+}
+
+// Batched forward by the window walk (one right-hand side, every matrix with
+// the window layout); items as in k_batch_forward.
+template <typename VT>
+__global__ void __launch_bounds__(1024) k_batch_forward_win(const MatDesc *__restrict__ descs,
+                                                            const int2 *__restrict__ items,
+                                                            const WinRec *__restrict__ wrec, int32_t stride,
+                                                            int32_t nitems) {
+    using X = typename Store<VT>::X;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x / kWave);
+    const int nw = blockDim.x / kWave;
+    unsigned char *lds = smem + size_t(wave) * win_forward_lds<VT>();
+    const int32_t b = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int32_t per = (nitems + gridDim.x - 1) / gridDim.x;
+    const int32_t i0 = b * per, i1 = min(nitems, i0 + per);
+    for (int32_t it = i0; it < i1; ++it) {
+        const MatDesc &d = descs[items[it].x];
+        for (int32_t w = wave; w < stride; w += nw) {
+            const WinRec rec = wrec[int64_t(it) * stride + w];
+            if (rec.rows() == 0) break;
+            win_forward<VT>(rec, global_ptr(d.wrend), global_ptr(d.wcols),
+                            global_ptr(static_cast<const VT *>(d.vals)), global_ptr(static_cast<const X *>(d.x)),
+                            global_ptr(static_cast<X *>(d.y)), d.nnz, lds, lane);
         }
     }
 }
@@ -146,10 +174,18 @@ hipError_t by_batch_shape(csrk_dtype store, int nrhs, const Shape &s, bool vec, 
 
 }  // namespace
 
-hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, int32_t stride, int32_t nitems,
-                         csrk_dtype store, int nrhs, Shape s, int grid, bool vec, hipStream_t st) {
+hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, const WinRec *wrec,
+                         int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool vec,
+                         hipStream_t st) {
     if (nitems == 0) return hipSuccess;
     const int block = s.waves * kWave;
+    if (nrhs == 1 && wrec)
+        return by_dtype(store, [&](auto vt) -> hipError_t {
+            using VT = decltype(vt);
+            hipLaunchKernelGGL((k_batch_forward_win<VT>), dim3(grid), dim3(block),
+                               size_t(s.waves) * win_forward_lds<VT>(), st, descs, items, wrec, stride, nitems);
+            return hipGetLastError();
+        });
     return by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
         using VT = decltype(vt);
         constexpr int VX = decltype(vc)::value, LL = decltype(lc)::value;
@@ -215,9 +251,18 @@ hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *b
     });
 }
 
-int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adj, bool ind, bool vec, bool all_sym, bool both) {
+int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adj, bool ind, bool vec, bool all_sym, bool both,
+                    bool win) {
     int blocks = 1;
     const int block = s.waves * kWave;
+    if (!adj && nrhs == 1 && win) {
+        const hipError_t e = by_dtype(store, [&](auto vt) -> hipError_t {
+            using VT = decltype(vt);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_batch_forward_win<VT>, block,
+                                                                size_t(s.waves) * win_forward_lds<VT>());
+        });
+        return (e != hipSuccess || blocks < 1) ? 1 : blocks;
+    }
     const hipError_t e = by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
         using VT = decltype(vt);
         constexpr int VX = decltype(vc)::value, LL = decltype(lc)::value;

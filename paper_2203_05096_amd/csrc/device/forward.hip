@@ -1,7 +1,7 @@
 // Forward kernels: the CSR-k product for one and for several right-hand sides,
 // the product with a fused partial inner product (for CG), and the plain CSR
 // baseline; with their launchers.
-#include "common.hpp"
+#include "window.hpp"
 
 namespace csrk {
 namespace dev {
@@ -84,6 +84,41 @@ __global__ void __launch_bounds__(1024) k_spmv_csrk_dot(const SrRec *__restrict_
     }
 }
 
+// The product by the window walk (every super-row one window of 16-bit
+// columns); with DOT also the partial inner products of k_spmv_csrk_dot.
+template <typename VT, bool DOT>
+__global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride, const VT *__restrict__ vals,
+                                                   const typename Store<VT>::X *__restrict__ x,
+                                                   typename Store<VT>::X *__restrict__ y, int64_t nnz, XcdSplit split,
+                                                   const double *__restrict__ pdot, double *__restrict__ part) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x / kWave);
+    const int nw = blockDim.x / kWave;
+    unsigned char *lds = smem + size_t(wave) * win_forward_lds<VT>();
+    const int32_t t = ssr_of_block(split, int32_t(blockIdx.x));
+    double dot = 0;
+    if (t >= 0) {
+        for (int32_t w = wave; w < stride; w += nw) {
+            const WinRec rec = win.rec[int64_t(t) * stride + w];
+            if (rec.rows() == 0) break;
+            win_forward<VT, DOT>(rec, win.rend, win.cols, vals, x, y, nnz, lds, lane, pdot, &dot);
+        }
+    }
+    if constexpr (DOT) {
+        __shared__ double wsum[1024 / kWave];
+#pragma unroll
+        for (int off = kWave / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
+        if (lane == 0) wsum[wave] = dot;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double s = 0;
+            for (int w = 0; w < nw; ++w) s += wsum[w];
+            part[blockIdx.x] = s;
+        }
+    }
+}
+
 template <typename VT, int RL, int VX>
 __global__ void __launch_bounds__(1024) k_spmv_csrk_mrhs(const SrRec *__restrict__ srec, int32_t stride,
                                                          const int32_t *__restrict__ row_ptr,
@@ -143,6 +178,24 @@ __global__ void __launch_bounds__(256) k_spmv_plain(int32_t n, const int32_t *__
     }
 }
 
+// Launches k_spmv_win (part == nullptr: the product alone).
+template <typename VT>
+hipError_t launch_win(const Arrays &a, const void *vals, const void *x, void *y, const double *pdot, double *part,
+                      Shape s, hipStream_t st) {
+    using X = typename Store<VT>::X;
+    const dim3 grid(a.split_fwd.width * kXcds), block(s.waves * kWave);
+    const size_t lds = size_t(s.waves) * win_forward_lds<VT>();
+    if (part)
+        hipLaunchKernelGGL((k_spmv_win<VT, true>), grid, block, lds, st, a.win, a.srec_stride,
+                           static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
+                           a.split_fwd, pdot, part);
+    else
+        hipLaunchKernelGGL((k_spmv_win<VT, false>), grid, block, lds, st, a.win, a.srec_stride,
+                           static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
+                           a.split_fwd, pdot, part);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t spmv(const Arrays &a, csrk_dtype store, const void *vals, const void *x, void *y, int nrhs, Shape s,
@@ -152,6 +205,7 @@ hipError_t spmv(const Arrays &a, csrk_dtype store, const void *vals, const void 
     return by_dtype(store, [&](auto vt) -> hipError_t {
         using VT = decltype(vt);
         using X = typename Store<VT>::X;
+        if (nrhs == 1 && a.win.rec) return launch_win<VT>(a, vals, x, y, nullptr, nullptr, s, st);
         if (nrhs == 1) {
             return by_lanes(s.lanes_per_row, [&](auto lc) -> hipError_t {
                 constexpr int L = decltype(lc)::value;
@@ -193,6 +247,7 @@ hipError_t spmv_dot(const Arrays &a, csrk_dtype store, const void *vals, const v
     return by_dtype(store, [&](auto vt) -> hipError_t {
         using VT = decltype(vt);
         using X = typename Store<VT>::X;
+        if (a.win.rec) return launch_win<VT>(a, vals, x, y, pdot, part, s, st);
         return by_lanes(s.lanes_per_row, [&](auto lc) -> hipError_t {
             constexpr int L = decltype(lc)::value;
             const int32_t long_blocks = (a.nlong + kXcds - 1) / kXcds * kXcds;

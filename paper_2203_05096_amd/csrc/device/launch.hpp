@@ -43,6 +43,37 @@ struct __attribute__((aligned(16))) SrRec {
     int32_t r0, r1, e0, e1;
 };
 
+// Row-lane window walk (device/window.hpp): the matrices whose super-rows all
+// have at most kWave (64) rows, at most kWinEntries entries (a staging window
+// of 512 less one load step of the widest group) and columns within 65536 of
+// each other.  A row is walked by the 1 to kWinMaxLanes lanes that its super-row
+// leaves it, in batches of 8 entries per lane; a matrix with a row that could
+// take more than kWinMaxBatches batches keeps the general walk, which sums
+// such rows by more lanes.
+constexpr int32_t kWinRows = 64;
+constexpr int32_t kWinEntries = 512 - 8;
+constexpr int32_t kWinSpan = 65536;
+constexpr int32_t kWinMaxBatches = 4;
+constexpr int32_t kWinMaxLanes = 16;
+
+// One super-row of the window walk: rows [r0, r0 + rows()), entries
+// [e0, e0 + entries()), columns base + cols16[k].  Slots as in SrRec (rows()
+// == 0: empty).
+struct __attribute__((aligned(16))) WinRec {
+    int32_t r0, e0;
+    uint32_t count;  // rows | entries << 16
+    int32_t base;
+    __host__ __device__ int rows() const { return int(count & 0xffffu); }
+    __host__ __device__ int entries() const { return int(count >> 16); }
+};
+
+// A' for the window walk; rec == nullptr when the matrix does not qualify.
+struct WinArrays {
+    const WinRec *rec = nullptr;       // per (SSR, slot), like Arrays::srec
+    const uint16_t *cols = nullptr;    // nnz offsets from the super-row's base, padded to a whole load
+    const uint16_t *rend = nullptr;    // n row ends, from the super-row's first entry
+};
+
 // Device arrays of one CSR-k matrix.
 struct Arrays {
     int32_t n = 0;
@@ -85,6 +116,7 @@ struct Arrays {
     const int32_t *erow_ptr = nullptr;  // extras of the rows before row i
     const SrRec *srec_u = nullptr;      // per (SSR, slot): rows [r0, r1), U entries [e0, e1)
     int64_t nu = 0;                     // U entries (with padding)
+    WinArrays win;  // 16-bit form of A' for the window walk
 };
 
 // Per-matrix record of a batched launch (device-resident table).
@@ -112,6 +144,8 @@ struct MatDesc {
     const int32_t *erow_ptr;
     const void *u_vals;
     int64_t nu;
+    const uint16_t *wcols;  // WinArrays of A' (batches whose matrices all have them)
+    const uint16_t *wrend;
 };
 
 // Kernel-shape knobs: lanes per row in the reduction, wavefronts per workgroup.
@@ -137,14 +171,22 @@ hipError_t transpose_values(const Arrays &a, csrk_dtype store, const void *vals,
 // out[p] = vals[idx[p]] (0 where idx[p] < 0) for p < count, storage type `store`.
 hipError_t gather_values(const int32_t *idx, int64_t count, csrk_dtype store, const void *vals, void *out,
                          hipStream_t st);
+// Fills a window layout from `count` super-row records: each slot's WinRec, its
+// entries' 16-bit column offsets and its rows' 16-bit ends (rp[r + 1] - rp[r0]).
+// *wide (one int32, cleared by the caller) becomes nonzero when some super-row's
+// columns span more than kWinSpan.  `cols` must be able to hold every entry.
+hipError_t window_layout(const SrRec *srec, int64_t count, const int32_t *col_idx, const int32_t *rp, WinRec *rec,
+                         uint16_t *cols, uint16_t *rend, int32_t *wide, hipStream_t st);
 hipError_t permute(const Arrays &a, int dir, const void *in, void *out, int nrhs, int elem_bytes, hipStream_t st);
 hipError_t convert_values(const double *src, void *dst, int64_t count, csrk_dtype store, hipStream_t st);
 
 // Batched launches: one grid over `nitems` (matrix, super-super-row) items.
 // `vec`: every right-hand-side block pointer is 16-byte aligned.
 // `brec`: per item, `stride` super-row records (SrRec) of its SSR.
-hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, int32_t stride, int32_t nitems,
-                         csrk_dtype store, int nrhs, Shape s, int grid, bool vec, hipStream_t st);
+// `wrec`: the same slots' window records when every matrix has the window
+// layout, else nullptr.
+hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, const WinRec *wrec,
+                         int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool vec, hipStream_t st);
 // `ind`: the descriptors' vals are caller values in CSR-k order (reached
 // through t_src); otherwise they are the handles' transposed copies.
 // `all_sym`: every matrix of the batch has a symmetric pattern; `both`: both
@@ -158,7 +200,7 @@ hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *b
 
 // Workgroups per CU the batched kernels can keep resident (for sizing the grid).
 int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adjoint, bool ind, bool vec, bool all_sym,
-                    bool both);
+                    bool both, bool win);
 
 // Bandwidth probes (device/util.hip): a streaming read of `bytes` (a multiple of
 // 16, 16-byte aligned) writing one word per workgroup to part[0 .. probe_grid()),

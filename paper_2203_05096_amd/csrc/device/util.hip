@@ -36,6 +36,41 @@ __global__ void k_permute(int32_t n, int nrhs, const int32_t *__restrict__ perm,
     }
 }
 
+// One wavefront per super-row slot: its smallest and largest column, then its
+// record, column offsets and row ends.
+__global__ void __launch_bounds__(256) k_window_layout(const SrRec *__restrict__ srec, int64_t count,
+                                                       const int32_t *__restrict__ col_idx,
+                                                       const int32_t *__restrict__ rp, WinRec *__restrict__ rec,
+                                                       uint16_t *__restrict__ cols, uint16_t *__restrict__ rend,
+                                                       int32_t *__restrict__ wide) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t step = int64_t(gridDim.x) * (blockDim.x / kWave);
+    for (int64_t s = int64_t(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave; s < count; s += step) {
+        const SrRec r = srec[s];
+        const int32_t nent = r.e1 - r.e0, nrows = r.r1 - r.r0;
+        int32_t lo = INT32_MAX, hi = -1;
+        for (int32_t k = r.e0 + lane; k < r.e1; k += kWave) {
+            lo = min(lo, col_idx[k]);
+            hi = max(hi, col_idx[k]);
+        }
+#pragma unroll
+        for (int off = kWave / 2; off >= 1; off >>= 1) {
+            lo = min(lo, __shfl_xor(lo, off));
+            hi = max(hi, __shfl_xor(hi, off));
+        }
+        if (nent == 0) lo = hi = 0;
+        if (lane == 0) {
+            if (int64_t(hi) - lo >= kWinSpan) atomicOr(wide, 1);
+            rec[s] = WinRec{r.r0, r.e0, uint32_t(nrows) | (uint32_t(nent) << 16), lo};
+        }
+        for (int32_t k = r.e0 + lane; k < r.e1; k += kWave) cols[k] = uint16_t(col_idx[k] - lo);
+        if (nrows > 0) {
+            const int32_t p0 = rp[r.r0];
+            for (int32_t i = r.r0 + lane; i < r.r1; i += kWave) rend[i] = uint16_t(rp[i + 1] - p0);
+        }
+    }
+}
+
 // FP64 -> FP32, round to nearest even (the conversion instruction's default mode).
 __global__ void k_to_f32(const double *__restrict__ src, float *__restrict__ dst, int64_t count) {
     for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count; i += int64_t(gridDim.x) * blockDim.x)
@@ -144,6 +179,14 @@ hipError_t gather_values(const int32_t *idx, int64_t count, csrk_dtype store, co
                            static_cast<const uint16_t *>(vals), static_cast<uint16_t *>(out), count);
         break;
     }
+    return hipGetLastError();
+}
+
+hipError_t window_layout(const SrRec *srec, int64_t count, const int32_t *col_idx, const int32_t *rp, WinRec *rec,
+                         uint16_t *cols, uint16_t *rend, int32_t *wide, hipStream_t st) {
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_window_layout, dim3(grid_for(count * kWave, 256)), dim3(256), 0, st, srec, count, col_idx, rp,
+                       rec, cols, rend, wide);
     return hipGetLastError();
 }
 

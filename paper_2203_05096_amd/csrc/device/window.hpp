@@ -1,0 +1,193 @@
+// Row-lane window walk for regular matrices (one right-hand side): every
+// super-row is one staging window of at most kWave rows and kWinEntries
+// entries whose columns span at most 65536, so its columns are kept as 16-bit
+// offsets from the super-row's first column and its row ends as 16-bit offsets
+// from its first entry (WinArrays, built on the device at upload).
+//
+// A wavefront streams one super-row's values and column offsets with 16-byte
+// (8-, 4-byte) loads straight from its record into LDS, as they are; then LL
+// lanes per row walk the row's entries in LDS, gather x and sum in registers
+// (by_rows: all rows of the super-row at once).
+//
+// What bounds it, and why it is laid out so (one MI355X, three matrices used
+// in turn, us before -> after):
+//  - HBM: 2 bytes less per entry and per row.  3D 7-point 128^3 FP64 reads
+//    184 MB instead of 217 MB.
+//  - Gathers.  In entry order (the general walk) a gather instruction's lanes
+//    lie V entries apart, so they touch up to 64 lines; here neighbouring
+//    lanes hold neighbouring rows, whose e-th columns lie next to each other.
+//    Forward with 16-bit columns, entry order -> row order: 3D 7-point 128^3
+//    FP64 32.9 -> 28.4 us (32-bit columns, entry order: 47.4), 27-point
+//    87x90x91 BF16 29.6 -> 20.5 (35.6), 27-point 75x80x77 FP32 22.5 -> 16.6
+//    (25.5).
+//  - The row sums need no second pass over LDS, and the adjoint no map from
+//    entries to rows: a row's g stays in its lanes' registers.
+// Measured and not kept: a resident grid that prefetches the next super-row
+// into registers (3D 7-point 32.9 -> 35.3 us), lane-contiguous scalar loads of
+// the stream (39.3 us), BF16 (value, column) pairs packed in one LDS word
+// (20.5 -> 21.5 us).
+#pragma once
+
+#include "common.hpp"
+
+namespace csrk {
+namespace dev {
+
+namespace {
+
+// Gathers of one lane in flight at once: a 7-point row or a quarter of a
+// 27-point row in one batch (4 measured 2-10% slower on both).
+constexpr int kWinBatch = 8;
+
+static_assert(kWinEntries <= kStageEntries - 8, "a window must fit the staging area from any 16-byte boundary");
+
+template <typename VT>
+struct WinStream {
+    static constexpr int V = Store<VT>::V;
+    static constexpr int U = kStageEntries / (kWave * V);
+    typedef VT VV __attribute__((ext_vector_type(V)));
+    typedef uint16_t CC __attribute__((ext_vector_type(V)));
+    VV v[U];
+    CC c[U];
+};
+
+// The window's values and column offsets, entries [e0, e0 + nent), in whole
+// groups of V from the 16-byte boundary at or below e0.  `cols` is padded to a
+// whole group; the values are the caller's or the handle's nnz elements, so
+// the last group of the array is read one by one.  IND: value k is
+// vals[src[k]] (0 where src[k] < 0), src holding nnz elements too.
+template <typename VT, bool IND>
+__device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t nent, const uint16_t *__restrict__ cols,
+                                         const int32_t *__restrict__ src, const VT *__restrict__ vals, int64_t nnz,
+                                         int lane) {
+    using W = WinStream<VT>;
+    constexpr int V = W::V;
+    typedef int32_t SV __attribute__((ext_vector_type(V)));
+    const int32_t ea = e0 & ~(V - 1), ce = e0 + nent;
+#pragma unroll
+    for (int u = 0; u < W::U; ++u) {
+        const int64_t pos = int64_t(ea) + (u * kWave + lane) * V;
+        if (pos < ce) {
+            w.c[u] = *reinterpret_cast<const typename W::CC *>(cols + pos);
+            if (pos + V <= nnz) {
+                if constexpr (IND) {
+                    const SV sv = *reinterpret_cast<const SV *>(src + pos);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) w.v[u][e] = sv[e] >= 0 ? vals[sv[e]] : VT(0);
+                } else {
+                    w.v[u] = __builtin_nontemporal_load(reinterpret_cast<const typename W::VV *>(vals + pos));
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const int64_t at = pos + e < nnz ? (IND ? int64_t(src[pos + e]) : pos + e) : -1;
+                    w.v[u][e] = at >= 0 ? vals[at] : VT(0);
+                }
+            }
+        }
+    }
+}
+
+// Stages the stream in LDS: entry k of the array at index k - ea.  Groups
+// past the window's end are not loaded and not staged.
+template <typename VT>
+__device__ __forceinline__ void win_stage(const WinStream<VT> &w, int32_t e0, int32_t nent, VT *__restrict__ sval,
+                                          uint16_t *__restrict__ scol, int lane) {
+    using W = WinStream<VT>;
+    constexpr int V = W::V;
+    const int end = (e0 & (V - 1)) + nent;
+#pragma unroll
+    for (int u = 0; u < W::U; ++u) {
+        const int at = (u * kWave + lane) * V;
+        if (at < end) {
+            *reinterpret_cast<typename W::CC *>(scol + at) = w.c[u];
+            *reinterpret_cast<typename W::VV *>(sval + at) = w.v[u];
+        }
+    }
+}
+
+// LDS bytes per wavefront of the forward walk: values and column offsets.
+template <typename VT>
+__host__ __device__ constexpr int win_forward_lds() {
+    return kStageEntries * int(sizeof(VT) + sizeof(uint16_t));
+}
+
+// Lanes per row for a super-row of `nrows` rows: f(integral_constant<int, LL>)
+// with the largest LL <= kWinMaxLanes that walks all rows at once (uniform
+// over the wavefront).  Measured on the stencils (us, forward): 16 rows of 27
+// entries, BF16, 4 lanes each 20.5, 2 lanes 23.6, 1 lane 32.6; 64 rows of 7,
+// FP64, 1 lane 28.4, 2 lanes (two passes) 30.1, 4 lanes 35.4.
+template <typename F>
+__device__ __forceinline__ void by_rows(int nrows, F &&f) {
+    static_assert(kWinMaxLanes == 16 && kWinRows == kWave, "");
+    if (nrows > 32)
+        f(std::integral_constant<int, 1>{});
+    else if (nrows > 16)
+        f(std::integral_constant<int, 2>{});
+    else if (nrows > 8)
+        f(std::integral_constant<int, 4>{});
+    else if (nrows > 4)
+        f(std::integral_constant<int, 8>{});
+    else
+        f(std::integral_constant<int, 16>{});
+}
+
+// y for the rows of one super-row.  With DOT, the lane that stores y[i] also
+// adds y[i] * pdot[i] (FP64, y as stored) to *dot.
+template <typename VT, bool DOT = false>
+__device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *__restrict__ rend16,
+                                            const uint16_t *__restrict__ cols, const VT *__restrict__ vals,
+                                            const typename Store<VT>::X *__restrict__ x,
+                                            typename Store<VT>::X *__restrict__ y, int64_t nnz,
+                                            unsigned char *__restrict__ lds, int lane,
+                                            const double *__restrict__ pdot = nullptr, double *dot = nullptr) {
+    using A = typename Store<VT>::A;
+    using X = typename Store<VT>::X;
+    constexpr int V = Store<VT>::V;
+    constexpr int B = kWinBatch;
+    VT *sval = reinterpret_cast<VT *>(lds);
+    uint16_t *scol = reinterpret_cast<uint16_t *>(lds + kStageEntries * sizeof(VT));
+    const int nrows = rec.rows(), nent = rec.entries(), off = rec.e0 & (V - 1);
+    WinStream<VT> w;
+    win_load<VT, false>(w, rec.e0, nent, cols, nullptr, vals, nnz, lane);
+    const int my_end = lane < nrows ? int(rend16[rec.r0 + lane]) : 0;
+    win_stage<VT>(w, rec.e0, nent, sval, scol, lane);
+    wave_lds_sync();
+    const X *xb = x + rec.base;
+    by_rows(nrows, [&](auto lc) {
+        constexpr int LL = decltype(lc)::value;
+        const int rr = lane / LL;
+        const bool act = rr < nrows;
+        const int rend = __shfl(my_end, act ? rr : 0);
+        const int prev = __shfl(my_end, (act && rr > 0) ? rr - 1 : 0);
+        int k = off + (rr > 0 ? prev : 0) + lane % LL;
+        const int ke = act ? off + rend : 0;
+        A acc = 0;
+        while (__any(k < ke)) {
+            X xv[B];
+            A a[B];
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                const bool ok = k + j * LL < ke;
+                const int kk = ok ? k + j * LL : off;
+                const uint32_t c = scol[kk];
+                a[j] = ok ? Store<VT>::widen(sval[kk]) : A(0);
+                xv[j] = ok ? xb[c] : X(0);
+            }
+#pragma unroll
+            for (int j = 0; j < B; ++j) acc += a[j] * A(xv[j]);
+            k += B * LL;
+        }
+        acc = group_sum<LL>(acc);
+        if (act && lane % LL == 0) {
+            y[rec.r0 + rr] = X(acc);
+            if constexpr (DOT) *dot += double(X(acc)) * pdot[rec.r0 + rr];
+        }
+    });
+    wave_lds_sync();
+}
+
+}  // namespace
+
+}  // namespace dev
+}  // namespace csrk

@@ -1,0 +1,95 @@
+"""The window walk at the edges of its rule: full and overfull windows, column spans around 16 bits, rows around a
+batch of gathers, empty rows and super-rows, windows that start and end off a load boundary; against the oracle."""
+
+import numpy as np
+import pytest
+
+from gen import CsrInput
+from tests.gpu_util import check_forward, params, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import precision as OP  # noqa: E402
+from paper_2203_05096_amd.matrix import CsrkBatch, CsrkMatrix  # noqa: E402
+
+DT = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.float32}
+
+
+def matrix(lengths, n=None, seed=0, span=None):
+    """Rows of the given lengths with random columns (the first `span` columns of a row's neighbourhood)."""
+    rng = np.random.default_rng(seed)
+    n = len(lengths) if n is None else n
+    cols = []
+    for i, m in enumerate(lengths):
+        w = n if span is None else span
+        lo = min(max(0, i - w // 2), n - w)
+        cols.append(np.sort(rng.choice(w, m, replace=False)) + lo)
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate(cols).astype(np.int32) if len(cols) else np.zeros(0, np.int32)
+    return CsrInput("w", n, rp, ci, rng.uniform(-1, 1, len(ci)), {})
+
+
+def wide(n, srs, gap):
+    """A band of three, and in the first row of each super-row an entry `gap` columns away from its first column."""
+    rows = [sorted({max(0, i - 1), i, min(n - 1, i + 1)}) for i in range(n)]
+    for i in range(0, n, srs):
+        far = rows[i][0] + gap
+        if far < n:
+            rows[i] = sorted(set(rows[i]) | {far})
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    return CsrInput("wide", n, rp, ci, np.random.default_rng(3).uniform(-1, 1, len(ci)), {})
+
+
+CASES = {
+    # 64 rows; 7 and 8 entries: one batch; 504 entries fill the window, 505 do not fit
+    "full": (lambda: matrix([8] * 63 + [0] + [7] * 64 + [8] * 62 + [4, 4]), 64),
+    "overfull": (lambda: matrix([8] * 62 + [9, 0] + [7] * 64), 64),
+    # rows around one and two batches of one lane, up to the four batches of the rule, and beyond it
+    "batches": (lambda: matrix([9, 15, 16, 17, 31, 32, 8, 0] * 13 + [5]), 33),
+    "beyond": (lambda: matrix([3] * 40 + [33] + [2] * 60), 40),
+    # two to sixteen lanes per row, with short last super-rows
+    "lanes2": (lambda: matrix([15, 17, 13, 0] * 21 + [16]), 32),
+    "lanes4": (lambda: matrix([27, 31, 33, 25, 32] * 20 + [64]), 15),
+    "lanes8": (lambda: matrix([64, 63, 65, 50, 56, 1] * 20 + [9]), 7),
+    "lanes16": (lambda: matrix([128, 127, 129, 100] * 40 + [3]), 3),
+    "one_row": (lambda: matrix([200, 0, 1, 7, 33, 180] * 40), 1),
+    "empty": (lambda: matrix([0] * 64 + [3] * 64 + [0] * 70), 64),
+    "tiny": (lambda: matrix([1, 0, 2]), 64),
+}
+
+
+def check(A, srs, store, waves):
+    A.vals = OP.stored_values(A.vals, store)
+    M = CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store,
+                            params=params(srs, 3, lanes=2, waves=waves, reorder="none"))
+    x = np.random.default_rng(1).uniform(-1, 1, A.n).astype(np.float32).astype(np.float64)
+    xd = to_dev(x, DT[store])
+    y = M.spmv(xd)
+    y2 = M.spmv(xd, vals=M.values())
+    B = CsrkBatch([M, M])
+    yb = B.spmv([xd, xd])
+    torch.cuda.synchronize()
+    perm = np.arange(A.n)
+    check_forward(y.double().cpu().numpy(), A, x, perm, store, False, label="window")
+    assert torch.equal(y, y2) and torch.equal(y, yb[0]) and torch.equal(y, yb[1])
+    B.close()
+    M.close()
+
+
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_window_edges(name, store):
+    make, srs = CASES[name]
+    say("window", name, store)
+    check(make(), srs, store, waves=2)
+
+
+@pytest.mark.parametrize("gap", [65535, 65536])
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+def test_window_column_span(gap, store):
+    """Column offsets up to 65535 are 16-bit; one more and the general walk takes the matrix."""
+    say("window span", gap, store)
+    check(wide(70001, 16, gap), 16, store, waves=4)
