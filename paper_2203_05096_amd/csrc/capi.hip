@@ -56,6 +56,9 @@ struct csrk_matrix {
     // window walk of a regular A' (csrk::dev::WinArrays); null when it does not qualify
     csrk::dev::WinRec *d_wrec = nullptr;
     uint16_t *d_wcols = nullptr, *d_wrend = nullptr;
+    // the same of its union pattern (nonsymmetric A')
+    csrk::dev::WinRec *d_wrec_u = nullptr;
+    uint16_t *d_wucols = nullptr, *d_wxend = nullptr;
 };
 
 struct csrk_batch_s {
@@ -66,7 +69,9 @@ struct csrk_batch_s {
     int2 *d_items = nullptr;
     csrk::dev::SrRec *d_brec = nullptr;  // per item, brec_stride super-row records of its SSR
     csrk::dev::SrRec *d_brec_u = nullptr;  // the same slots' union-pattern records (matrices that have one)
-    csrk::dev::WinRec *d_bwrec = nullptr;  // the same slots' window records, when every matrix has them
+    // the same slots' window records, when every matrix has them: of A', and of what its adjoint streams
+    // (the union pattern's where A' is nonsymmetric)
+    csrk::dev::WinRec *d_bwrec = nullptr, *d_bwrec_u = nullptr;
     int32_t brec_stride = 1;
     // Descriptor tables on the device (forward, adjoint) and the host copies
     // they were written from; a call re-uploads only when its pointers change.
@@ -131,10 +136,10 @@ void free_device(csrk_matrix *h) {
                     h->d_vals_t == h->d_vals ? nullptr : h->d_vals_t, (void *)h->d_long, (void *)h->d_t_long,
                     (void *)h->d_srec, (void *)h->d_srec_t, (void *)h->d_u_col, (void *)h->d_u_src,
                     (void *)h->d_erow_ptr, h->d_u_vals, (void *)h->d_srec_u, (void *)h->d_wrec, (void *)h->d_wcols,
-                    (void *)h->d_wrend})
+                    (void *)h->d_wrend, (void *)h->d_wrec_u, (void *)h->d_wucols, (void *)h->d_wxend})
         if (p) (void)hipFree(p);
-    h->d_wrec = nullptr;
-    h->d_wcols = h->d_wrend = nullptr;
+    h->d_wrec = h->d_wrec_u = nullptr;
+    h->d_wcols = h->d_wrend = h->d_wucols = h->d_wxend = nullptr;
     h->d_u_col = h->d_u_src = h->d_erow_ptr = nullptr;
     h->d_u_vals = nullptr;
     h->d_srec_u = nullptr;
@@ -267,6 +272,9 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     a.win.rec = h->d_wrec;
     a.win.cols = h->d_wcols;
     a.win.rend = h->d_wrend;
+    a.win.urec = h->d_wrec_u;
+    a.win.ucols = h->d_wucols;
+    a.win.xend = h->d_wxend;
     return a;
 }
 
@@ -325,27 +333,35 @@ bool window_fits(const csrk_matrix *h) {
     return h->max_row_any <= kWinMaxBatches * 8 * lanes;
 }
 
-// Builds the window layout on the device from the uploaded arrays (upload
-// calls it last; the launch stream is the default one).
-void upload_window(csrk_matrix *h) {
+// One window layout (csrk::dev::window_layout) of `entries` entries: allocates
+// and fills rec, cols and ends; leaves them null when some super-row's columns
+// span more than 16 bits.
+void build_window(const csrk_matrix *h, const csrk::dev::SrRec *srec, int64_t entries, const int32_t *col_idx,
+                  const int32_t *rp, csrk::dev::WinRec *&rec, uint16_t *&cols, uint16_t *&ends) {
     using namespace csrk::dev;
-    if (!window_fits(h)) return;
     const size_t slots = (h->ssr_ptr.size() - 1) * size_t(h->srec_stride);
-    hip_check(hipMalloc(&h->d_wrec, slots * sizeof(WinRec)), "window records");
-    hip_check(hipMalloc(&h->d_wcols, (size_t(h->nnz) + 8) * sizeof(uint16_t)), "window columns");
-    hip_check(hipMalloc(&h->d_wrend, size_t(h->n) * sizeof(uint16_t)), "window row ends");
+    hip_check(hipMalloc(&rec, slots * sizeof(WinRec)), "window records");
+    hip_check(hipMalloc(&cols, (size_t(entries) + 8) * sizeof(uint16_t)), "window columns");
+    hip_check(hipMalloc(&ends, size_t(h->n) * sizeof(uint16_t)), "window row ends");
     int32_t *wide = upload_array(std::vector<int32_t>(1, 0), "window flag");
     int32_t is_wide = 1;
-    hipError_t e = window_layout(h->d_srec, int64_t(slots), h->d_col_idx, h->d_row_ptr, h->d_wrec, h->d_wcols,
-                                 h->d_wrend, wide, nullptr);
+    hipError_t e = window_layout(srec, int64_t(slots), col_idx, rp, rec, cols, ends, wide, nullptr);
     if (e == hipSuccess) e = hipMemcpy(&is_wide, wide, sizeof(is_wide), hipMemcpyDeviceToHost);
     (void)hipFree(wide);
     hip_check(e, "window layout");
-    if (is_wide) {  // some super-row's columns span more than 16 bits
-        for (void *p : {(void *)h->d_wrec, (void *)h->d_wcols, (void *)h->d_wrend}) (void)hipFree(p);
-        h->d_wrec = nullptr;
-        h->d_wcols = h->d_wrend = nullptr;
-    }
+    if (!is_wide) return;
+    for (void *p : {(void *)rec, (void *)cols, (void *)ends}) (void)hipFree(p);
+    rec = nullptr;
+    cols = ends = nullptr;
+}
+
+// Builds the window layouts of A' and of its union pattern from the uploaded
+// arrays (upload calls it last; the launch stream is the default one).
+void upload_window(csrk_matrix *h) {
+    if (!window_fits(h)) return;
+    build_window(h, h->d_srec, h->nnz, h->d_col_idx, h->d_row_ptr, h->d_wrec, h->d_wcols, h->d_wrend);
+    if (h->d_wrec && h->d_srec_u)
+        build_window(h, h->d_srec_u, h->nu, h->d_u_col, h->d_erow_ptr, h->d_wrec_u, h->d_wucols, h->d_wxend);
 }
 
 void need_device(const csrk_matrix *h) {
@@ -993,6 +1009,38 @@ csrk_status csrk_destroy(csrk_handle h) {
     });
 }
 
+namespace {
+
+// The batch's window records: each matrix's slots in item order, empty where
+// its super-super-rows have fewer than the batch's.
+void batch_windows(csrk_batch bt, size_t nitems) {
+    using csrk::dev::WinRec;
+    const size_t row = size_t(bt->brec_stride) * sizeof(WinRec);
+    auto gather = [&](auto &&of) -> WinRec * {
+        for (const csrk_matrix *h : bt->handles)
+            if (h->ssr_ptr.size() > 1 && !of(h)) return nullptr;
+        WinRec *out = nullptr;
+        hip_check(hipMalloc(&out, std::max<size_t>(1, nitems) * row), "batch window records");
+        hipError_t e = hipMemset(out, 0, nitems * row);
+        size_t at = 0;
+        for (const csrk_matrix *h : bt->handles) {
+            const size_t nssr = h->ssr_ptr.size() - 1, width = size_t(h->srec_stride) * sizeof(WinRec);
+            if (nssr && e == hipSuccess)
+                e = hipMemcpy2D(out + at * size_t(bt->brec_stride), row, of(h), width, width, nssr,
+                                hipMemcpyDeviceToDevice);
+            at += nssr;
+        }
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);  // before any stream reads them
+        if (e != hipSuccess) (void)hipFree(out);
+        hip_check(e, "batch window records");
+        return out;
+    };
+    bt->d_bwrec = gather([](const csrk_matrix *h) { return h->d_wrec; });
+    if (bt->d_bwrec) bt->d_bwrec_u = gather([](const csrk_matrix *h) { return h->trans.symmetric ? h->d_wrec : h->d_wrec_u; });
+}
+
+}  // namespace
+
 csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_batch *out) {
     return guard([&] {
         if (!out || !handles || count < 1) throw Error{CSRK_ERR_ARG, "need count >= 1 handles and an output"};
@@ -1043,23 +1091,7 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
                 }
             }
             bt->d_brec_u = upload_array(brec, "batch union super-row records");
-            if (std::all_of(handles, handles + count, [](csrk_handle h) { return h->d_wrec || h->ssr_ptr.size() == 1; })) {
-                // each matrix's slots in item order, empty where its super-super-rows have fewer than the batch's
-                const size_t row = size_t(bt->brec_stride) * sizeof(csrk::dev::WinRec);
-                hip_check(hipMalloc(&bt->d_bwrec, std::max<size_t>(1, items.size()) * row), "batch window records");
-                hip_check(hipMemset(bt->d_bwrec, 0, items.size() * row), "batch window records");
-                size_t at = 0;
-                for (int32_t b = 0; b < count; ++b) {
-                    const csrk_matrix *h = handles[b];
-                    const size_t nssr = h->ssr_ptr.size() - 1, width = size_t(h->srec_stride) * sizeof(csrk::dev::WinRec);
-                    if (nssr)
-                        hip_check(hipMemcpy2D(bt->d_bwrec + at * size_t(bt->brec_stride), row, h->d_wrec, width, width,
-                                              nssr, hipMemcpyDeviceToDevice),
-                                  "batch window records");
-                    at += nssr;
-                }
-                hip_check(hipStreamSynchronize(nullptr), "batch window records");  // before any stream reads them
-            }
+            batch_windows(bt, items.size());
             for (int k = 0; k < 2; ++k)
                 hip_check(hipMalloc(&bt->d_descs[k], sizeof(csrk::dev::MatDesc) * size_t(count)), "batch descriptors");
             // Batch-wide kernel shape: the first handle's lanes/waves, which
@@ -1073,6 +1105,7 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
             if (bt->d_brec) (void)hipFree(bt->d_brec);
             if (bt->d_brec_u) (void)hipFree(bt->d_brec_u);
             if (bt->d_bwrec) (void)hipFree(bt->d_bwrec);
+            if (bt->d_bwrec_u) (void)hipFree(bt->d_bwrec_u);
             for (auto *p : bt->d_descs)
                 if (p) (void)hipFree(p);
             delete bt;
@@ -1113,6 +1146,8 @@ csrk::dev::MatDesc *upload_descs(csrk_batch b, int which, const void *const *val
         m.sym = h->trans.symmetric ? 1 : 0;
         m.wcols = h->d_wcols;
         m.wrend = h->d_wrend;
+        m.wucols = h->d_wucols;
+        m.wxend = h->d_wxend;
         if (which == 1 && h->d_srec_u) {
             m.uni = 1;
             m.u_col = a.u_col;
@@ -1162,7 +1197,8 @@ bool all_aligned16(std::initializer_list<const void *const *> arrays, size_t cou
 int batch_grid(csrk_batch b, int nrhs, bool adj, bool ind, bool vec, bool both) {
     if (b->blocks_per_cu == 0) return std::max(1, b->nitems);
     const int per_cu = std::max(b->blocks_per_cu, csrk::dev::batch_occupancy(b->store, nrhs, b->shape, adj, ind, vec,
-                                                                              b->all_sym, both, b->d_bwrec != nullptr));
+                                                                              b->all_sym, both,
+                                                                              (adj ? b->d_bwrec_u : b->d_bwrec) != nullptr));
     const int64_t g = int64_t(b->cus) * per_cu;
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(g, b->nitems)));
 }
@@ -1207,8 +1243,12 @@ csrk_status csrk_batch_spmv_adjoint(csrk_batch b, const void *const *vals, const
         const bool ind = vals && std::any_of(vals, vals + b->handles.size(), [](const void *p) { return p != nullptr; });
         const bool vec = all_aligned16({x, g, reinterpret_cast<const void *const *>(grad_x)}, b->handles.size());
         const bool both = grad_x && grad_vals;
-        hip_check(csrk::dev::batch_adjoint(descs, b->d_items, b->d_brec, b->d_brec_u, b->brec_stride, b->nitems,
-                                           b->store, nrhs,
+        // the window walk writes both outputs of every matrix; NULL entries are left to the general walk
+        bool whole = both;
+        for (size_t i = 0; whole && i < b->handles.size(); ++i)
+            whole = b->handles[i]->n == 0 || (grad_x[i] && grad_vals[i]);
+        hip_check(csrk::dev::batch_adjoint(descs, b->d_items, b->d_brec, b->d_brec_u, b->d_bwrec,
+                                           whole ? b->d_bwrec_u : nullptr, b->brec_stride, b->nitems, b->store, nrhs,
                                            b->shape,
                                            batch_grid(b, nrhs, true, ind, vec, both), ind, vec, b->all_sym, both, st),
                   "csrk_batch_spmv_adjoint launch");
@@ -1256,6 +1296,7 @@ csrk_status csrk_batch_destroy(csrk_batch b) {
         if (b->d_brec) (void)hipFree(b->d_brec);
         if (b->d_brec_u) (void)hipFree(b->d_brec_u);
         if (b->d_bwrec) (void)hipFree(b->d_bwrec);
+        if (b->d_bwrec_u) (void)hipFree(b->d_bwrec_u);
         for (auto *p : b->d_descs)
             if (p) (void)hipFree(p);
         delete b;

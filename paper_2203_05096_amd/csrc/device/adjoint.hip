@@ -109,6 +109,8 @@ __global__ void __launch_bounds__(1024) k_adjoint_csrk_mrhs(
 hipError_t adjoint(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
                    void *gv, int nrhs, Shape s, hipStream_t st) {
     if (a.nssr == 0) return hipSuccess;
+    if (nrhs == 1 && gx && gv && a.win.rec && (a.sym || a.win.urec))
+        return adjoint_win(a, store, vals, x, g, gx, gv, s, st);
     const int block = s.waves * kWave;
     // Values passed by the caller are reached through the transposed map (the
     // union's source map on the union path); the handle's own values use its

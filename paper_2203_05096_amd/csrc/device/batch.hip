@@ -228,9 +228,11 @@ hipError_t by_adj_variant(bool ind, int path, F &&f) {
 }
 
 hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *brec, const SrRec *brec_u,
-                         int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool ind,
-                         bool vec, bool all_sym, bool both, hipStream_t st) {
+                         const WinRec *wrec, const WinRec *wrec_u, int32_t stride, int32_t nitems, csrk_dtype store,
+                         int nrhs, Shape s, int grid, bool ind, bool vec, bool all_sym, bool both, hipStream_t st) {
     if (nitems == 0) return hipSuccess;
+    if (nrhs == 1 && both && wrec_u)
+        return batch_adjoint_win(descs, items, wrec, wrec_u, stride, nitems, store, s, grid, ind, st);
     const int block = s.waves * kWave;
     const int path = adj_path(nrhs, all_sym, both);
     return by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
@@ -263,6 +265,7 @@ int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adj, bool ind, boo
         });
         return (e != hipSuccess || blocks < 1) ? 1 : blocks;
     }
+    if (adj && nrhs == 1 && both && win) return batch_adjoint_win_occupancy(store, s, ind);
     const hipError_t e = by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
         using VT = decltype(vt);
         constexpr int VX = decltype(vc)::value, LL = decltype(lc)::value;

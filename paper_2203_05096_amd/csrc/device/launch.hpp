@@ -72,6 +72,10 @@ struct WinArrays {
     const WinRec *rec = nullptr;       // per (SSR, slot), like Arrays::srec
     const uint16_t *cols = nullptr;    // nnz offsets from the super-row's base, padded to a whole load
     const uint16_t *rend = nullptr;    // n row ends, from the super-row's first entry
+    // the union pattern's, for the adjoint of a nonsymmetric pattern (nullptr: general walk)
+    const WinRec *urec = nullptr;      // r0, first U entry, rows, U entries, base
+    const uint16_t *ucols = nullptr;   // nu offsets, padded to a whole load
+    const uint16_t *xend = nullptr;    // n ends of the rows' extras, from the super-row's first extra
 };
 
 // Device arrays of one CSR-k matrix.
@@ -146,6 +150,8 @@ struct MatDesc {
     int64_t nu;
     const uint16_t *wcols;  // WinArrays of A' (batches whose matrices all have them)
     const uint16_t *wrend;
+    const uint16_t *wucols;  // their union's, where the pattern is nonsymmetric
+    const uint16_t *wxend;
 };
 
 // Kernel-shape knobs: lanes per row in the reduction, wavefronts per workgroup.
@@ -166,6 +172,10 @@ hipError_t spmv_plain(const Arrays &a, csrk_dtype store, const void *vals, const
                       Shape s, hipStream_t st);
 hipError_t adjoint(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
                    void *gv, int nrhs, Shape s, hipStream_t st);
+// adjoint with both outputs and one right-hand side by the window walk: a.win.rec
+// set and, for a nonsymmetric pattern, a.win.urec.
+hipError_t adjoint_win(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
+                       void *gv, Shape s, hipStream_t st);
 // vals_t[p] = vals[t_src[p]]: the values in A'^T order.
 hipError_t transpose_values(const Arrays &a, csrk_dtype store, const void *vals, void *vals_t, hipStream_t st);
 // out[p] = vals[idx[p]] (0 where idx[p] < 0) for p < count, storage type `store`.
@@ -194,9 +204,18 @@ hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *b
 // accumulation runs the fused-only kernel).
 // `brec_u`: per item, the same slots' union-pattern records (for matrices
 // with uni set; other slots repeat brec).
+// `wrec`, `wrec_u`: the same slots' window records, of A' and of what the
+// adjoint streams (A' itself or the union), when every matrix has them.
 hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *brec, const SrRec *brec_u,
-                         int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool ind,
+                         const WinRec *wrec, const WinRec *wrec_u, int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool ind,
                          bool vec, bool all_sym, bool both, hipStream_t st);
+
+// batch_adjoint's window walk (one right-hand side, both outputs), and the
+// workgroups per CU it can keep resident.
+hipError_t batch_adjoint_win(const MatDesc *descs, const int2 *items, const WinRec *wrec, const WinRec *wrec_u,
+                             int32_t stride, int32_t nitems, csrk_dtype store, Shape s, int grid, bool ind,
+                             hipStream_t st);
+int batch_adjoint_win_occupancy(csrk_dtype store, Shape s, bool ind);
 
 // Workgroups per CU the batched kernels can keep resident (for sizing the grid).
 int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adjoint, bool ind, bool vec, bool all_sym,

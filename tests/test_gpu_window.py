@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+from oracle import adjoint as OA  # noqa: E402
 from oracle import precision as OP  # noqa: E402
 from paper_2203_05096_amd.matrix import CsrkBatch, CsrkMatrix  # noqa: E402
 
@@ -61,20 +62,52 @@ CASES = {
 }
 
 
+def check_adjoint(M, A, x, g, B, vals):
+    """Both gradients (alone and batched): grad_x within 1e-12 (FP64) or gamma_c(2^-24) of the oracle's, c a column's
+    entries; grad_vals, one rounded product per entry, equal to it."""
+    store = M.store
+    xd, gd = to_dev(x, DT[store]), to_dev(g, DT[store])
+    gx, gv = M.adjoint(xd, gd, vals=vals)
+    bx, bv = B.adjoint([xd, xd], [gd, gd], vals=None if vals is None else [vals, vals])
+    torch.cuda.synchronize()
+    ref = OA.grad_x(A.row_ptr, A.col_idx, A.vals, g)
+    scale = OA.grad_x(A.row_ptr, A.col_idx, np.abs(A.vals), np.abs(g))
+    c = np.maximum(np.bincount(A.col_idx, minlength=A.n), 1)
+    beta = 1e-12 if store == "f64" else OP.gamma(c, 2.0 ** -24)
+    for out in (gx, bx[0]):
+        assert np.all(np.abs(out.double().cpu().numpy() - ref) <= beta * scale)
+    refv = OA.grad_vals(A.row_ptr, A.col_idx, x, g)
+    refv = refv if store == "f64" else refv.astype(np.float32).astype(np.float64)
+    assert np.array_equal(gv.double().cpu().numpy(), refv)
+    assert torch.equal(bx[0], bx[1]) and torch.equal(bv[0], gv) and torch.equal(bv[1], gv)
+
+
+def symmetrised(A):
+    import scipy.sparse as sp
+    P = sp.csr_matrix((np.ones(A.nnz), A.col_idx, A.row_ptr), shape=(A.n, A.n))
+    P = (P + P.T).tocsr()
+    P.sort_indices()
+    return CsrInput("sym", A.n, P.indptr.astype(np.int32), P.indices.astype(np.int32),
+                    np.random.default_rng(7).uniform(-1, 1, P.nnz), {})
+
+
 def check(A, srs, store, waves):
     A.vals = OP.stored_values(A.vals, store)
     M = CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store,
                             params=params(srs, 3, lanes=2, waves=waves, reorder="none"))
-    x = np.random.default_rng(1).uniform(-1, 1, A.n).astype(np.float32).astype(np.float64)
+    x, g = np.random.default_rng(1).uniform(-1, 1, (2, A.n)).astype(np.float32).astype(np.float64)
     xd = to_dev(x, DT[store])
     y = M.spmv(xd)
     y2 = M.spmv(xd, vals=M.values())
     B = CsrkBatch([M, M])
     yb = B.spmv([xd, xd])
     torch.cuda.synchronize()
-    perm = np.arange(A.n)
-    check_forward(y.double().cpu().numpy(), A, x, perm, store, False, label="window")
-    assert torch.equal(y, y2) and torch.equal(y, yb[0]) and torch.equal(y, yb[1])
+    # the general walk sums long rows in another order alone than batched: each against the oracle
+    for out in (y, yb[0]):
+        check_forward(out.double().cpu().numpy(), A, x, np.arange(A.n), store, False, label="window")
+    assert torch.equal(y, y2) and torch.equal(yb[0], yb[1])
+    for vals in (None, M.values()):
+        check_adjoint(M, A, x, g, B, vals)
     B.close()
     M.close()
 
@@ -83,8 +116,9 @@ def check(A, srs, store, waves):
 @pytest.mark.parametrize("name", list(CASES))
 def test_window_edges(name, store):
     make, srs = CASES[name]
-    say("window", name, store)
-    check(make(), srs, store, waves=2)
+    for A in (make(), symmetrised(make())):
+        say("window", name, store, A.name)
+        check(A, srs, store, waves=2)
 
 
 @pytest.mark.parametrize("gap", [65535, 65536])
@@ -93,3 +127,20 @@ def test_window_column_span(gap, store):
     """Column offsets up to 65535 are 16-bit; one more and the general walk takes the matrix."""
     say("window span", gap, store)
     check(wide(70001, 16, gap), 16, store, waves=4)
+
+
+def band(n, drop, seed=5):
+    """A band of nine with entries dropped: nonsymmetric, short extras per row."""
+    rng = np.random.default_rng(seed)
+    rows = [[j for j in range(max(0, i - 4), min(n, i + 5)) if j == i or rng.random() >= drop] for i in range(n)]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    return CsrInput("band", n, rp, ci, rng.uniform(-1, 1, len(ci)), {})
+
+
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("srs,drop", [(40, 0.1), (48, 0.5), (17, 0.3), (8, 0.2), (3, 0.1)])
+def test_window_union(srs, drop, store):
+    """Nonsymmetric patterns whose union fits the window, every number of lanes per row."""
+    say("window union", srs, drop, store)
+    check(band(1203, drop), srs, store, waves=3)
