@@ -59,6 +59,8 @@ struct csrk_matrix {
     // the same of its union pattern (nonsymmetric A')
     csrk::dev::WinRec *d_wrec_u = nullptr;
     uint16_t *d_wucols = nullptr, *d_wxend = nullptr;
+    int32_t win_lanes = 0;  // WinArrays::lanes
+    int32_t max_union = 0;  // most union entries of a super-row
 };
 
 struct csrk_batch_s {
@@ -72,6 +74,7 @@ struct csrk_batch_s {
     // the same slots' window records, when every matrix has them: of A', and of what its adjoint streams
     // (the union pattern's where A' is nonsymmetric)
     csrk::dev::WinRec *d_bwrec = nullptr, *d_bwrec_u = nullptr;
+    csrk::dev::BatchWin win;  // those and their LDS entries, as the launches take them
     int32_t brec_stride = 1;
     // Descriptor tables on the device (forward, adjoint) and the host copies
     // they were written from; a call re-uploads only when its pointers change.
@@ -188,6 +191,9 @@ void finish_host(csrk_matrix *h, const int32_t *row_ptr, const int32_t *col_idx,
     h->trans = csrk::transpose_index(h->n, h->row_ptr, h->col_idx);
     h->uni = csrk::union_index(h->n, h->row_ptr, h->col_idx, h->sr_ptr, h->trans, csrk::dev::kUnionRows,
                                csrk::dev::kUnionWindow);
+    h->max_union = 0;
+    for (size_t s = 0; s < h->uni.sr_begin.size(); ++s)
+        h->max_union = std::max(h->max_union, h->uni.sr_end[s] - h->uni.sr_begin[s]);
     h->max_row_any = 0;
     for (int32_t i = 0; i < h->n; ++i) {
         h->max_row_any = std::max(h->max_row_any, h->row_ptr[size_t(i) + 1] - h->row_ptr[size_t(i)]);
@@ -236,6 +242,9 @@ csrk_params resolve_params(int32_t n, int64_t nnz, const csrk_params *p) {
     return q;
 }
 
+// LDS entries for windows of at most `entries` entries from the 16-byte boundary before them.
+int32_t window_cap(int32_t entries) { return (entries + 7 + 7) / 8 * 8; }
+
 csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     csrk::dev::Arrays a;
     a.n = h->n;
@@ -275,6 +284,9 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     a.win.urec = h->d_wrec_u;
     a.win.ucols = h->d_wucols;
     a.win.xend = h->d_wxend;
+    a.win.cap = window_cap(h->max_sr_nnz);
+    a.win.ucap = window_cap(h->max_union);
+    a.win.lanes = h->win_lanes;
     return a;
 }
 
@@ -319,18 +331,20 @@ std::vector<int32_t> long_rows_of(const std::vector<int32_t> &rp) {
     return out;
 }
 
-// Whether the window walk can take the matrix, by its rows and entries (see
-// csrk::dev::kWinRows): the longest row must fit kWinMaxBatches batches of the
-// lanes that the fullest super-row leaves to each row.
-bool window_fits(const csrk_matrix *h) {
+// Lanes per row of the window walk, or 0 when its rows and entries rule the
+// matrix out (see csrk::dev::kWinRows): the most lanes that still walk every
+// row of a super-row at once.  Measured on the stencils (us, forward): 16 rows
+// of 27 entries, BF16, 4 lanes each 20.5, 2 lanes 23.6, 1 lane 32.6; 64 rows of
+// 7, FP64, 1 lane 28.4, 2 lanes (two passes) 30.1, 4 lanes 35.4.
+int32_t window_lanes(const csrk_matrix *h) {
     using namespace csrk::dev;
-    if (h->nnz == 0) return false;
+    if (h->nnz == 0) return 0;
     int32_t rows = 1;
     for (size_t s = 0; s + 1 < h->sr_ptr.size(); ++s) rows = std::max(rows, h->sr_ptr[s + 1] - h->sr_ptr[s]);
-    if (rows > kWinRows || h->max_sr_nnz > kWinEntries) return false;
+    if (rows > kWinRows || h->max_sr_nnz > kWinEntries) return 0;
     int32_t lanes = 1;
     while (lanes < kWinMaxLanes && rows * lanes * 2 <= kWinRows) lanes *= 2;
-    return h->max_row_any <= kWinMaxBatches * 8 * lanes;
+    return h->max_row_any <= kWinMaxBatches * 8 * lanes ? lanes : 0;
 }
 
 // One window layout (csrk::dev::window_layout) of `entries` entries: allocates
@@ -358,7 +372,8 @@ void build_window(const csrk_matrix *h, const csrk::dev::SrRec *srec, int64_t en
 // Builds the window layouts of A' and of its union pattern from the uploaded
 // arrays (upload calls it last; the launch stream is the default one).
 void upload_window(csrk_matrix *h) {
-    if (!window_fits(h)) return;
+    h->win_lanes = window_lanes(h);
+    if (!h->win_lanes) return;
     build_window(h, h->d_srec, h->nnz, h->d_col_idx, h->d_row_ptr, h->d_wrec, h->d_wcols, h->d_wrend);
     if (h->d_wrec && h->d_srec_u)
         build_window(h, h->d_srec_u, h->nu, h->d_u_col, h->d_erow_ptr, h->d_wrec_u, h->d_wucols, h->d_wxend);
@@ -1036,7 +1051,17 @@ void batch_windows(csrk_batch bt, size_t nitems) {
         return out;
     };
     bt->d_bwrec = gather([](const csrk_matrix *h) { return h->d_wrec; });
-    if (bt->d_bwrec) bt->d_bwrec_u = gather([](const csrk_matrix *h) { return h->trans.symmetric ? h->d_wrec : h->d_wrec_u; });
+    if (!bt->d_bwrec) return;
+    bt->d_bwrec_u = gather([](const csrk_matrix *h) { return h->trans.symmetric ? h->d_wrec : h->d_wrec_u; });
+    bt->win.rec = bt->d_bwrec;
+    bt->win.urec = bt->d_bwrec_u;
+    bt->win.sym = bt->all_sym;
+    bt->win.lanes = bt->handles[0]->win_lanes;
+    for (const csrk_matrix *h : bt->handles) {
+        if (h->win_lanes != bt->win.lanes) bt->win.lanes = 0;
+        bt->win.cap = std::max(bt->win.cap, window_cap(h->max_sr_nnz));
+        bt->win.ucap = std::max(bt->win.ucap, window_cap(h->trans.symmetric ? h->max_sr_nnz : h->max_union));
+    }
 }
 
 }  // namespace
@@ -1148,6 +1173,7 @@ csrk::dev::MatDesc *upload_descs(csrk_batch b, int which, const void *const *val
         m.wrend = h->d_wrend;
         m.wucols = h->d_wucols;
         m.wxend = h->d_wxend;
+        m.wlanes = h->win_lanes;
         if (which == 1 && h->d_srec_u) {
             m.uni = 1;
             m.u_col = a.u_col;
@@ -1194,11 +1220,10 @@ bool all_aligned16(std::initializer_list<const void *const *> arrays, size_t cou
 // range and the L2 hit rate fell to about a third).  With blocks_per_cu > 0
 // (autotuner), the grid is at least that many workgroups per CU, each taking
 // a contiguous range of items.
-int batch_grid(csrk_batch b, int nrhs, bool adj, bool ind, bool vec, bool both) {
+int batch_grid(csrk_batch b, int nrhs, bool adj, bool ind, bool vec, bool both, const csrk::dev::BatchWin &win) {
     if (b->blocks_per_cu == 0) return std::max(1, b->nitems);
     const int per_cu = std::max(b->blocks_per_cu, csrk::dev::batch_occupancy(b->store, nrhs, b->shape, adj, ind, vec,
-                                                                              b->all_sym, both,
-                                                                              (adj ? b->d_bwrec_u : b->d_bwrec) != nullptr));
+                                                                              b->all_sym, both, win));
     const int64_t g = int64_t(b->cus) * per_cu;
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(g, b->nitems)));
 }
@@ -1218,9 +1243,9 @@ csrk_status csrk_batch_spmv(csrk_batch b, const void *const *vals, const void *c
         hipStream_t st = static_cast<hipStream_t>(stream);
         csrk::dev::MatDesc *descs = upload_descs(b, 0, vals, x, y, nullptr, nullptr, nullptr, st);
         const bool vec = all_aligned16({x, reinterpret_cast<const void *const *>(y)}, b->handles.size());
-        hip_check(csrk::dev::batch_forward(descs, b->d_items, b->d_brec, b->d_bwrec, b->brec_stride, b->nitems,
+        hip_check(csrk::dev::batch_forward(descs, b->d_items, b->d_brec, b->win, b->brec_stride, b->nitems,
                                            b->store, nrhs, b->shape,
-                                           batch_grid(b, nrhs, false, false, vec, false), vec, st),
+                                           batch_grid(b, nrhs, false, false, vec, false, b->win), vec, st),
                   "csrk_batch_spmv launch");
         return CSRK_OK;
     });
@@ -1247,10 +1272,11 @@ csrk_status csrk_batch_spmv_adjoint(csrk_batch b, const void *const *vals, const
         bool whole = both;
         for (size_t i = 0; whole && i < b->handles.size(); ++i)
             whole = b->handles[i]->n == 0 || (grad_x[i] && grad_vals[i]);
-        hip_check(csrk::dev::batch_adjoint(descs, b->d_items, b->d_brec, b->d_brec_u, b->d_bwrec,
-                                           whole ? b->d_bwrec_u : nullptr, b->brec_stride, b->nitems, b->store, nrhs,
-                                           b->shape,
-                                           batch_grid(b, nrhs, true, ind, vec, both), ind, vec, b->all_sym, both, st),
+        const csrk::dev::BatchWin win = whole ? b->win : csrk::dev::BatchWin{};
+        hip_check(csrk::dev::batch_adjoint(descs, b->d_items, b->d_brec, b->d_brec_u, win, b->brec_stride, b->nitems,
+                                           b->store, nrhs, b->shape,
+                                           batch_grid(b, nrhs, true, ind, vec, both, win), ind, vec, b->all_sym, both,
+                                           st),
                   "csrk_batch_spmv_adjoint launch");
         return CSRK_OK;
     });

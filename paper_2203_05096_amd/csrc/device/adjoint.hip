@@ -111,6 +111,8 @@ hipError_t adjoint(const Arrays &a, csrk_dtype store, const void *vals, const vo
     if (a.nssr == 0) return hipSuccess;
     if (nrhs == 1 && gx && gv && a.win.rec && (a.sym || a.win.urec))
         return adjoint_win(a, store, vals, x, g, gx, gv, s, st);
+    if (nrhs > 1 && gv && a.win.rec && win_block(store, nrhs) && (!gx || a.sym || a.win.urec))
+        return adjoint_win_mrhs(a, store, vals, x, g, gx, gv, nrhs, s, st);
     const int block = s.waves * kWave;
     // Values passed by the caller are reached through the transposed map (the
     // union's source map on the union path); the handle's own values use its

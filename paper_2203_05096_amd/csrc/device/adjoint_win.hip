@@ -7,7 +7,7 @@ namespace dev {
 
 namespace {
 
-template <typename VT, bool IND, bool UNI>
+template <typename VT, int LL, bool IND, bool UNI>
 __global__ void __launch_bounds__(1024) k_adjoint_win(WinArrays win, int32_t stride, const int32_t *__restrict__ src,
                                                       const VT *__restrict__ vals,
                                                       const typename Store<VT>::X *__restrict__ x,
@@ -27,17 +27,18 @@ __global__ void __launch_bounds__(1024) k_adjoint_win(WinArrays win, int32_t str
         const WinRec rec = win.rec[slot];
         if (rec.rows() == 0) break;
         if constexpr (UNI)
-            win_adjoint<VT, IND, true>(rec, win.urec[slot], win.rend, win.xend, win.ucols, src, vals, x, g, gx, gv,
+            win_adjoint<VT, LL, IND, true>(rec, win.urec[slot], win.rend, win.xend, win.ucols, src, vals, x, g, gx, gv,
                                        nnz, lds, lane);
         else
-            win_adjoint<VT, IND, false>(rec, rec, win.rend, nullptr, win.cols, src, vals, x, g, gx, gv, nnz, lds,
+            win_adjoint<VT, LL, IND, false>(rec, rec, win.rend, nullptr, win.cols, src, vals, x, g, gx, gv, nnz, lds,
                                         lane);
     }
 }
 
-// Batched: items and XCD order as in k_batch_forward.  A matrix takes the
-// union form where its pattern is nonsymmetric (its descriptor's uni).
-template <typename VT, bool IND>
+// Batched: items and XCD order as in k_batch_forward; LL as in
+// k_batch_forward_win.  SYM: every pattern is symmetric; otherwise a matrix
+// takes the union form where its own is not (its descriptor's uni).
+template <typename VT, int LL, bool IND, bool SYM>
 __global__ void __launch_bounds__(1024) k_batch_adjoint_win(const MatDesc *__restrict__ descs,
                                                             const int2 *__restrict__ items,
                                                             const WinRec *__restrict__ wrec,
@@ -63,23 +64,36 @@ __global__ void __launch_bounds__(1024) k_batch_adjoint_win(const MatDesc *__res
             const int64_t slot = int64_t(it) * stride + w;
             const WinRec rec = wrec[slot];
             if (rec.rows() == 0) break;
-            if (d.uni)
-                win_adjoint<VT, IND, true>(rec, wrec_u[slot], rend, global_ptr(d.wxend), global_ptr(d.wucols),
-                                           global_ptr(d.u_src),
-                                           global_ptr(static_cast<const VT *>(IND ? d.vals : d.u_vals)), x, g, gx, gv,
-                                           d.nu, lds, lane);
+            auto go = [&](auto lc) {
+                constexpr int L = decltype(lc)::value;
+                if constexpr (!SYM) {
+                    if (d.uni) {
+                        win_adjoint<VT, L, IND, true>(rec, wrec_u[slot], rend, global_ptr(d.wxend),
+                                                      global_ptr(d.wucols), global_ptr(d.u_src),
+                                                      global_ptr(static_cast<const VT *>(IND ? d.vals : d.u_vals)), x,
+                                                      g, gx, gv, d.nu, lds, lane);
+                        return;
+                    }
+                }
+                win_adjoint<VT, L, IND, false>(rec, rec, rend, nullptr, global_ptr(d.wcols), global_ptr(d.t_src),
+                                               global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv, d.nnz, lds,
+                                               lane);
+            };
+            if constexpr (LL)
+                go(std::integral_constant<int, LL>{});
             else
-                win_adjoint<VT, IND, false>(rec, rec, rend, nullptr, global_ptr(d.wcols), global_ptr(d.t_src),
-                                            global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv, d.nnz, lds,
-                                            lane);
+                by_win_lanes_dev(d.wlanes, go);
         }
     }
 }
 
+// Calls f(VT{}, integral_constant<LL>, bool_constant<IND>, bool_constant<SYM>).
 template <typename F>
-hipError_t by_store_ind(csrk_dtype store, bool ind, F &&f) {
-    return by_dtype(store, [&](auto vt) -> hipError_t {
-        return ind ? f(vt, std::true_type{}) : f(vt, std::false_type{});
+hipError_t by_adj_win(csrk_dtype store, int lanes, bool ind, bool sym, F &&f) {
+    return by_batch_win(store, lanes, [&](auto vt, auto lc) -> hipError_t {
+        if (ind)
+            return sym ? f(vt, lc, std::true_type{}, std::true_type{}) : f(vt, lc, std::true_type{}, std::false_type{});
+        return sym ? f(vt, lc, std::false_type{}, std::true_type{}) : f(vt, lc, std::false_type{}, std::false_type{});
     });
 }
 
@@ -88,45 +102,46 @@ hipError_t by_store_ind(csrk_dtype store, bool ind, F &&f) {
 hipError_t adjoint_win(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
                        void *gv, Shape s, hipStream_t st) {
     if (a.nssr == 0) return hipSuccess;
-    return by_store_ind(store, vals != nullptr, [&](auto vt, auto ic) -> hipError_t {
+    return by_adj_win(store, a.win.lanes, vals != nullptr, a.sym, [&](auto vt, auto lc, auto ic, auto sc) -> hipError_t {
         using VT = decltype(vt);
         using X = typename Store<VT>::X;
         using A = typename Store<VT>::A;
-        constexpr bool IND = decltype(ic)::value;
-        const dim3 grid(a.split_adj.width * kXcds), block(s.waves * kWave);
-        const size_t lds = size_t(s.waves) * win_adjoint_lds<VT>();
-        if (a.sym)
-            hipLaunchKernelGGL((k_adjoint_win<VT, IND, false>), grid, block, lds, st, a.win, a.srec_stride, a.t_src,
-                               static_cast<const VT *>(IND ? vals : a.vals_t), static_cast<const X *>(x),
-                               static_cast<const X *>(g), static_cast<X *>(gx), static_cast<A *>(gv), a.nnz,
-                               a.split_adj);
-        else
-            hipLaunchKernelGGL((k_adjoint_win<VT, IND, true>), grid, block, lds, st, a.win, a.srec_stride, a.u_src,
-                               static_cast<const VT *>(IND ? vals : a.u_vals), static_cast<const X *>(x),
-                               static_cast<const X *>(g), static_cast<X *>(gx), static_cast<A *>(gv), a.nu,
-                               a.split_adj);
-        return hipGetLastError();
+        constexpr int LL = decltype(lc)::value;
+        constexpr bool IND = decltype(ic)::value, SYM = decltype(sc)::value;
+        if constexpr (LL == 0) {
+            return hipErrorInvalidValue;  // batches only
+        } else {
+            hipLaunchKernelGGL((k_adjoint_win<VT, LL, IND, !SYM>), dim3(a.split_adj.width * kXcds),
+                               dim3(s.waves * kWave), size_t(s.waves) * win_adjoint_lds<VT>(), st, a.win, a.srec_stride,
+                               SYM ? a.t_src : a.u_src,
+                               static_cast<const VT *>(IND ? vals : SYM ? a.vals_t : a.u_vals),
+                               static_cast<const X *>(x), static_cast<const X *>(g), static_cast<X *>(gx),
+                               static_cast<A *>(gv), SYM ? a.nnz : a.nu, a.split_adj);
+            return hipGetLastError();
+        }
     });
 }
 
-hipError_t batch_adjoint_win(const MatDesc *descs, const int2 *items, const WinRec *wrec, const WinRec *wrec_u,
-                             int32_t stride, int32_t nitems, csrk_dtype store, Shape s, int grid, bool ind,
-                             hipStream_t st) {
-    return by_store_ind(store, ind, [&](auto vt, auto ic) -> hipError_t {
+hipError_t batch_adjoint_win(const MatDesc *descs, const int2 *items, const BatchWin &win, int32_t stride,
+                             int32_t nitems, csrk_dtype store, Shape s, int grid, bool ind, hipStream_t st) {
+    return by_adj_win(store, win.lanes, ind, win.sym, [&](auto vt, auto lc, auto ic, auto sc) -> hipError_t {
         using VT = decltype(vt);
-        hipLaunchKernelGGL((k_batch_adjoint_win<VT, decltype(ic)::value>), dim3(grid), dim3(s.waves * kWave),
-                           size_t(s.waves) * win_adjoint_lds<VT>(), st, descs, items, wrec, wrec_u, stride, nitems);
+        hipLaunchKernelGGL((k_batch_adjoint_win<VT, decltype(lc)::value, decltype(ic)::value, decltype(sc)::value>),
+                           dim3(grid), dim3(s.waves * kWave), size_t(s.waves) * win_adjoint_lds<VT>(), st, descs, items,
+                           win.rec, win.urec, stride, nitems);
         return hipGetLastError();
     });
 }
 
-int batch_adjoint_win_occupancy(csrk_dtype store, Shape s, bool ind) {
+int batch_adjoint_win_occupancy(csrk_dtype store, const BatchWin &win, Shape s, bool ind) {
     int blocks = 1;
-    const hipError_t e = by_store_ind(store, ind, [&](auto vt, auto ic) -> hipError_t {
-        using VT = decltype(vt);
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_batch_adjoint_win<VT, decltype(ic)::value>,
-                                                            s.waves * kWave, size_t(s.waves) * win_adjoint_lds<VT>());
-    });
+    const hipError_t e =
+        by_adj_win(store, win.lanes, ind, win.sym, [&](auto vt, auto lc, auto ic, auto sc) -> hipError_t {
+            using VT = decltype(vt);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &blocks, k_batch_adjoint_win<VT, decltype(lc)::value, decltype(ic)::value, decltype(sc)::value>,
+                s.waves * kWave, size_t(s.waves) * win_adjoint_lds<VT>());
+        });
     return (e != hipSuccess || blocks < 1) ? 1 : blocks;
 }
 

@@ -49,8 +49,9 @@ __global__ void __launch_bounds__(1024) k_batch_forward(const MatDesc *__restric
 }
 
 // Batched forward by the window walk (one right-hand side, every matrix with
-// the window layout); items as in k_batch_forward.
-template <typename VT>
+// the window layout); items as in k_batch_forward.  LL: every matrix's lanes
+// per row, 0 when they differ.
+template <typename VT, int LL>
 __global__ void __launch_bounds__(1024) k_batch_forward_win(const MatDesc *__restrict__ descs,
                                                             const int2 *__restrict__ items,
                                                             const WinRec *__restrict__ wrec, int32_t stride,
@@ -69,9 +70,16 @@ __global__ void __launch_bounds__(1024) k_batch_forward_win(const MatDesc *__res
         for (int32_t w = wave; w < stride; w += nw) {
             const WinRec rec = wrec[int64_t(it) * stride + w];
             if (rec.rows() == 0) break;
-            win_forward<VT>(rec, global_ptr(d.wrend), global_ptr(d.wcols),
-                            global_ptr(static_cast<const VT *>(d.vals)), global_ptr(static_cast<const X *>(d.x)),
-                            global_ptr(static_cast<X *>(d.y)), d.nnz, lds, lane);
+            auto go = [&](auto lc) {
+                win_forward<VT, decltype(lc)::value>(rec, global_ptr(d.wrend), global_ptr(d.wcols),
+                                                     global_ptr(static_cast<const VT *>(d.vals)),
+                                                     global_ptr(static_cast<const X *>(d.x)),
+                                                     global_ptr(static_cast<X *>(d.y)), d.nnz, lds, lane);
+            };
+            if constexpr (LL)
+                go(std::integral_constant<int, LL>{});
+            else
+                by_win_lanes_dev(d.wlanes, go);
         }
     }
 }
@@ -174,16 +182,18 @@ hipError_t by_batch_shape(csrk_dtype store, int nrhs, const Shape &s, bool vec, 
 
 }  // namespace
 
-hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, const WinRec *wrec,
+hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, const BatchWin &win,
                          int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool vec,
                          hipStream_t st) {
     if (nitems == 0) return hipSuccess;
     const int block = s.waves * kWave;
-    if (nrhs == 1 && wrec)
-        return by_dtype(store, [&](auto vt) -> hipError_t {
+    if (nrhs > 1 && win.rec && win_block(store, nrhs))
+        return batch_forward_win_mrhs(descs, items, win, stride, nitems, store, nrhs, s, grid, st);
+    if (nrhs == 1 && win.rec)
+        return by_batch_win(store, win.lanes, [&](auto vt, auto lc) -> hipError_t {
             using VT = decltype(vt);
-            hipLaunchKernelGGL((k_batch_forward_win<VT>), dim3(grid), dim3(block),
-                               size_t(s.waves) * win_forward_lds<VT>(), st, descs, items, wrec, stride, nitems);
+            hipLaunchKernelGGL((k_batch_forward_win<VT, decltype(lc)::value>), dim3(grid), dim3(block),
+                               size_t(s.waves) * win_forward_lds<VT>(), st, descs, items, win.rec, stride, nitems);
             return hipGetLastError();
         });
     return by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
@@ -228,11 +238,13 @@ hipError_t by_adj_variant(bool ind, int path, F &&f) {
 }
 
 hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *brec, const SrRec *brec_u,
-                         const WinRec *wrec, const WinRec *wrec_u, int32_t stride, int32_t nitems, csrk_dtype store,
-                         int nrhs, Shape s, int grid, bool ind, bool vec, bool all_sym, bool both, hipStream_t st) {
+                         const BatchWin &win, int32_t stride, int32_t nitems, csrk_dtype store, int nrhs,
+                         Shape s, int grid, bool ind, bool vec, bool all_sym, bool both, hipStream_t st) {
     if (nitems == 0) return hipSuccess;
-    if (nrhs == 1 && both && wrec_u)
-        return batch_adjoint_win(descs, items, wrec, wrec_u, stride, nitems, store, s, grid, ind, st);
+    if (nrhs == 1 && win.urec)
+        return batch_adjoint_win(descs, items, win, stride, nitems, store, s, grid, ind, st);
+    if (nrhs > 1 && win.urec && win_block(store, nrhs))
+        return batch_adjoint_win_mrhs(descs, items, win, stride, nitems, store, nrhs, s, grid, ind, st);
     const int block = s.waves * kWave;
     const int path = adj_path(nrhs, all_sym, both);
     return by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
@@ -254,18 +266,22 @@ hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *b
 }
 
 int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adj, bool ind, bool vec, bool all_sym, bool both,
-                    bool win) {
+                    const BatchWin &win) {
     int blocks = 1;
     const int block = s.waves * kWave;
-    if (!adj && nrhs == 1 && win) {
-        const hipError_t e = by_dtype(store, [&](auto vt) -> hipError_t {
+    if (nrhs > 1 && win_block(store, nrhs)) {
+        if (adj && win.urec) return batch_adjoint_win_mrhs_occupancy(store, nrhs, win, s, ind);
+        if (!adj && win.rec) return batch_forward_win_mrhs_occupancy(store, nrhs, win, s);
+    }
+    if (!adj && nrhs == 1 && win.rec) {
+        const hipError_t e = by_batch_win(store, win.lanes, [&](auto vt, auto lc) -> hipError_t {
             using VT = decltype(vt);
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_batch_forward_win<VT>, block,
-                                                                size_t(s.waves) * win_forward_lds<VT>());
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_batch_forward_win<VT, decltype(lc)::value>,
+                                                                block, size_t(s.waves) * win_forward_lds<VT>());
         });
         return (e != hipSuccess || blocks < 1) ? 1 : blocks;
     }
-    if (adj && nrhs == 1 && both && win) return batch_adjoint_win_occupancy(store, s, ind);
+    if (adj && nrhs == 1 && win.urec) return batch_adjoint_win_occupancy(store, win, s, ind);
     const hipError_t e = by_batch_shape(store, nrhs, s, vec, [&](auto vt, auto vc, auto lc) -> hipError_t {
         using VT = decltype(vt);
         constexpr int VX = decltype(vc)::value, LL = decltype(lc)::value;

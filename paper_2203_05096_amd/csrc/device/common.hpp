@@ -125,6 +125,35 @@ __device__ __forceinline__ T group_sum(T v) {
     return v;
 }
 
+// v of another lane of the same row of 16 (DPP control CTRL), without a trip
+// through LDS.
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_lane(T v) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "");
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+    } else {
+        typedef int I2 __attribute__((ext_vector_type(2)));
+        I2 w = __builtin_bit_cast(I2, v);
+        w[0] = __builtin_amdgcn_mov_dpp(w[0], CTRL, 0xf, 0xf, true);
+        w[1] = __builtin_amdgcn_mov_dpp(w[1], CTRL, 0xf, 0xf, true);
+        return __builtin_bit_cast(T, w);
+    }
+}
+
+// Sum over aligned groups of W <= 16 lanes (all active), from the nearest lanes
+// outwards: xor 1 and xor 2 within the quad, then the mirrored quad and the
+// mirrored half of the row, whose lanes already hold equal sums.
+template <int W, typename T>
+__device__ __forceinline__ T row_sum(T v) {
+    static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16, "");
+    if constexpr (W >= 2) v += dpp_lane<0xB1>(v);   // quad_perm 1,0,3,2
+    if constexpr (W >= 4) v += dpp_lane<0x4E>(v);   // quad_perm 2,3,0,1
+    if constexpr (W >= 8) v += dpp_lane<0x141>(v);  // row_half_mirror
+    if constexpr (W >= 16) v += dpp_lane<0x140>(v); // row_mirror
+    return v;
+}
+
 // Products of one window staged in LDS at their offset from the window's
 // 16-byte-aligned start: lane l's V products of step u go to
 // buf[u * 64 * V + l * V ..], one aligned vector write per lane and step (no
@@ -2176,6 +2205,11 @@ void by_adapt(bool adapt, F &&f) {
         }
     }
     f(std::false_type{});
+}
+
+// Whether a block of nrhs columns fits the window walk's 32-bit row offsets.
+inline bool win_block(csrk_dtype store, int nrhs) {
+    return int64_t(nrhs) * (store == CSRK_F64 ? 8 : 4) <= kWinBlockBytes;
 }
 
 inline int grid_for(int64_t work, int block) {

@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(1024) k_spmv_csrk_dot(const SrRec *__restrict_
 
 // The product by the window walk (every super-row one window of 16-bit
 // columns); with DOT also the partial inner products of k_spmv_csrk_dot.
-template <typename VT, bool DOT>
+template <typename VT, int LL, bool DOT>
 __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride, const VT *__restrict__ vals,
                                                    const typename Store<VT>::X *__restrict__ x,
                                                    typename Store<VT>::X *__restrict__ y, int64_t nnz, XcdSplit split,
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride
         for (int32_t w = wave; w < stride; w += nw) {
             const WinRec rec = win.rec[int64_t(t) * stride + w];
             if (rec.rows() == 0) break;
-            win_forward<VT, DOT>(rec, win.rend, win.cols, vals, x, y, nnz, lds, lane, pdot, &dot);
+            win_forward<VT, LL, DOT>(rec, win.rend, win.cols, vals, x, y, nnz, lds, lane, pdot, &dot);
         }
     }
     if constexpr (DOT) {
@@ -183,17 +183,20 @@ template <typename VT>
 hipError_t launch_win(const Arrays &a, const void *vals, const void *x, void *y, const double *pdot, double *part,
                       Shape s, hipStream_t st) {
     using X = typename Store<VT>::X;
-    const dim3 grid(a.split_fwd.width * kXcds), block(s.waves * kWave);
-    const size_t lds = size_t(s.waves) * win_forward_lds<VT>();
-    if (part)
-        hipLaunchKernelGGL((k_spmv_win<VT, true>), grid, block, lds, st, a.win, a.srec_stride,
-                           static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
-                           a.split_fwd, pdot, part);
-    else
-        hipLaunchKernelGGL((k_spmv_win<VT, false>), grid, block, lds, st, a.win, a.srec_stride,
-                           static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
-                           a.split_fwd, pdot, part);
-    return hipGetLastError();
+    return by_win_lanes(a.win.lanes, [&](auto lc) -> hipError_t {
+        constexpr int LL = decltype(lc)::value;
+        const dim3 grid(a.split_fwd.width * kXcds), block(s.waves * kWave);
+        const size_t lds = size_t(s.waves) * win_forward_lds<VT>();
+        if (part)
+            hipLaunchKernelGGL((k_spmv_win<VT, LL, true>), grid, block, lds, st, a.win, a.srec_stride,
+                               static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
+                               a.split_fwd, pdot, part);
+        else
+            hipLaunchKernelGGL((k_spmv_win<VT, LL, false>), grid, block, lds, st, a.win, a.srec_stride,
+                               static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
+                               a.split_fwd, pdot, part);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace
@@ -202,6 +205,7 @@ hipError_t spmv(const Arrays &a, csrk_dtype store, const void *vals, const void 
                 hipStream_t st) {
     if (a.nssr == 0) return hipSuccess;
     const int block = s.waves * kWave;
+    if (nrhs > 1 && a.win.rec && win_block(store, nrhs)) return spmv_win_mrhs(a, store, vals, x, y, nrhs, s, st);
     return by_dtype(store, [&](auto vt) -> hipError_t {
         using VT = decltype(vt);
         using X = typename Store<VT>::X;

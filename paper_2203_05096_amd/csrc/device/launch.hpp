@@ -46,10 +46,10 @@ struct __attribute__((aligned(16))) SrRec {
 // Row-lane window walk (device/window.hpp): the matrices whose super-rows all
 // have at most kWave (64) rows, at most kWinEntries entries (a staging window
 // of 512 less one load step of the widest group) and columns within 65536 of
-// each other.  A row is walked by the 1 to kWinMaxLanes lanes that its super-row
-// leaves it, in batches of 8 entries per lane; a matrix with a row that could
-// take more than kWinMaxBatches batches keeps the general walk, which sums
-// such rows by more lanes.
+// each other.  A row is walked by 1 to kWinMaxLanes lanes (WinArrays::lanes) in
+// batches of 8 entries per lane; a matrix with a row longer than
+// kWinMaxBatches batches keeps the general walk, which sums such rows by more
+// lanes.
 constexpr int32_t kWinRows = 64;
 constexpr int32_t kWinEntries = 512 - 8;
 constexpr int32_t kWinSpan = 65536;
@@ -76,7 +76,14 @@ struct WinArrays {
     const WinRec *urec = nullptr;      // r0, first U entry, rows, U entries, base
     const uint16_t *ucols = nullptr;   // nu offsets, padded to a whole load
     const uint16_t *xend = nullptr;    // n ends of the rows' extras, from the super-row's first extra
+    // LDS entries that hold any window from the 16-byte boundary before it (multiples of 8)
+    int32_t cap = 0, ucap = 0;
+    int32_t lanes = 1;  // lanes per row, one right-hand side (a power of two)
 };
+
+// Row bytes that a block of right-hand sides may have for the window walk: the
+// byte offset of a gathered row from the window's first column is 32-bit.
+constexpr int64_t kWinBlockBytes = 65536;
 
 // Device arrays of one CSR-k matrix.
 struct Arrays {
@@ -152,6 +159,8 @@ struct MatDesc {
     const uint16_t *wrend;
     const uint16_t *wucols;  // their union's, where the pattern is nonsymmetric
     const uint16_t *wxend;
+    int32_t wlanes;
+    int32_t pad;
 };
 
 // Kernel-shape knobs: lanes per row in the reduction, wavefronts per workgroup.
@@ -176,6 +185,13 @@ hipError_t adjoint(const Arrays &a, csrk_dtype store, const void *vals, const vo
 // set and, for a nonsymmetric pattern, a.win.urec.
 hipError_t adjoint_win(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
                        void *gv, Shape s, hipStream_t st);
+// The same for blocks of right-hand sides (nrhs >= 2, rows of at most
+// kWinBlockBytes): the product, and the adjoint with both outputs or (gx ==
+// nullptr) grad_vals alone.
+hipError_t spmv_win_mrhs(const Arrays &a, csrk_dtype store, const void *vals, const void *x, void *y, int nrhs,
+                         Shape s, hipStream_t st);
+hipError_t adjoint_win_mrhs(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
+                            void *gv, int nrhs, Shape s, hipStream_t st);
 // vals_t[p] = vals[t_src[p]]: the values in A'^T order.
 hipError_t transpose_values(const Arrays &a, csrk_dtype store, const void *vals, void *vals_t, hipStream_t st);
 // out[p] = vals[idx[p]] (0 where idx[p] < 0) for p < count, storage type `store`.
@@ -193,9 +209,16 @@ hipError_t convert_values(const double *src, void *dst, int64_t count, csrk_dtyp
 // Batched launches: one grid over `nitems` (matrix, super-super-row) items.
 // `vec`: every right-hand-side block pointer is 16-byte aligned.
 // `brec`: per item, `stride` super-row records (SrRec) of its SSR.
-// `wrec`: the same slots' window records when every matrix has the window
-// layout, else nullptr.
-hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, const WinRec *wrec,
+// `win`: the same slots' window records when every matrix has the window
+// layout (rec == nullptr otherwise).
+struct BatchWin {
+    const WinRec *rec = nullptr;   // of A'
+    const WinRec *urec = nullptr;  // of what the adjoint streams: the union where A' is nonsymmetric
+    int32_t cap = 0, ucap = 0;     // WinArrays::cap over all matrices, and over what the adjoint streams
+    int32_t lanes = 0;             // WinArrays::lanes of every matrix, 0 when they differ
+    bool sym = true;               // every pattern is symmetric
+};
+hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *brec, const BatchWin &win,
                          int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool vec, hipStream_t st);
 // `ind`: the descriptors' vals are caller values in CSR-k order (reached
 // through t_src); otherwise they are the handles' transposed copies.
@@ -204,22 +227,29 @@ hipError_t batch_forward(const MatDesc *descs, const int2 *items, const SrRec *b
 // accumulation runs the fused-only kernel).
 // `brec_u`: per item, the same slots' union-pattern records (for matrices
 // with uni set; other slots repeat brec).
-// `wrec`, `wrec_u`: the same slots' window records, of A' and of what the
-// adjoint streams (A' itself or the union), when every matrix has them.
+// `win`: as for batch_forward, rec and urec set when both outputs of every
+// matrix are wanted.
 hipError_t batch_adjoint(const MatDesc *descs, const int2 *items, const SrRec *brec, const SrRec *brec_u,
-                         const WinRec *wrec, const WinRec *wrec_u, int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool ind,
+                         const BatchWin &win, int32_t stride, int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool ind,
                          bool vec, bool all_sym, bool both, hipStream_t st);
 
 // batch_adjoint's window walk (one right-hand side, both outputs), and the
 // workgroups per CU it can keep resident.
-hipError_t batch_adjoint_win(const MatDesc *descs, const int2 *items, const WinRec *wrec, const WinRec *wrec_u,
-                             int32_t stride, int32_t nitems, csrk_dtype store, Shape s, int grid, bool ind,
-                             hipStream_t st);
-int batch_adjoint_win_occupancy(csrk_dtype store, Shape s, bool ind);
+hipError_t batch_adjoint_win(const MatDesc *descs, const int2 *items, const BatchWin &win, int32_t stride,
+                             int32_t nitems, csrk_dtype store, Shape s, int grid, bool ind, hipStream_t st);
+int batch_adjoint_win_occupancy(csrk_dtype store, const BatchWin &win, Shape s, bool ind);
+// The window walks for blocks of right-hand sides, and their occupancies.
+hipError_t batch_forward_win_mrhs(const MatDesc *descs, const int2 *items, const BatchWin &win, int32_t stride,
+                                  int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, hipStream_t st);
+int batch_forward_win_mrhs_occupancy(csrk_dtype store, int nrhs, const BatchWin &win, Shape s);
+hipError_t batch_adjoint_win_mrhs(const MatDesc *descs, const int2 *items, const BatchWin &win, int32_t stride,
+                                  int32_t nitems, csrk_dtype store, int nrhs, Shape s, int grid, bool ind,
+                                  hipStream_t st);
+int batch_adjoint_win_mrhs_occupancy(csrk_dtype store, int nrhs, const BatchWin &win, Shape s, bool ind);
 
 // Workgroups per CU the batched kernels can keep resident (for sizing the grid).
 int batch_occupancy(csrk_dtype store, int nrhs, Shape s, bool adjoint, bool ind, bool vec, bool all_sym,
-                    bool both, bool win);
+                    bool both, const BatchWin &win);
 
 // Bandwidth probes (device/util.hip): a streaming read of `bytes` (a multiple of
 // 16, 16-byte aligned) writing one word per workgroup to part[0 .. probe_grid()),

@@ -6,8 +6,10 @@
 //
 // A wavefront streams one super-row's values and column offsets with 16-byte
 // (8-, 4-byte) loads straight from its record into LDS, as they are; then LL
-// lanes per row walk the row's entries in LDS, gather x and sum in registers
-// (by_rows: all rows of the super-row at once).
+// lanes per row walk the row's entries in LDS, gather x and sum in registers.
+// LL is the matrix's (window_lanes), a template argument: one body that picks
+// LL per super-row took 72 instead of 60 registers in the FP64 forward, 84
+// instead of 70 in the adjoint, and with them a wavefront per SIMD.
 //
 // What bounds it, and why it is laid out so (one MI355X, three matrices used
 // in turn, us before -> after):
@@ -35,9 +37,15 @@ namespace dev {
 
 namespace {
 
-// Gathers of one lane in flight at once: a 7-point row or a quarter of a
-// 27-point row in one batch (4 measured 2-10% slower on both).
-constexpr int kWinBatch = 8;
+// Gathers of one lane in flight at once.  8 hold a 7-point row or a quarter of
+// a 27-point row (4 measured 2-10% slower on both); 4-byte vectors leave the
+// registers for 12, which takes a 9-point row in one batch (forward, 2D 9-point
+// 1201x999 FP32 18.3 -> 16.1 us; with 8-byte vectors 12 cost the 7-point forward
+// 29.2 -> 32.5 us).
+template <typename X>
+constexpr int win_batch() {
+    return sizeof(X) == 8 ? 8 : 12;
+}
 
 static_assert(kWinEntries <= kStageEntries - 8, "a window must fit the staging area from any 16-byte boundary");
 
@@ -112,29 +120,9 @@ __host__ __device__ constexpr int win_forward_lds() {
     return kStageEntries * int(sizeof(VT) + sizeof(uint16_t));
 }
 
-// Lanes per row for a super-row of `nrows` rows: f(integral_constant<int, LL>)
-// with the largest LL <= kWinMaxLanes that walks all rows at once (uniform
-// over the wavefront).  Measured on the stencils (us, forward): 16 rows of 27
-// entries, BF16, 4 lanes each 20.5, 2 lanes 23.6, 1 lane 32.6; 64 rows of 7,
-// FP64, 1 lane 28.4, 2 lanes (two passes) 30.1, 4 lanes 35.4.
-template <typename F>
-__device__ __forceinline__ void by_rows(int nrows, F &&f) {
-    static_assert(kWinMaxLanes == 16 && kWinRows == kWave, "");
-    if (nrows > 32)
-        f(std::integral_constant<int, 1>{});
-    else if (nrows > 16)
-        f(std::integral_constant<int, 2>{});
-    else if (nrows > 8)
-        f(std::integral_constant<int, 4>{});
-    else if (nrows > 4)
-        f(std::integral_constant<int, 8>{});
-    else
-        f(std::integral_constant<int, 16>{});
-}
-
 // y for the rows of one super-row.  With DOT, the lane that stores y[i] also
 // adds y[i] * pdot[i] (FP64, y as stored) to *dot.
-template <typename VT, bool DOT = false>
+template <typename VT, int LL, bool DOT = false>
 __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *__restrict__ rend16,
                                             const uint16_t *__restrict__ cols, const VT *__restrict__ vals,
                                             const typename Store<VT>::X *__restrict__ x,
@@ -144,7 +132,7 @@ __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *_
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     constexpr int V = Store<VT>::V;
-    constexpr int B = kWinBatch;
+    constexpr int B = win_batch<X>();
     VT *sval = reinterpret_cast<VT *>(lds);
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + kStageEntries * sizeof(VT));
     const int nrows = rec.rows(), nent = rec.entries(), off = rec.e0 & (V - 1);
@@ -154,36 +142,33 @@ __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *_
     win_stage<VT>(w, rec.e0, nent, sval, scol, lane);
     wave_lds_sync();
     const X *xb = x + rec.base;
-    by_rows(nrows, [&](auto lc) {
-        constexpr int LL = decltype(lc)::value;
-        const int rr = lane / LL;
-        const bool act = rr < nrows;
-        const int rend = __shfl(my_end, act ? rr : 0);
-        const int prev = __shfl(my_end, (act && rr > 0) ? rr - 1 : 0);
-        int k = off + (rr > 0 ? prev : 0) + lane % LL;
-        const int ke = act ? off + rend : 0;
-        A acc = 0;
-        while (__any(k < ke)) {
-            X xv[B];
-            A a[B];
+    const int rr = lane / LL;
+    const bool act = rr < nrows;
+    const int rend = __shfl(my_end, act ? rr : 0);
+    const int prev = __shfl(my_end, (act && rr > 0) ? rr - 1 : 0);
+    int k = off + (rr > 0 ? prev : 0) + lane % LL;
+    const int ke = act ? off + rend : 0;
+    A acc = 0;
+    while (__any(k < ke)) {
+        X xv[B];
+        A a[B];
 #pragma unroll
-            for (int j = 0; j < B; ++j) {
-                const bool ok = k + j * LL < ke;
-                const int kk = ok ? k + j * LL : off;
-                const uint32_t c = scol[kk];
-                a[j] = ok ? Store<VT>::widen(sval[kk]) : A(0);
-                xv[j] = ok ? xb[c] : X(0);
-            }
+        for (int j = 0; j < B; ++j) {
+            const bool ok = k + j * LL < ke;
+            const int kk = ok ? k + j * LL : off;
+            const uint32_t c = scol[kk];
+            a[j] = ok ? Store<VT>::widen(sval[kk]) : A(0);
+            xv[j] = ok ? xb[c] : X(0);
+        }
 #pragma unroll
-            for (int j = 0; j < B; ++j) acc += a[j] * A(xv[j]);
-            k += B * LL;
-        }
-        acc = group_sum<LL>(acc);
-        if (act && lane % LL == 0) {
-            y[rec.r0 + rr] = X(acc);
-            if constexpr (DOT) *dot += double(X(acc)) * pdot[rec.r0 + rr];
-        }
-    });
+        for (int j = 0; j < B; ++j) acc += a[j] * A(xv[j]);
+        k += B * LL;
+    }
+    acc = row_sum<LL>(acc);
+    if (act && lane % LL == 0) {
+        y[rec.r0 + rr] = X(acc);
+        if constexpr (DOT) *dot += double(X(acc)) * pdot[rec.r0 + rr];
+    }
     wave_lds_sync();
 }
 
@@ -233,7 +218,7 @@ __device__ __forceinline__ void win_store_gv(const A *__restrict__ sgv, int off,
 // the super-row's union range `ru` holds its A' entries (at a fixed offset, a
 // multiple of 8, from their A' positions) and then its rows' extras, whose ends
 // are xend16; columns, values and src are the union's, `nnz` its entries.
-template <typename VT, bool IND, bool UNI>
+template <typename VT, int LL, bool IND, bool UNI>
 __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, const uint16_t *__restrict__ rend16,
                                             const uint16_t *__restrict__ xend16, const uint16_t *__restrict__ cols,
                                             const int32_t *__restrict__ src, const VT *__restrict__ vals,
@@ -245,7 +230,7 @@ __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, 
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     constexpr int V = Store<VT>::V;
-    constexpr int B = kWinBatch;
+    constexpr int B = win_batch<X>();
     constexpr bool OVER = sizeof(VT) == sizeof(A);
     A *sgv = reinterpret_cast<A *>(lds);
     VT *sval = reinterpret_cast<VT *>(lds + (OVER ? 0 : kStageEntries * sizeof(A)));
@@ -259,56 +244,100 @@ __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, 
     win_stage<VT>(w, ru.e0, ru.entries(), sval, scol, lane);
     wave_lds_sync();
     const X *xb = x + ru.base, *gb = g + ru.base;
-    by_rows(nrows, [&](auto lc) {
-        constexpr int LL = decltype(lc)::value;
-        const int rr = lane / LL;
-        const bool act = rr < nrows;
-        const int at = act ? rr : 0, before = (act && rr > 0) ? rr - 1 : 0;
-        const int rend = __shfl(my_end, at), prev = __shfl(my_end, before);
-        const A gi = __shfl(my_g, at);
-        int k = off + (rr > 0 ? prev : 0) + lane % LL;
-        int ke = act ? off + rend : 0;
-        A acc = 0;
+    const int rr = lane / LL;
+    const bool act = rr < nrows;
+    const int at = act ? rr : 0, before = (act && rr > 0) ? rr - 1 : 0;
+    const int rend = __shfl(my_end, at), prev = __shfl(my_end, before);
+    const A gi = __shfl(my_g, at);
+    int k = off + (rr > 0 ? prev : 0) + lane % LL;
+    int ke = act ? off + rend : 0;
+    A acc = 0;
+    while (__any(k < ke)) {
+        X xv[B], gw[B];
+        uint32_t c[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) c[j] = scol[k + j * LL < ke ? k + j * LL : off];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            xv[j] = gw[j] = X(0);
+            if (k + j * LL < ke) {
+                xv[j] = xb[c[j]];
+                gw[j] = gb[c[j]];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if (k + j * LL < ke) {
+                acc += Store<VT>::widen(sval[k + j * LL]) * A(gw[j]);
+                sgv[k + j * LL] = gi * A(xv[j]);
+            }
+        k += B * LL;
+    }
+    if constexpr (UNI) {
+        constexpr int BX = 2;  // a dropped entry in ten leaves a row about one extra
+        const int xend = __shfl(my_xend, at), xprev = __shfl(my_xend, before);
+        k = off + nent + (rr > 0 ? xprev : 0) + lane % LL;
+        ke = act ? off + nent + xend : 0;
         while (__any(k < ke)) {
-            X xv[B], gw[B];
+            X gw[BX];
 #pragma unroll
-            for (int j = 0; j < B; ++j) {
-                xv[j] = gw[j] = X(0);
-                if (k + j * LL < ke) {
-                    const uint32_t c = scol[k + j * LL];
-                    xv[j] = xb[c];
-                    gw[j] = gb[c];
-                }
-            }
+            for (int j = 0; j < BX; ++j) gw[j] = k + j * LL < ke ? gb[uint32_t(scol[k + j * LL])] : X(0);
 #pragma unroll
-            for (int j = 0; j < B; ++j)
-                if (k + j * LL < ke) {
-                    acc += Store<VT>::widen(sval[k + j * LL]) * A(gw[j]);
-                    sgv[k + j * LL] = gi * A(xv[j]);
-                }
-            k += B * LL;
+            for (int j = 0; j < BX; ++j)
+                if (k + j * LL < ke) acc += Store<VT>::widen(sval[k + j * LL]) * A(gw[j]);
+            k += BX * LL;
         }
-        if constexpr (UNI) {
-            constexpr int BX = 2;  // a dropped entry in ten leaves a row about one extra
-            const int xend = __shfl(my_xend, at), xprev = __shfl(my_xend, before);
-            k = off + nent + (rr > 0 ? xprev : 0) + lane % LL;
-            ke = act ? off + nent + xend : 0;
-            while (__any(k < ke)) {
-                X gw[BX];
-#pragma unroll
-                for (int j = 0; j < BX; ++j) gw[j] = k + j * LL < ke ? gb[uint32_t(scol[k + j * LL])] : X(0);
-#pragma unroll
-                for (int j = 0; j < BX; ++j)
-                    if (k + j * LL < ke) acc += Store<VT>::widen(sval[k + j * LL]) * A(gw[j]);
-                k += BX * LL;
-            }
-        }
-        acc = group_sum<LL>(acc);
-        if (act && lane % LL == 0) gx[ra.r0 + rr] = X(acc);
-    });
+    }
+    acc = row_sum<LL>(acc);
+    if (act && lane % LL == 0) gx[ra.r0 + rr] = X(acc);
     wave_lds_sync();
     win_store_gv<A>(sgv, off, nent, gv + (ra.e0 & ~(V - 1)), lane);
     wave_lds_sync();
+}
+
+// ------------------------------------------------------------------ dispatch
+
+// Calls f(integral_constant<int, LL>) for a matrix's lanes per row.
+template <typename F>
+hipError_t by_win_lanes(int lanes, F &&f) {
+    static_assert(kWinMaxLanes == 16, "");
+    switch (lanes) {
+    case 1:
+        return f(std::integral_constant<int, 1>{});
+    case 2:
+        return f(std::integral_constant<int, 2>{});
+    case 4:
+        return f(std::integral_constant<int, 4>{});
+    case 8:
+        return f(std::integral_constant<int, 8>{});
+    case 16:
+        return f(std::integral_constant<int, 16>{});
+    }
+    return hipErrorInvalidValue;
+}
+
+// The same inside a kernel (a batch whose matrices differ; uniform).
+template <typename F>
+__device__ __forceinline__ void by_win_lanes_dev(int lanes, F &&f) {
+    if (lanes == 1)
+        f(std::integral_constant<int, 1>{});
+    else if (lanes == 2)
+        f(std::integral_constant<int, 2>{});
+    else if (lanes == 4)
+        f(std::integral_constant<int, 4>{});
+    else if (lanes == 8)
+        f(std::integral_constant<int, 8>{});
+    else
+        f(std::integral_constant<int, 16>{});
+}
+
+// Calls f(VT{}, integral_constant<int, LL>) for a batch (LL = 0 where lanes is).
+template <typename F>
+hipError_t by_batch_win(csrk_dtype store, int lanes, F &&f) {
+    return by_dtype(store, [&](auto vt) -> hipError_t {
+        if (lanes == 0) return f(vt, std::integral_constant<int, 0>{});
+        return by_win_lanes(lanes, [&](auto lc) { return f(vt, lc); });
+    });
 }
 
 }  // namespace

@@ -144,3 +144,49 @@ def test_window_union(srs, drop, store):
     """Nonsymmetric patterns whose union fits the window, every number of lanes per row."""
     say("window union", srs, drop, store)
     check(band(1203, drop), srs, store, waves=3)
+
+
+def block(a, store, shift):
+    """The block on the GPU, `shift` elements into its allocation."""
+    raw = torch.empty(a.size + shift, dtype=DT[store], device="cuda")
+    raw[shift:] = to_dev(a, DT[store]).reshape(-1)
+    return raw[shift:].view(a.shape)
+
+
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("nrhs,shift", [(2, 0), (3, 1), (4, 1), (5, 0), (8, 0), (13, 1), (33, 0), (65, 1), (130, 0)])
+@pytest.mark.parametrize("name", ["full", "batches", "lanes2", "lanes4", "lanes16", "tiny", "band"])
+def test_window_blocks(name, nrhs, shift, store):
+    """Blocks of right-hand sides: slices that end off a slice boundary, blocks off 16 bytes, several chunks of columns.
+    Forward and grad_x within the bounds of one column; grad_vals, a sum over the columns, within gamma_nrhs."""
+    make, srs = CASES[name] if name != "band" else (lambda: band(407, 0.2), 24)
+    for A in (make(), symmetrised(make())):
+        say("window blocks", name, nrhs, shift, store, A.name)
+        A.vals = OP.stored_values(A.vals, store)
+        M = CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store,
+                                params=params(srs, 3, lanes=2, waves=2, reorder="none"))
+        X, G = np.random.default_rng(nrhs).uniform(-1, 1, (2, A.n, nrhs)).astype(np.float32).astype(np.float64)
+        x, g = block(X, store, shift), block(G, store, shift)
+        B = CsrkBatch([M, M])
+        for vals in (None, M.values()):
+            two = None if vals is None else [vals, vals]
+            gx, gv = M.adjoint(x, g, vals=vals)
+            only = M.adjoint(x, g, vals=vals, grad_x=False)[1]
+            ys = [M.spmv(x, vals=vals)] + B.spmv([x, x], vals=two)
+            bx, bv = B.adjoint([x, x], [g, g], vals=two)
+            torch.cuda.synchronize()
+            for y in ys:
+                check_forward(y.double().cpu().numpy(), A, X, np.arange(A.n), store, False, label="window block")
+            ref = OA.grad_x(A.row_ptr, A.col_idx, A.vals, G)
+            scale = OA.grad_x(A.row_ptr, A.col_idx, np.abs(A.vals), np.abs(G))
+            c = np.maximum(np.bincount(A.col_idx, minlength=A.n), 1)[:, None]
+            beta = 1e-12 if store == "f64" else OP.gamma(c, 2.0 ** -24)
+            for out in [gx] + bx:
+                assert np.all(np.abs(out.double().cpu().numpy() - ref) <= beta * scale)
+            ref = OA.grad_vals(A.row_ptr, A.col_idx, X, G)
+            scale = OA.grad_vals(A.row_ptr, A.col_idx, np.abs(X), np.abs(G))
+            beta = 1e-12 if store == "f64" else OP.gamma(nrhs, 2.0 ** -24)
+            for out in [gv, only] + bv:
+                assert np.all(np.abs(out.double().cpu().numpy() - ref) <= beta * scale)
+        B.close()
+        M.close()
