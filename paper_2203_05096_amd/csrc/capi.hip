@@ -31,6 +31,10 @@ struct csrk_matrix {
     int32_t max_sr_nnz = 0, max_ssr_rows = 0;
     csrk::Transposed trans;  // index structure of A'^T for the adjoint
     csrk::UnionIndex uni;    // union pattern A' + A'^T of a nonsymmetric A' (ok == false otherwise)
+    csrk::Windows win;       // the launches' windows and groups (the super-rows and super-super-rows if they fit)
+    csrk::UnionIndex win_uni;  // the union pattern by windows, where the super-rows' (uni) does not fit them
+    int32_t max_win_rows = 0, max_win_nnz = 0;
+    const csrk::UnionIndex &launch_union() const { return uni.ok ? uni : win_uni; }
     // device side
     bool on_device = false;
     csrk_dtype store = CSRK_F64;
@@ -60,6 +64,7 @@ struct csrk_matrix {
     csrk::dev::WinRec *d_wrec_u = nullptr;
     uint16_t *d_wucols = nullptr, *d_wxend = nullptr;
     int32_t win_lanes = 0;  // WinArrays::lanes
+    bool interleave = false;  // groups go to the XCDs in turn, not in contiguous ranges (irregular matrices)
     int32_t max_union = 0;  // most union entries of a super-row
 };
 
@@ -169,6 +174,61 @@ T *upload_array(const std::vector<T> &v, const char *what) {
     return d;
 }
 
+// Rows of more entries than this stand alone in a window of a cut super-row:
+// its other rows would wait for the lanes that sum it.
+constexpr int32_t kHeavyRow = 256;
+// Wavefronts per workgroup, at least, for a matrix with long rows: one
+// workgroup computes each, and the longest is what the launch waits for.
+constexpr int32_t kLongRowWaves = 8;
+
+bool has_long_rows(const csrk_matrix *h) { return h->max_row_any > csrk::dev::kLongRow; }
+
+// Lanes per row of the window walk, or 0 when its rows and entries rule the
+// matrix out (see csrk::dev::kWinRows): the most lanes that still walk every
+// row of a super-row at once.  Measured on the stencils (us, forward): 16 rows
+// of 27 entries, BF16, 4 lanes each 20.5, 2 lanes 23.6, 1 lane 32.6; 64 rows of
+// 7, FP64, 1 lane 28.4, 2 lanes (two passes) 30.1, 4 lanes 35.4.
+int32_t window_lanes(const csrk_matrix *h) {
+    using namespace csrk::dev;
+    if (h->nnz == 0) return 0;
+    const int32_t rows = h->max_win_rows;
+    if (rows > kWinRows || h->max_win_nnz > kWinEntries) return 0;
+    int32_t lanes = 1;
+    while (lanes < kWinMaxLanes && rows * lanes * 2 <= kWinRows) lanes *= 2;
+    return h->max_row_any <= kWinMaxBatches * 8 * lanes ? lanes : 0;
+}
+
+// The launches' windows of h (csrk::launch_windows) and the union pattern they
+// carry.  Irregular matrices used to be walked super-row by super-row, one
+// wavefront each: super-rows of up to 2048 entries took four windows in turn.
+// An R-MAT graph of 2^18 rows (mean 8.7, longest row about 10,000 entries):
+// forward 30 us, adjoint 46 us then; see the launch rule at kLongRowWaves.
+void launch_shape(csrk_matrix *h) {
+    using namespace csrk::dev;
+    const int32_t waves = has_long_rows(h) ? std::max(h->params.waves_per_wg, kLongRowWaves) : h->params.waves_per_wg;
+    const std::vector<int32_t> len = csrk::union_lengths(h->n, h->row_ptr, h->col_idx, h->trans);
+    h->win = csrk::launch_windows(h->sr_ptr, h->ssr_ptr, len, kWinRows, kWinEntries, kHeavyRow,
+                                  std::max(h->params.ssrs, waves));
+    if (!h->uni.ok)
+        h->win_uni = csrk::union_index(h->n, h->row_ptr, h->col_idx, h->win.win_ptr, h->trans, kUnionRows, kUnionWindow);
+    const csrk::UnionIndex &u = h->launch_union();
+    h->max_union = h->max_win_rows = h->max_win_nnz = 0;
+    for (size_t s = 0; s < u.sr_begin.size(); ++s) h->max_union = std::max(h->max_union, u.sr_end[s] - u.sr_begin[s]);
+    for (size_t w = 0; w + 1 < h->win.win_ptr.size(); ++w) {
+        const int32_t r0 = h->win.win_ptr[w], r1 = h->win.win_ptr[w + 1];
+        h->max_win_rows = std::max(h->max_win_rows, r1 - r0);
+        h->max_win_nnz = std::max(h->max_win_nnz, h->row_ptr[size_t(r1)] - h->row_ptr[size_t(r0)]);
+    }
+    h->win_lanes = window_lanes(h);
+    h->interleave = h->win_lanes == 0 && h->win.grp_ptr != h->ssr_ptr;
+}
+
+// Where group t's records stand in the tables: in order, or (interleave) so
+// that block t runs it and group t + 1 goes to the next XCD.
+size_t table_row(const csrk_matrix *h, size_t t) {
+    return h->interleave ? size_t(h->split_fwd.b[t % csrk::dev::kXcds]) + t / csrk::dev::kXcds : t;
+}
+
 void finish_host(csrk_matrix *h, const int32_t *row_ptr, const int32_t *col_idx, const double *vals,
                  csrk::Grouping &&gr) {
     csrk::Permuted pm = csrk::permute(h->n, row_ptr, col_idx, vals, gr.perm);
@@ -191,9 +251,6 @@ void finish_host(csrk_matrix *h, const int32_t *row_ptr, const int32_t *col_idx,
     h->trans = csrk::transpose_index(h->n, h->row_ptr, h->col_idx);
     h->uni = csrk::union_index(h->n, h->row_ptr, h->col_idx, h->sr_ptr, h->trans, csrk::dev::kUnionRows,
                                csrk::dev::kUnionWindow);
-    h->max_union = 0;
-    for (size_t s = 0; s < h->uni.sr_begin.size(); ++s)
-        h->max_union = std::max(h->max_union, h->uni.sr_end[s] - h->uni.sr_begin[s]);
     h->max_row_any = 0;
     for (int32_t i = 0; i < h->n; ++i) {
         h->max_row_any = std::max(h->max_row_any, h->row_ptr[size_t(i) + 1] - h->row_ptr[size_t(i)]);
@@ -201,6 +258,7 @@ void finish_host(csrk_matrix *h, const int32_t *row_ptr, const int32_t *col_idx,
             h->max_row_any =
                 std::max(h->max_row_any, h->trans.t_row_ptr[size_t(i) + 1] - h->trans.t_row_ptr[size_t(i)]);
     }
+    launch_shape(h);
 }
 
 // The host keeps an FP64 master copy of the values.  FP32 and BF16 input
@@ -250,7 +308,7 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     a.n = h->n;
     a.nnz = h->nnz;
     a.nsr = static_cast<int32_t>(h->sr_ptr.size()) - 1;
-    a.nssr = static_cast<int32_t>(h->ssr_ptr.size()) - 1;
+    a.nssr = static_cast<int32_t>(h->win.grp_ptr.size()) - 1;
     a.row_ptr = h->d_row_ptr;
     a.col_idx = h->d_col_idx;
     a.sr_ptr = h->d_sr_ptr;
@@ -284,7 +342,7 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     a.win.urec = h->d_wrec_u;
     a.win.ucols = h->d_wucols;
     a.win.xend = h->d_wxend;
-    a.win.cap = window_cap(h->max_sr_nnz);
+    a.win.cap = window_cap(h->max_win_nnz);
     a.win.ucap = window_cap(h->max_union);
     a.win.lanes = h->win_lanes;
     return a;
@@ -294,11 +352,21 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
 // its nonzeros (0 for rows longer than kLongRow, which run elsewhere) plus 1,
 // summed over row_ptr and, when given, a second row pointer array (the
 // adjoint's transposed rows).  Range x ends at the first SSR whose prefix cost
-// reaches x/8 of the total.
+// reaches x/8 of the total.  Irregular matrices cut into windows are dealt to
+// the XCDs group by group instead: their cost per nonzero differs between the
+// dense and the sparse end of the ordering (where columns repeat), and random
+// columns leave an XCD's L2 nothing to share.
 csrk::dev::XcdSplit xcd_split(const csrk_matrix *h, const std::vector<int32_t> &rp,
                               const std::vector<int32_t> *rp2) {
     using csrk::dev::kXcds;
-    const int64_t nssr = int64_t(h->ssr_ptr.size()) - 1;
+    const std::vector<int32_t> &grp = h->win.grp_ptr, &win = h->win.win_ptr;
+    const int64_t nssr = int64_t(grp.size()) - 1;
+    if (h->interleave) {
+        csrk::dev::XcdSplit sp;
+        for (int x = 0; x < kXcds; ++x) sp.b[x + 1] = sp.b[x] + static_cast<int32_t>((nssr - x + kXcds - 1) / kXcds);
+        sp.width = sp.b[1];
+        return sp;
+    }
     std::vector<int64_t> prefix(size_t(nssr) + 1, 0);
     auto row_cost = [](const std::vector<int32_t> &p, int32_t i) -> int64_t {
         const int64_t len = int64_t(p[i + 1]) - p[i];
@@ -306,7 +374,7 @@ csrk::dev::XcdSplit xcd_split(const csrk_matrix *h, const std::vector<int32_t> &
     };
     for (int64_t t = 0; t < nssr; ++t) {
         int64_t c = 0;
-        for (int32_t i = h->sr_ptr[h->ssr_ptr[t]]; i < h->sr_ptr[h->ssr_ptr[t + 1]]; ++i)
+        for (int32_t i = win[grp[t]]; i < win[grp[t + 1]]; ++i)
             c += 1 + row_cost(rp, i) + (rp2 ? row_cost(*rp2, i) : 0);
         prefix[t + 1] = prefix[t] + c;
     }
@@ -331,29 +399,13 @@ std::vector<int32_t> long_rows_of(const std::vector<int32_t> &rp) {
     return out;
 }
 
-// Lanes per row of the window walk, or 0 when its rows and entries rule the
-// matrix out (see csrk::dev::kWinRows): the most lanes that still walk every
-// row of a super-row at once.  Measured on the stencils (us, forward): 16 rows
-// of 27 entries, BF16, 4 lanes each 20.5, 2 lanes 23.6, 1 lane 32.6; 64 rows of
-// 7, FP64, 1 lane 28.4, 2 lanes (two passes) 30.1, 4 lanes 35.4.
-int32_t window_lanes(const csrk_matrix *h) {
-    using namespace csrk::dev;
-    if (h->nnz == 0) return 0;
-    int32_t rows = 1;
-    for (size_t s = 0; s + 1 < h->sr_ptr.size(); ++s) rows = std::max(rows, h->sr_ptr[s + 1] - h->sr_ptr[s]);
-    if (rows > kWinRows || h->max_sr_nnz > kWinEntries) return 0;
-    int32_t lanes = 1;
-    while (lanes < kWinMaxLanes && rows * lanes * 2 <= kWinRows) lanes *= 2;
-    return h->max_row_any <= kWinMaxBatches * 8 * lanes ? lanes : 0;
-}
-
 // One window layout (csrk::dev::window_layout) of `entries` entries: allocates
 // and fills rec, cols and ends; leaves them null when some super-row's columns
 // span more than 16 bits.
 void build_window(const csrk_matrix *h, const csrk::dev::SrRec *srec, int64_t entries, const int32_t *col_idx,
                   const int32_t *rp, csrk::dev::WinRec *&rec, uint16_t *&cols, uint16_t *&ends) {
     using namespace csrk::dev;
-    const size_t slots = (h->ssr_ptr.size() - 1) * size_t(h->srec_stride);
+    const size_t slots = (h->win.grp_ptr.size() - 1) * size_t(h->srec_stride);
     hip_check(hipMalloc(&rec, slots * sizeof(WinRec)), "window records");
     hip_check(hipMalloc(&cols, (size_t(entries) + 8) * sizeof(uint16_t)), "window columns");
     hip_check(hipMalloc(&ends, size_t(h->n) * sizeof(uint16_t)), "window row ends");
@@ -372,7 +424,6 @@ void build_window(const csrk_matrix *h, const csrk::dev::SrRec *srec, int64_t en
 // Builds the window layouts of A' and of its union pattern from the uploaded
 // arrays (upload calls it last; the launch stream is the default one).
 void upload_window(csrk_matrix *h) {
-    h->win_lanes = window_lanes(h);
     if (!h->win_lanes) return;
     build_window(h, h->d_srec, h->nnz, h->d_col_idx, h->d_row_ptr, h->d_wrec, h->d_wcols, h->d_wrend);
     if (h->d_wrec && h->d_srec_u)
@@ -402,6 +453,13 @@ csrk::dev::Shape shape_of(const csrk_matrix *h) {
     csrk::dev::Shape s;
     s.lanes_per_row = h->params.lanes_per_row;
     s.waves = h->params.waves_per_wg;
+    return s;
+}
+
+// The shape of a launch over h alone (a batch leaves long rows in their windows).
+csrk::dev::Shape launch_shape_of(const csrk_matrix *h) {
+    csrk::dev::Shape s = shape_of(h);
+    if (has_long_rows(h)) s.waves = std::max(s.waves, kLongRowWaves);
     return s;
 }
 
@@ -557,16 +615,19 @@ csrk_status csrk_upload(csrk_handle h, csrk_dtype store) {
             }
             h->long_rows = long_rows_of(h->row_ptr);
             h->t_long_rows = h->trans.symmetric ? std::vector<int32_t>() : long_rows_of(h->trans.t_row_ptr);
+            h->split_fwd = xcd_split(h, h->row_ptr, nullptr);
+            h->split_adj = h->trans.symmetric ? h->split_fwd : xcd_split(h, h->row_ptr, &h->trans.t_row_ptr);
             {
-                // one record per (SSR, slot): the slot-th super-row's rows and entries
-                const size_t nssr = h->ssr_ptr.size() - 1;
+                // one record per (group, slot): the slot-th window's rows and entries
+                const std::vector<int32_t> &win = h->win.win_ptr, &grp = h->win.grp_ptr;
+                const size_t nssr = grp.size() - 1;
                 int32_t stride = 1;
-                for (size_t t = 0; t < nssr; ++t) stride = std::max(stride, h->ssr_ptr[t + 1] - h->ssr_ptr[t]);
+                for (size_t t = 0; t < nssr; ++t) stride = std::max(stride, grp[t + 1] - grp[t]);
                 std::vector<csrk::dev::SrRec> rec(nssr * size_t(stride), csrk::dev::SrRec{0, 0, 0, 0});
                 for (size_t t = 0; t < nssr; ++t)
-                    for (int32_t s = h->ssr_ptr[t]; s < h->ssr_ptr[t + 1]; ++s) {
-                        const int32_t r0 = h->sr_ptr[size_t(s)], r1 = h->sr_ptr[size_t(s) + 1];
-                        rec[t * size_t(stride) + size_t(s - h->ssr_ptr[t])] =
+                    for (int32_t s = grp[t]; s < grp[t + 1]; ++s) {
+                        const int32_t r0 = win[size_t(s)], r1 = win[size_t(s) + 1];
+                        rec[table_row(h, t) * size_t(stride) + size_t(s - grp[t])] =
                             csrk::dev::SrRec{r0, r1, h->row_ptr[size_t(r0)], h->row_ptr[size_t(r1)]};
                     }
                 h->srec_stride = stride;
@@ -579,12 +640,12 @@ csrk_status csrk_upload(csrk_handle h, csrk_dtype store) {
                             r.e1 = h->trans.t_row_ptr[size_t(r.r1)];
                         }
                     h->d_srec_t = upload_array(rec, "transposed super-row records");
-                    // the union pattern, when every super-row fits one staging window
-                    const csrk::UnionIndex &un = h->uni;
+                    // the union pattern, when every window's fits one staging window
+                    const csrk::UnionIndex &un = h->launch_union();
                     if (un.ok) {
                         for (size_t t = 0; t < nssr; ++t)
-                            for (int32_t s = h->ssr_ptr[t]; s < h->ssr_ptr[t + 1]; ++s) {
-                                auto &r = rec[t * size_t(stride) + size_t(s - h->ssr_ptr[t])];
+                            for (int32_t s = grp[t]; s < grp[t + 1]; ++s) {
+                                auto &r = rec[table_row(h, t) * size_t(stride) + size_t(s - grp[t])];
                                 r.e0 = un.sr_begin[size_t(s)];
                                 r.e1 = un.sr_end[size_t(s)];
                             }
@@ -598,8 +659,6 @@ csrk_status csrk_upload(csrk_handle h, csrk_dtype store) {
             }
             if (!h->long_rows.empty()) h->d_long = upload_array(h->long_rows, "long rows");
             if (!h->t_long_rows.empty()) h->d_t_long = upload_array(h->t_long_rows, "transposed long rows");
-            h->split_fwd = xcd_split(h, h->row_ptr, nullptr);
-            h->split_adj = h->trans.symmetric ? h->split_fwd : xcd_split(h, h->row_ptr, &h->trans.t_row_ptr);
             // A symmetric matrix (pattern and values) is its own transpose: the
             // adjoint then reads the values the forward reads, instead of a copy.
             // (compared bit for bit: a -0.0 mirrored by a +0.0 keeps the copy)
@@ -683,7 +742,7 @@ csrk_status csrk_get_info(csrk_handle h, csrk_info *out) {
         i.store = h->store;
         i.long_rows = static_cast<int32_t>(long_rows_of(h->row_ptr).size());
         i.values_symmetric = h->on_device && h->values_symmetric ? 1 : 0;
-        i.adjoint_union = h->on_device && h->d_srec_u ? 1 : 0;
+        i.adjoint_union = h->on_device && h->uni.ok && h->d_srec_u ? 1 : 0;
         i.params = h->params;
         *out = i;
         return CSRK_OK;
@@ -772,7 +831,7 @@ csrk_status csrk_spmv(csrk_handle h, const void *vals_dev, const void *x_dev, vo
         if (h->n > 0 && x_dev == y_dev) throw Error{CSRK_ERR_ARG, "y must not alias x"};
         const void *v = values_for(h, vals_dev);
         DeviceScope ds(h->device);
-        hip_check(csrk::dev::spmv(arrays_of(h), h->store, v, x_dev, y_dev, nrhs, shape_of(h),
+        hip_check(csrk::dev::spmv(arrays_of(h), h->store, v, x_dev, y_dev, nrhs, launch_shape_of(h),
                                   static_cast<hipStream_t>(stream)),
                   "csrk_spmv launch");
         return CSRK_OK;
@@ -835,7 +894,7 @@ void cg_run(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int3
     const int64_t n = h->n;
     const bool lo = h->store != CSRK_F64;  // product vectors are FP32
     const csrk::dev::Arrays a = arrays_of(h);
-    const csrk::dev::Shape shp = shape_of(h);
+    const csrk::dev::Shape shp = launch_shape_of(h);
     double *r = w.r, *p = w.p, *part = w.part, *s = w.s;
     void *q = w.q;
     float *p_lo = w.p_lo;
@@ -991,7 +1050,7 @@ csrk_status csrk_spmv_adjoint(csrk_handle h, const void *vals_dev, const void *x
         if (vals_dev) check_align16(vals_dev, "vals_dev");
         DeviceScope ds(h->device);
         hip_check(csrk::dev::adjoint(arrays_of(h), h->store, vals_dev, x_dev, g_dev, grad_x_dev, grad_vals_dev, nrhs,
-                                     shape_of(h), static_cast<hipStream_t>(stream)),
+                                     launch_shape_of(h), static_cast<hipStream_t>(stream)),
                   "csrk_spmv_adjoint launch");
         return CSRK_OK;
     });
@@ -1033,13 +1092,13 @@ void batch_windows(csrk_batch bt, size_t nitems) {
     const size_t row = size_t(bt->brec_stride) * sizeof(WinRec);
     auto gather = [&](auto &&of) -> WinRec * {
         for (const csrk_matrix *h : bt->handles)
-            if (h->ssr_ptr.size() > 1 && !of(h)) return nullptr;
+            if (h->n > 0 && !of(h)) return nullptr;
         WinRec *out = nullptr;
         hip_check(hipMalloc(&out, std::max<size_t>(1, nitems) * row), "batch window records");
         hipError_t e = hipMemset(out, 0, nitems * row);
         size_t at = 0;
         for (const csrk_matrix *h : bt->handles) {
-            const size_t nssr = h->ssr_ptr.size() - 1, width = size_t(h->srec_stride) * sizeof(WinRec);
+            const size_t nssr = h->win.grp_ptr.size() - 1, width = size_t(h->srec_stride) * sizeof(WinRec);
             if (nssr && e == hipSuccess)
                 e = hipMemcpy2D(out + at * size_t(bt->brec_stride), row, of(h), width, width, nssr,
                                 hipMemcpyDeviceToDevice);
@@ -1059,8 +1118,8 @@ void batch_windows(csrk_batch bt, size_t nitems) {
     bt->win.lanes = bt->handles[0]->win_lanes;
     for (const csrk_matrix *h : bt->handles) {
         if (h->win_lanes != bt->win.lanes) bt->win.lanes = 0;
-        bt->win.cap = std::max(bt->win.cap, window_cap(h->max_sr_nnz));
-        bt->win.ucap = std::max(bt->win.ucap, window_cap(h->trans.symmetric ? h->max_sr_nnz : h->max_union));
+        bt->win.cap = std::max(bt->win.cap, window_cap(h->max_win_nnz));
+        bt->win.ucap = std::max(bt->win.ucap, window_cap(h->trans.symmetric ? h->max_win_nnz : h->max_union));
     }
 }
 
@@ -1083,7 +1142,7 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
             DeviceScope ds(bt->device);
             std::vector<int2> items;
             for (int32_t b = 0; b < count; ++b) {
-                const int32_t nssr = static_cast<int32_t>(handles[b]->ssr_ptr.size()) - 1;
+                const int32_t nssr = static_cast<int32_t>(handles[b]->win.grp_ptr.size()) - 1;
                 for (int32_t t = 0; t < nssr; ++t) items.push_back(make_int2(b, t));
                 bt->max_n = std::max(bt->max_n, handles[b]->n);
                 bt->all_sym = bt->all_sym && handles[b]->trans.symmetric;
@@ -1097,9 +1156,9 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
             for (size_t it = 0; it < items.size(); ++it) {
                 const csrk_matrix *h = handles[items[it].x];
                 const int32_t t = items[it].y;
-                for (int32_t s = h->ssr_ptr[size_t(t)]; s < h->ssr_ptr[size_t(t) + 1]; ++s) {
-                    const int32_t r0 = h->sr_ptr[size_t(s)], r1 = h->sr_ptr[size_t(s) + 1];
-                    brec[it * size_t(bt->brec_stride) + size_t(s - h->ssr_ptr[size_t(t)])] =
+                for (int32_t s = h->win.grp_ptr[size_t(t)]; s < h->win.grp_ptr[size_t(t) + 1]; ++s) {
+                    const int32_t r0 = h->win.win_ptr[size_t(s)], r1 = h->win.win_ptr[size_t(s) + 1];
+                    brec[it * size_t(bt->brec_stride) + size_t(s - h->win.grp_ptr[size_t(t)])] =
                         csrk::dev::SrRec{r0, r1, h->row_ptr[size_t(r0)], h->row_ptr[size_t(r1)]};
                 }
             }
@@ -1109,10 +1168,10 @@ csrk_status csrk_batch_create(const csrk_handle *handles, int32_t count, csrk_ba
                 const csrk_matrix *h = handles[items[it].x];
                 if (!h->d_srec_u) continue;
                 const int32_t t = items[it].y;
-                for (int32_t s = h->ssr_ptr[size_t(t)]; s < h->ssr_ptr[size_t(t) + 1]; ++s) {
-                    auto &r = brec[it * size_t(bt->brec_stride) + size_t(s - h->ssr_ptr[size_t(t)])];
-                    r.e0 = h->uni.sr_begin[size_t(s)];
-                    r.e1 = h->uni.sr_end[size_t(s)];
+                for (int32_t s = h->win.grp_ptr[size_t(t)]; s < h->win.grp_ptr[size_t(t) + 1]; ++s) {
+                    auto &r = brec[it * size_t(bt->brec_stride) + size_t(s - h->win.grp_ptr[size_t(t)])];
+                    r.e0 = h->launch_union().sr_begin[size_t(s)];
+                    r.e1 = h->launch_union().sr_end[size_t(s)];
                 }
             }
             bt->d_brec_u = upload_array(brec, "batch union super-row records");
@@ -1167,7 +1226,7 @@ csrk::dev::MatDesc *upload_descs(csrk_batch b, int which, const void *const *val
         m.gv = gv ? gv[i] : nullptr;
         m.nnz = h->nnz;
         m.n = h->n;
-        m.nssr = static_cast<int32_t>(h->ssr_ptr.size()) - 1;
+        m.nssr = a.nssr;
         m.sym = h->trans.symmetric ? 1 : 0;
         m.wcols = h->d_wcols;
         m.wrend = h->d_wrend;

@@ -184,4 +184,58 @@ UnionIndex union_index(int32_t n, const std::vector<int32_t> &row_ptr, const std
     return u;
 }
 
+std::vector<int32_t> union_lengths(int32_t n, const std::vector<int32_t> &row_ptr, const std::vector<int32_t> &col_idx,
+                                   const Transposed &tr) {
+    std::vector<int32_t> len(size_t(n), 0);
+    for (int32_t i = 0; i < n; ++i) {
+        len[size_t(i)] = row_ptr[size_t(i) + 1] - row_ptr[size_t(i)];
+        if (tr.symmetric) continue;
+        int32_t k = row_ptr[size_t(i)];
+        for (int32_t p = tr.t_row_ptr[size_t(i)]; p < tr.t_row_ptr[size_t(i) + 1]; ++p) {  // both by increasing column
+            while (k < row_ptr[size_t(i) + 1] && col_idx[size_t(k)] < tr.t_col[size_t(p)]) ++k;
+            if (k == row_ptr[size_t(i) + 1] || col_idx[size_t(k)] != tr.t_col[size_t(p)]) ++len[size_t(i)];
+        }
+    }
+    return len;
+}
+
+Windows launch_windows(const std::vector<int32_t> &sr_ptr, const std::vector<int32_t> &ssr_ptr,
+                       const std::vector<int32_t> &len, int32_t max_rows, int32_t max_entries, int32_t heavy,
+                       int32_t group) {
+    Windows w;
+    w.win_ptr.push_back(0);
+    bool cut = false;
+    for (size_t s = 0; s + 1 < sr_ptr.size(); ++s) {
+        const int32_t r0 = sr_ptr[s], r1 = sr_ptr[s + 1];
+        int64_t total = 0;
+        for (int32_t i = r0; i < r1; ++i) total += len[size_t(i)];
+        if (r1 - r0 <= max_rows && total <= max_entries) {
+            w.win_ptr.push_back(r1);
+            continue;
+        }
+        cut = true;
+        const int32_t pieces = (r1 - r0 + max_rows - 1) / max_rows, rows = (r1 - r0 + pieces - 1) / pieces;
+        int64_t sum = 0;
+        bool alone = false;  // the open window holds a heavy row
+        for (int32_t i = r0; i < r1; ++i) {
+            const int32_t m = len[size_t(i)], start = w.win_ptr.back();
+            if (i > start && (alone || m > heavy || i - start == rows || sum + m > max_entries)) {
+                w.win_ptr.push_back(i);
+                sum = 0;
+            }
+            sum += m;
+            alone = m > heavy;
+        }
+        w.win_ptr.push_back(r1);
+    }
+    if (!cut) {
+        w.grp_ptr = ssr_ptr;
+        return w;
+    }
+    const int32_t nwin = static_cast<int32_t>(w.win_ptr.size()) - 1;
+    for (int32_t t = 0; t < nwin; t += group) w.grp_ptr.push_back(t);
+    w.grp_ptr.push_back(nwin);
+    return w;
+}
+
 }  // namespace csrk

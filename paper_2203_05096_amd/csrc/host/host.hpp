@@ -196,4 +196,25 @@ csrk_status tune_rhs(int64_t n, int64_t nnz, int32_t nrhs, csrk_model model, csr
 // Sanity-checks parameters (throws Error CSRK_ERR_ARG).
 void check_params(const csrk_params &p);
 
+// Launch windows: the unit of rows that one wavefront of a device kernel takes.
+// They are the super-rows (win_ptr = sr_ptr, grp_ptr = ssr_ptr) when every
+// super-row has at most max_rows rows and max_entries entries.  Otherwise each
+// super-row beyond that is cut into consecutive windows within both limits, of
+// about equal rows, in which a row of more than `heavy` entries stands alone
+// (also one of more than max_entries); the windows are then grouped `group` at a
+// time in order (grp_ptr), whatever super-super-row they come from, so that no
+// workgroup gets more of them than another.  len[i]: entries that row i counts
+// for.
+struct Windows {
+    std::vector<int32_t> win_ptr;  // rows before window w
+    std::vector<int32_t> grp_ptr;  // windows before group t
+};
+Windows launch_windows(const std::vector<int32_t> &sr_ptr, const std::vector<int32_t> &ssr_ptr,
+                       const std::vector<int32_t> &len, int32_t max_rows, int32_t max_entries, int32_t heavy,
+                       int32_t group);
+
+// Entries per row of the union pattern A' + A'^T (A's own for a symmetric one).
+std::vector<int32_t> union_lengths(int32_t n, const std::vector<int32_t> &row_ptr, const std::vector<int32_t> &col_idx,
+                                   const Transposed &tr);
+
 }  // namespace csrk

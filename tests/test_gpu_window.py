@@ -1,5 +1,6 @@
 """The window walk at the edges of its rule: full and overfull windows, column spans around 16 bits, rows around a
-batch of gathers, empty rows and super-rows, windows that start and end off a load boundary; against the oracle."""
+batch of gathers, empty rows and super-rows, windows that start and end off a load boundary, super-rows cut into
+windows; against the oracle."""
 
 import numpy as np
 import pytest
@@ -57,6 +58,10 @@ CASES = {
     "lanes8": (lambda: matrix([64, 63, 65, 50, 56, 1] * 20 + [9]), 7),
     "lanes16": (lambda: matrix([128, 127, 129, 100] * 40 + [3]), 3),
     "one_row": (lambda: matrix([200, 0, 1, 7, 33, 180] * 40), 1),
+    # super-rows cut into windows: more rows or entries than one holds, heavy and long rows alone
+    "rows96": (lambda: matrix([3, 4, 5, 2] * 130), 96),
+    "cut": (lambda: matrix([14, 16, 9, 31] * 50), 50),
+    "heavy": (lambda: matrix(([2] * 30 + [300, 129, 128, 505] + [3] * 51) * 20 + [1500, 1024, 1025] + [7] * 5), 64),
     "empty": (lambda: matrix([0] * 64 + [3] * 64 + [0] * 70), 64),
     "tiny": (lambda: matrix([1, 0, 2]), 64),
 }
@@ -155,7 +160,7 @@ def block(a, store, shift):
 
 @pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
 @pytest.mark.parametrize("nrhs,shift", [(2, 0), (3, 1), (4, 1), (5, 0), (8, 0), (13, 1), (33, 0), (65, 1), (130, 0)])
-@pytest.mark.parametrize("name", ["full", "batches", "lanes2", "lanes4", "lanes16", "tiny", "band"])
+@pytest.mark.parametrize("name", ["full", "batches", "lanes2", "lanes4", "lanes16", "rows96", "tiny", "band"])
 def test_window_blocks(name, nrhs, shift, store):
     """Blocks of right-hand sides: slices that end off a slice boundary, blocks off 16 bytes, several chunks of columns.
     Forward and grad_x within the bounds of one column; grad_vals, a sum over the columns, within gamma_nrhs."""
