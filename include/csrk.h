@@ -327,11 +327,12 @@ csrk_status csrk_spmv_host(csrk_handle h, const double *x, double *y, int32_t nt
  * when ||r||_2 <= rtol * ||b||_2 (r the recurrence residual, checked every
  * check_every iterations) or after max_iter iterations; *iters_out and
  * *rel_resid_out (both may be NULL) receive the iteration count and
- * ||r||_2 / ||b||_2.  Allocates, for the call, one device block holding 3
- * work vectors (4 with FP32/BF16 storage) and one FP64 partial sum per
- * workgroup of the product (p'Ap is summed by the product's own workgroups),
- * and synchronises
- * `stream` before returning.  Errors: CSRK_ERR_ARG (null
+ * ||r||_2 / ||b||_2.  Works in one device block holding 3 or 4 work vectors
+ * and one FP64 partial sum per workgroup of the product (p'Ap is summed by the
+ * product's own workgroups); the handle keeps it for its next call, and with it
+ * 16 bytes of mapped host memory, until csrk_destroy or csrk_upload (a call that
+ * finds it in use by another allocates its own).  Synchronises `stream` before
+ * returning.  Errors: CSRK_ERR_ARG (null
  * vectors, rtol <= 0, max_iter < 0, check_every < 1), CSRK_ERR_UNSUPPORTED on
  * a breakdown (p'A p <= 0: the stored matrix is not positive definite),
  * CSRK_ERR_ALLOC, CSRK_ERR_DEVICE.

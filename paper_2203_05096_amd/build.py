@@ -20,7 +20,8 @@ BUILD_DIR = os.path.join(ROOT, "_build", "csrk")
 
 HOST_SOURCES = ["host/graph.cpp", "host/csr.cpp", "host/tune.cpp", "host/cpu_spmv.cpp"]
 HIP_SOURCES = ["device/adjoint.hip", "device/batch.hip", "device/adjoint_mrhs.hip", "device/forward.hip",
-               "device/forward_mrhs.hip", "device/adjoint_win.hip", "device/util.hip", "device/cg.hip", "capi.hip"]
+               "device/forward_mrhs.hip", "device/adjoint_win.hip", "device/util.hip", "device/cg.hip",
+               "device/cg_iter.hip", "capi.hip"]
 
 ARCH = os.environ.get("CSRK_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")

@@ -8,6 +8,7 @@
 #include <mutex>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <numeric>
 #include <string>
@@ -18,6 +19,19 @@
 #include "host/host.hpp"
 
 using csrk::Error;
+
+// What a handle keeps of its CG calls for the next one: device work memory and
+// two mapped host words for the scalars that a convergence check reads.
+struct CgMemory {
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    double *report = nullptr;
+    void free() {
+        if (ptr) (void)hipFree(ptr);
+        if (report) (void)hipHostFree(report);
+        *this = CgMemory{};
+    }
+};
 
 struct csrk_matrix {
     int32_t n = 0;
@@ -65,6 +79,8 @@ struct csrk_matrix {
     uint16_t *d_wucols = nullptr, *d_wxend = nullptr;
     int32_t win_lanes = 0;  // WinArrays::lanes
     bool interleave = false;  // groups go to the XCDs in turn, not in contiguous ranges (irregular matrices)
+    std::mutex cg_mu;
+    CgMemory cg_mem;
     int32_t max_union = 0;  // most union entries of a super-row
 };
 
@@ -139,6 +155,7 @@ struct DeviceScope {
 void free_device(csrk_matrix *h) {
     if (!h->on_device) return;
     DeviceScope ds(h->device);
+    h->cg_mem.free();
     for (void *p : {(void *)h->d_row_ptr, (void *)h->d_col_idx, (void *)h->d_sr_ptr, (void *)h->d_ssr_ptr,
                     (void *)h->d_perm, (void *)h->d_t_row_ptr, (void *)h->d_t_col, (void *)h->d_t_src, h->d_vals,
                     h->d_vals_t == h->d_vals ? nullptr : h->d_vals_t, (void *)h->d_long, (void *)h->d_t_long,
@@ -840,37 +857,56 @@ csrk_status csrk_spmv(csrk_handle h, const void *vals_dev, const void *x_dev, vo
 
 namespace {
 
-// Work memory of one CG solve: r and p (FP64), q (the product's output:
-// FP32 with FP32/BF16 storage), p_lo (FP32 copy of p feeding FP32/BF16
-// storage), one FP64 partial sum per workgroup of the largest reduction grid,
-// and the scalars.  Each array starts on a 256-byte boundary.
+// Work memory of one CG solve: r and p (FP64; with two launches an iteration a
+// second p), q (the product's output: FP32 with FP32/BF16 storage), p_lo (FP32
+// copy of p feeding FP32/BF16 storage; none with two launches), one FP64 partial
+// sum per workgroup of the largest reduction grid, the scalars, and the
+// residual's partial sums.  Each array starts on a 256-byte boundary.
 struct CgWork {
-    double *r = nullptr, *p = nullptr;
+    bool two = false;  // two launches an iteration (csrk::dev::CgIter)
+    double *r = nullptr, *p = nullptr, *p2 = nullptr;
     void *q = nullptr;
     float *p_lo = nullptr;
-    double *part = nullptr, *s = nullptr;
+    double *part = nullptr, *part2 = nullptr, *s = nullptr;
 };
 
 size_t round256(size_t b) { return (std::max<size_t>(b, 16) + 255) / 256 * 256; }
 
-// Bytes of CgWork for this handle, and the pointers inside base.
+// The residual's partial sums, behind the bytes that cg_work_layout counts.
+constexpr size_t kCgPartBytes = size_t(csrk::dev::kCgGrid) * 8;
+
+// Rows up to which a solve takes two launches an iteration, where the matrix has
+// the window layout: beyond, gathering p and r for every entry costs more than a
+// launch.  3D 7-point FP64, us for 50 iterations, two launches / three / the five
+// before: 24x25x26 627 / 751 / 998; 64^3 833 / 967 / 1383; 80^3 1532 / 1402 / 1900;
+// 120^3 3685 / 2972 / 3448.
+constexpr int32_t kCgTwoRows = 3 << 17;
+
+bool cg_two_launches(const csrk_matrix *h) { return h->n > 0 && h->d_wrec && h->n <= kCgTwoRows; }
+
+// Bytes of CgWork for this handle without the residual's partial sums, and the
+// pointers inside base (which holds kCgPartBytes more).
 size_t cg_work_layout(const csrk_matrix *h, unsigned char *base, CgWork *w) {
     const size_t n = size_t(h->n);
-    const bool lo = h->store != CSRK_F64;
+    const bool lo = h->store != CSRK_F64, two = cg_two_launches(h);
     const int nparts = std::max(csrk::dev::kCgGrid, csrk::dev::spmv_grid(arrays_of(h)));
-    const size_t sizes[6] = {n * 8, n * 8, n * (lo ? 4 : 8), lo ? n * 4 : 0, size_t(nparts) * 8, 8 * 8};
-    size_t off[6], total = 0;
-    for (int i = 0; i < 6; ++i) {
+    const size_t sizes[7] = {n * 8, n * 8, two ? n * 8 : 0, n * (lo ? 4 : 8), lo && !two ? n * 4 : 0,
+                             size_t(nparts) * 8, 8 * 8};
+    size_t off[7], total = 0;
+    for (int i = 0; i < 7; ++i) {
         off[i] = total;
         total += sizes[i] ? round256(sizes[i]) : 0;
     }
     if (base && w) {
+        w->two = two;
         w->r = reinterpret_cast<double *>(base + off[0]);
         w->p = reinterpret_cast<double *>(base + off[1]);
-        w->q = base + off[2];
-        w->p_lo = lo ? reinterpret_cast<float *>(base + off[3]) : nullptr;
-        w->part = reinterpret_cast<double *>(base + off[4]);
-        w->s = reinterpret_cast<double *>(base + off[5]);
+        w->p2 = two ? reinterpret_cast<double *>(base + off[2]) : nullptr;
+        w->q = base + off[3];
+        w->p_lo = lo && !two ? reinterpret_cast<float *>(base + off[4]) : nullptr;
+        w->part = reinterpret_cast<double *>(base + off[5]);
+        w->s = reinterpret_cast<double *>(base + off[6]);
+        w->part2 = reinterpret_cast<double *>(base + total);
     }
     return total;
 }
@@ -890,7 +926,7 @@ void cg_check_args(csrk_handle h, const double *b_dev, double *x_dev, double rto
 // update, q by the product, each partial sum by its workgroup, each scalar by
 // the reduction that produces it), so w needs no clearing.
 void cg_run(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int32_t max_iter, int32_t check_every,
-            hipStream_t st, const CgWork &w, int32_t *iters_out, double *rel_resid_out) {
+            hipStream_t st, const CgWork &w, double *report, int32_t *iters_out, double *rel_resid_out) {
     const int64_t n = h->n;
     const bool lo = h->store != CSRK_F64;  // product vectors are FP32
     const csrk::dev::Arrays a = arrays_of(h);
@@ -901,53 +937,85 @@ void cg_run(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int3
     auto spmv = [&](const void *in) {
         hip_check(csrk::dev::spmv(a, h->store, h->d_vals, in, q, 1, shp, st), "cg product");
     };
-    // r = b - A x0, p = r, rr = r . r, bb = b . b
-    if (lo) hip_check(csrk::dev::cg_round(x_dev, p_lo, n, st), "cg round");
-    spmv(lo ? static_cast<const void *>(p_lo) : static_cast<const void *>(x_dev));
-    hip_check(csrk::dev::cg_residual(b_dev, q, lo, r, n, part, s, st), "cg residual");
+    // r = b - A x0, rr = r . r, bb = b . b (and p = r).  An FP32 x0 for the first
+    // product goes where the second p will be.
+    float *x_lo = w.two ? reinterpret_cast<float *>(w.p2) : p_lo;
+    if (lo) hip_check(csrk::dev::cg_round(x_dev, x_lo, n, st), "cg round");
+    spmv(lo ? static_cast<const void *>(x_lo) : static_cast<const void *>(x_dev));
+    hip_check(csrk::dev::cg_residual(b_dev, q, lo, r, n, w.part2, s, st), "cg residual");
     hip_check(csrk::dev::cg_norm2(b_dev, n, part, s, st), "cg norm");
-    hip_check(csrk::dev::cg_set_p(r, p, p_lo, s, n, false, st), "cg p");
+    if (!w.two) hip_check(csrk::dev::cg_set_p(r, p, p_lo, n, st), "cg p");
+    csrk::dev::CgIter iter;
+    iter.two = w.two;
+    iter.x = x_dev;
+    iter.r = r;
+    iter.p[0] = p;
+    iter.p[1] = w.p2;
+    iter.p_lo = p_lo;
+    iter.q = q;
+    iter.pq_part = part;
+    iter.rr_part = w.part2;
+    iter.s = s;
+    iter.rr_parts0 = csrk::dev::cg_grid(n);
     double host_s[6] = {0, 0, 0, 0, 0, 0};
-    auto read_scalars = [&]() {
-        hip_check(hipMemcpyAsync(host_s, s, sizeof(host_s), hipMemcpyDeviceToHost, st), "cg read");
-        hip_check(hipStreamSynchronize(st), "cg sync");
-    };
-    read_scalars();
+    hip_check(hipMemcpyAsync(host_s, s, sizeof(host_s), hipMemcpyDeviceToHost, st), "cg read");
+    hip_check(hipStreamSynchronize(st), "cg sync");
     const double bnorm = std::sqrt(host_s[5]);
     const double target = rtol * (bnorm > 0 ? bnorm : 1.0);
+    double rr = host_s[0];
     int32_t it = 0;
-    bool done = std::sqrt(host_s[0]) <= target;
-    // Per iteration: q = A p with p . q summed per workgroup of the product
-    // (no separate pass over p and q), alpha; r -= alpha q with r . r, beta;
-    // then x += alpha p and p = r + beta p in one pass over p.
+    bool done = std::sqrt(rr) <= target;
     while (!done && it < max_iter) {
-        hip_check(csrk::dev::spmv_dot(a, h->store, h->d_vals,
-                                      lo ? static_cast<const void *>(p_lo) : static_cast<const void *>(p), q, p,
-                                      part, shp, st),
-                  "cg product");
-        hip_check(csrk::dev::cg_alpha_parts(part, csrk::dev::spmv_grid(a), s, st), "cg alpha");
-        hip_check(csrk::dev::cg_update_r(r, q, lo, n, part, s, st), "cg residual update");
-        hip_check(csrk::dev::cg_update_xp(x_dev, p, p_lo, r, s, n, st), "cg x and p update");
+        hip_check(csrk::dev::cg_iteration(a, h->store, h->d_vals, iter, it, shp, st), "cg iteration");
         ++it;
         if (it % check_every == 0 || it == max_iter) {
-            read_scalars();
-            if (!(host_s[1] > 0) || !std::isfinite(host_s[0]))
+            // (r . r, p . q) to the mapped host words, or by way of device scalars that nothing else uses
+            double *out = report ? report : s + 3;
+            hip_check(csrk::dev::cg_report(w.part2, csrk::dev::cg_iter_grid(n), s, out, st), "cg residual norm");
+            if (!report) hip_check(hipMemcpyAsync(host_s, out, 2 * sizeof(double), hipMemcpyDeviceToHost, st), "cg read");
+            hip_check(hipStreamSynchronize(st), "cg sync");
+            if (report) std::copy(report, report + 2, host_s);
+            rr = host_s[0];
+            if (!(host_s[1] > 0) || !std::isfinite(rr))
                 throw Error{CSRK_ERR_UNSUPPORTED,
                             "CG breakdown (p'Ap <= 0 or a non-finite residual): the matrix is not symmetric "
                             "positive definite in the stored precision"};
-            done = std::sqrt(host_s[0]) <= target;
+            done = std::sqrt(rr) <= target;
         }
     }
+    if (w.two && it > 0) hip_check(csrk::dev::cg_last(iter, it, n, st), "cg x update");
     if (iters_out) *iters_out = it;
-    if (rel_resid_out) *rel_resid_out = std::sqrt(host_s[0]) / (bnorm > 0 ? bnorm : 1.0);
+    if (rel_resid_out) *rel_resid_out = std::sqrt(rr) / (bnorm > 0 ? bnorm : 1.0);
     hip_check(hipStreamSynchronize(st), "cg sync");
 }
 
-// Device work memory of one csrk_cg call, freed on every exit path.
-struct CgAlloc {
-    void *ptr = nullptr;
-    ~CgAlloc() {
-        if (ptr) (void)hipFree(ptr);
+// Work memory of one csrk_cg call: taken from the handle, or allocated, and on
+// every exit path left with the handle for the next call, or freed where the
+// handle keeps one already (calls at once on one handle); not before the call's
+// launches are done.
+struct CgLease {
+    csrk_matrix *h;
+    hipStream_t st;
+    CgMemory m;
+    CgLease(csrk_matrix *handle, size_t bytes, hipStream_t stream) : h(handle), st(stream) {
+        {
+            std::lock_guard<std::mutex> lock(h->cg_mu);
+            std::swap(m, h->cg_mem);
+        }
+        if (!m.report) hip_check(hipHostMalloc(reinterpret_cast<void **>(&m.report), 2 * sizeof(double)), "cg report");
+        if (m.bytes >= bytes) return;
+        if (m.ptr) (void)hipFree(m.ptr);
+        m.ptr = nullptr;
+        const hipError_t e = hipMalloc(&m.ptr, bytes);
+        if (e != hipSuccess) m.free();
+        hip_check(e, "cg work vectors");
+        m.bytes = bytes;
+    }
+    ~CgLease() {
+        if (std::uncaught_exceptions() > 0) (void)hipStreamSynchronize(st);  // cg_run waited otherwise
+        std::lock_guard<std::mutex> lock(h->cg_mu);
+        if (!h->cg_mem.ptr) std::swap(m, h->cg_mem);
+        m.free();
     }
 };
 
@@ -956,7 +1024,7 @@ struct CgAlloc {
 // address comes from hipGetSymbolAddress, once per device, with that device
 // current.
 constexpr size_t kCgScratchBytes = size_t(CSRK_CG_NOALLOC_BYTES);
-__device__ __align__(256) unsigned char scratch[kCgScratchBytes];
+__device__ __align__(256) unsigned char scratch[kCgScratchBytes + kCgPartBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -981,13 +1049,11 @@ csrk_status csrk_cg(csrk_handle h, const double *b_dev, double *x_dev, double rt
     return guard([&] {
         cg_check_args(h, b_dev, x_dev, rtol, max_iter, check_every);
         DeviceScope ds(h->device);
-        const size_t bytes = cg_work_layout(h, nullptr, nullptr);
-        CgAlloc mem;
-        hip_check(hipMalloc(&mem.ptr, bytes), "cg work vectors");
+        const hipStream_t st = static_cast<hipStream_t>(stream);
+        CgLease mem(h, cg_work_layout(h, nullptr, nullptr) + kCgPartBytes, st);
         CgWork w;
-        cg_work_layout(h, static_cast<unsigned char *>(mem.ptr), &w);
-        cg_run(h, b_dev, x_dev, rtol, max_iter, check_every, static_cast<hipStream_t>(stream), w, iters_out,
-               rel_resid_out);
+        cg_work_layout(h, static_cast<unsigned char *>(mem.m.ptr), &w);
+        cg_run(h, b_dev, x_dev, rtol, max_iter, check_every, st, w, mem.m.report, iters_out, rel_resid_out);
         return CSRK_OK;
     });
 }
@@ -1013,7 +1079,7 @@ csrk_status csrk_cg_noalloc(csrk_handle h, const double *b_dev, double *x_dev, d
         DeviceScope ds(h->device);
         CgWork w;
         cg_work_layout(h, scratch_on(h->device), &w);
-        cg_run(h, b_dev, x_dev, rtol, max_iter, check_every, static_cast<hipStream_t>(stream), w, iters_out,
+        cg_run(h, b_dev, x_dev, rtol, max_iter, check_every, static_cast<hipStream_t>(stream), w, nullptr, iters_out,
                rel_resid_out);
         return CSRK_OK;
     });

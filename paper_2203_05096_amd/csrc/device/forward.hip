@@ -91,6 +91,8 @@ __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride
                                                    const typename Store<VT>::X *__restrict__ x,
                                                    typename Store<VT>::X *__restrict__ y, int64_t nnz, XcdSplit split,
                                                    const double *__restrict__ pdot, double *__restrict__ part) {
+    using A = typename Store<VT>::A;
+    using X = typename Store<VT>::X;
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = uniform(threadIdx.x / kWave);
@@ -102,7 +104,17 @@ __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride
         for (int32_t w = wave; w < stride; w += nw) {
             const WinRec rec = win.rec[int64_t(t) * stride + w];
             if (rec.rows() == 0) break;
-            win_forward<VT, LL, DOT>(rec, win.rend, win.cols, vals, x, y, nnz, lds, lane, pdot, &dot);
+            if constexpr (DOT) {
+                const X *xb = x + rec.base;
+                win_product<VT, LL>(
+                    rec, win.rend, win.cols, vals, nnz, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
+                    [&](int rr, A acc) {
+                        y[rec.r0 + rr] = X(acc);
+                        dot += double(X(acc)) * pdot[rec.r0 + rr];
+                    });
+            } else {
+                win_forward<VT, LL>(rec, win.rend, win.cols, vals, x, y, nnz, lds, lane);
+            }
         }
     }
     if constexpr (DOT) {

@@ -259,9 +259,8 @@ hipError_t probe_read(const void *buf, int64_t bytes, double *part, hipStream_t 
 hipError_t probe_copy(const void *src, void *dst, int64_t bytes, hipStream_t st);
 
 // Conjugate-gradient vector kernels (device/cg.hip).  FP64 vectors; q (the
-// product's output) is FP32 when q_f32.  part holds kCgGrid partial sums
-// (or spmv_grid's, for cg_alpha_parts); s the scalars rr, pq, alpha, beta,
-// rr_new, bb at s[0..5].
+// product's output) is FP32 when q_f32.  part holds kCgGrid partial sums; s the
+// scalars rr and bb at s[0] and s[5].
 constexpr int kCgGrid = 1024;
 int cg_grid(int64_t n);
 // r = b - q, s[0] = r . r
@@ -269,18 +268,31 @@ hipError_t cg_residual(const double *b, const void *q, bool q_f32, double *r, in
                        hipStream_t st);
 // s[5] = b . b
 hipError_t cg_norm2(const double *b, int64_t n, double *part, double *s, hipStream_t st);
-// p = r + beta p (p = r when !use_beta); p_lo = float(p) when p_lo != NULL
-hipError_t cg_set_p(const double *r, double *p, float *p_lo, const double *s, int64_t n, bool use_beta,
-                    hipStream_t st);
-// s[1] = sum of part[0..count) (p . q from spmv_dot), s[2] = alpha = s[0] / s[1]
-hipError_t cg_alpha_parts(const double *part, int count, double *s, hipStream_t st);
-// r -= alpha q, s[4] = r . r, s[3] = beta = s[4] / s[0], s[0] = s[4]
-hipError_t cg_update_r(double *r, const void *q, bool q_f32, int64_t n, double *part, double *s, hipStream_t st);
-// x += alpha p, then p = r + beta p (one pass over the old p); p_lo = float(p) when p_lo != NULL
-hipError_t cg_update_xp(double *x, double *p, float *p_lo, const double *r, const double *s, int64_t n,
-                        hipStream_t st);
+// p = r; p_lo = float(p) when p_lo != NULL
+hipError_t cg_set_p(const double *r, double *p, float *p_lo, int64_t n, hipStream_t st);
 // out = float(v)
 hipError_t cg_round(const double *v, float *out, int64_t n, hipStream_t st);
+
+// CG iterations without launches for their sums (device/cg_iter.hip).  x, r and
+// p hold n doubles, q the product's vector type, p_lo n floats (FP32/BF16
+// storage, three launches), pq_part spmv_grid(a) and rr_part kCgGrid partial
+// sums (rr_parts0 of them before iteration 0), s 8 scalars.  s[1] is p . q of the
+// last iteration; r . r after it is rr_part's sum.
+struct CgIter {
+    bool two = false;  // two launches an iteration: a.win.rec set, p has two buffers
+    double *x = nullptr, *r = nullptr, *p[2] = {nullptr, nullptr};
+    float *p_lo = nullptr;
+    void *q = nullptr;
+    double *pq_part = nullptr, *rr_part = nullptr, *s = nullptr;
+    int rr_parts0 = 0;
+};
+int cg_iter_grid(int64_t n);  // partial sums of r . r after an iteration
+hipError_t cg_iteration(const Arrays &a, csrk_dtype store, const void *vals, const CgIter &w, int it, Shape s,
+                        hipStream_t st);
+// x += alpha p after `iterations` >= 1 iterations of two launches
+hipError_t cg_last(const CgIter &w, int iterations, int64_t n, hipStream_t st);
+// out[0] = sum of part[0..count), out[1] = s[1] (out: mapped host memory)
+hipError_t cg_report(const double *part, int count, const double *s, double *out, hipStream_t st);
 
 }  // namespace dev
 }  // namespace csrk

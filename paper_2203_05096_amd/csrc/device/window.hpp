@@ -120,15 +120,13 @@ __host__ __device__ constexpr int win_forward_lds() {
     return kStageEntries * int(sizeof(VT) + sizeof(uint16_t));
 }
 
-// y for the rows of one super-row.  With DOT, the lane that stores y[i] also
-// adds y[i] * pdot[i] (FP64, y as stored) to *dot.
-template <typename VT, int LL, bool DOT = false>
-__device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *__restrict__ rend16,
-                                            const uint16_t *__restrict__ cols, const VT *__restrict__ vals,
-                                            const typename Store<VT>::X *__restrict__ x,
-                                            typename Store<VT>::X *__restrict__ y, int64_t nnz,
-                                            unsigned char *__restrict__ lds, int lane,
-                                            const double *__restrict__ pdot = nullptr, double *dot = nullptr) {
+// The product of one super-row with a vector given by its entries: ready() is
+// called once the stream is requested, gather(c) returns x at column base + c,
+// and one lane per row calls emit(row, sum), the row counted from r0.
+template <typename VT, int LL, typename R, typename G, typename E>
+__device__ __forceinline__ void win_product(const WinRec &rec, const uint16_t *__restrict__ rend16,
+                                            const uint16_t *__restrict__ cols, const VT *__restrict__ vals, int64_t nnz,
+                                            unsigned char *__restrict__ lds, int lane, R &&ready, G &&gather, E &&emit) {
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     constexpr int V = Store<VT>::V;
@@ -139,9 +137,9 @@ __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *_
     WinStream<VT> w;
     win_load<VT, false>(w, rec.e0, nent, cols, nullptr, vals, nnz, lane);
     const int my_end = lane < nrows ? int(rend16[rec.r0 + lane]) : 0;
+    ready();
     win_stage<VT>(w, rec.e0, nent, sval, scol, lane);
     wave_lds_sync();
-    const X *xb = x + rec.base;
     const int rr = lane / LL;
     const bool act = rr < nrows;
     const int rend = __shfl(my_end, act ? rr : 0);
@@ -158,18 +156,30 @@ __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *_
             const int kk = ok ? k + j * LL : off;
             const uint32_t c = scol[kk];
             a[j] = ok ? Store<VT>::widen(sval[kk]) : A(0);
-            xv[j] = ok ? xb[c] : X(0);
+            xv[j] = ok ? gather(c) : X(0);
         }
 #pragma unroll
         for (int j = 0; j < B; ++j) acc += a[j] * A(xv[j]);
         k += B * LL;
     }
     acc = row_sum<LL>(acc);
-    if (act && lane % LL == 0) {
-        y[rec.r0 + rr] = X(acc);
-        if constexpr (DOT) *dot += double(X(acc)) * pdot[rec.r0 + rr];
-    }
+    if (act && lane % LL == 0) emit(rr, acc);
     wave_lds_sync();
+}
+
+// y for the rows of one super-row.
+template <typename VT, int LL>
+__device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *__restrict__ rend16,
+                                            const uint16_t *__restrict__ cols, const VT *__restrict__ vals,
+                                            const typename Store<VT>::X *__restrict__ x,
+                                            typename Store<VT>::X *__restrict__ y, int64_t nnz,
+                                            unsigned char *__restrict__ lds, int lane) {
+    using A = typename Store<VT>::A;
+    using X = typename Store<VT>::X;
+    const X *xb = x + rec.base;
+    win_product<VT, LL>(
+        rec, rend16, cols, vals, nnz, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
+        [&](int rr, A acc) { y[rec.r0 + rr] = X(acc); });
 }
 
 // ------------------------------------------------------------------ adjoint

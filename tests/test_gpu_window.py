@@ -14,6 +14,7 @@ torch = pytest.importorskip("torch")
 
 from oracle import adjoint as OA  # noqa: E402
 from oracle import precision as OP  # noqa: E402
+from oracle import spmv as OS  # noqa: E402
 from paper_2203_05096_amd.matrix import CsrkBatch, CsrkMatrix  # noqa: E402
 
 DT = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.float32}
@@ -195,3 +196,37 @@ def test_window_blocks(name, nrhs, shift, store):
                 assert np.all(np.abs(out.double().cpu().numpy() - ref) <= beta * scale)
         B.close()
         M.close()
+
+
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("side,band_rows", [(16, 0), (0, 500000)])
+def test_cg_launch_rules(side, band_rows, store):
+    """CG with two launches an iteration (a small grid) and with three (more rows than that rule takes), checked by the
+    residual of the stored matrix: the recurrence drifts from it by the FP32 rounding of the products at most (100x the
+    tolerance), in FP64 storage by rounding alone (2x).  Twice on one handle, which keeps its work memory: equal bits."""
+    if side:
+        from gen import laplacian
+        A = laplacian((side, side + 1, side + 3), "3d7", 6.0)
+    else:
+        n = band_rows
+        rp = np.concatenate([[0], np.cumsum(np.r_[2, np.full(n - 2, 3), 2])]).astype(np.int32)
+        ci = np.concatenate([[0, 1], (np.arange(1, n - 1)[:, None] + [-1, 0, 1]).ravel(), [n - 2, n - 1]]).astype(np.int32)
+        A = CsrInput("tri", n, rp, ci, np.where(ci == np.repeat(np.arange(n), np.diff(rp)), 4.0, -1.0), {})
+    say("cg launches", A.n, store)
+    M = CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store)
+    perm = M.structure()["perm"]
+    b = np.random.default_rng(4).uniform(-1, 1, A.n)
+    bd = to_dev(b[perm], torch.float64)
+    rtol = 1e-6
+    x, it, rel = M.cg(bd, rtol=rtol, max_iter=500, check_every=7)
+    x2, it2, rel2 = M.cg(bd, rtol=rtol, max_iter=500, check_every=7)
+    torch.cuda.synchronize()
+    assert it == it2 and rel == rel2 and torch.equal(x, x2)
+    assert 0 < it < 500 and it % 7 == 0 and rel <= rtol
+    xin = np.empty(A.n)
+    xin[perm] = x.cpu().numpy()
+    res = np.linalg.norm(b - OS.spmv(A.row_ptr, A.col_idx, A.vals, xin)) / np.linalg.norm(b)
+    assert res <= (2 if store == "f64" else 100) * rtol, res
+    x, it, rel = M.cg(bd, x0=x, rtol=rtol, max_iter=500, check_every=1)  # from the solution: at most a few iterations
+    assert it <= 7
+    M.close()
