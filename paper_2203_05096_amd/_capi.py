@@ -303,7 +303,9 @@ def csrk_copy_device_vals(h: int, dst_dev, stream):
 
 
 def csrk_spmv(h: int, vals_dev, x_dev, y_dev, nrhs: int, stream):
-    _check(lib().csrk_spmv(h, vals_dev, x_dev, y_dev, int(nrhs), stream), "csrk_spmv")
+    status = (_lib or lib()).csrk_spmv(h, vals_dev, x_dev, y_dev, int(nrhs), stream)
+    if status:
+        _check(status, "csrk_spmv")
 
 
 def csrk_spmv_host(h: int, x, y=None, nthreads: int = 0):
@@ -351,8 +353,9 @@ def csrk_spmv_plain(h: int, vals_dev, x_dev, y_dev, nrhs: int, stream):
 
 
 def csrk_spmv_adjoint(h: int, vals_dev, x_dev, g_dev, grad_x_dev, grad_vals_dev, nrhs: int, stream):
-    _check(lib().csrk_spmv_adjoint(h, vals_dev, x_dev, g_dev, grad_x_dev, grad_vals_dev, int(nrhs), stream),
-           "csrk_spmv_adjoint")
+    status = (_lib or lib()).csrk_spmv_adjoint(h, vals_dev, x_dev, g_dev, grad_x_dev, grad_vals_dev, int(nrhs), stream)
+    if status:
+        _check(status, "csrk_spmv_adjoint")
 
 
 def csrk_permute(h: int, direction: int, in_dev, out_dev, nrhs: int, elem_bytes: int, stream):
@@ -366,7 +369,7 @@ def csrk_destroy(h: int):
 def _ptr_array(ptrs):
     if ptrs is None:
         return None
-    return (_vp * len(ptrs))(*[p if p else None for p in ptrs])
+    return (_vp * len(ptrs))(*ptrs)  # 0 and None are both NULL
 
 
 def csrk_batch_create(handles) -> int:

@@ -18,7 +18,14 @@ _VAL_DTYPE = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16
 _GRADV_DTYPE = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.float32}
 
 
+_CUDA = torch.device("cuda")
+# the current stream's handle without building a Stream object (0.2 us against 1.5 us a call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -67,6 +74,14 @@ class CsrkMatrix:
         return t
 
     def _check_vec(self, t, name, nrhs=None):
+        # one pass over what has to hold; only a tensor that fails it is asked which part it was
+        if t.dtype is self.vec_dtype and t.is_cuda and t.is_contiguous():
+            s = t.shape
+            if len(s) == 1:
+                if s[0] == self.n and (nrhs is None or nrhs == 1):
+                    return 1
+            elif len(s) == 2 and s[0] == self.n and (nrhs is None or nrhs == s[1]):
+                return s[1]
         if t.device.type != "cuda" or t.dtype != self.vec_dtype or not t.is_contiguous() or t.dim() not in (1, 2):
             raise TypeError(f"{name} must be a contiguous {self.vec_dtype} CUDA tensor of shape (n,) or (n, nrhs)")
         if t.shape[0] != self.n:
@@ -96,7 +111,8 @@ class CsrkMatrix:
         nrhs = self._check_vec(x, "x")
         if y is None:
             y = torch.empty_like(x)
-        self._check_vec(y, "y", nrhs)
+        else:
+            self._check_vec(y, "y", nrhs)
         C.csrk_spmv(self.handle, self._check_vals(vals), _ptr(x), _ptr(y), nrhs, _stream())
         return y
 
@@ -130,11 +146,14 @@ class CsrkMatrix:
         gx = None
         gv = None
         if grad_x:
-            gx = out_x if out_x is not None else torch.empty_like(g)
-            self._check_vec(gx, "grad_x", nrhs)
+            if out_x is None:
+                gx = torch.empty_like(g)
+            else:
+                gx = out_x
+                self._check_vec(gx, "grad_x", nrhs)
         if grad_vals:
             gv = self._check_grad_vals(out_vals) if out_vals is not None else \
-                torch.empty(self.nnz, dtype=_GRADV_DTYPE[self.store], device="cuda")
+                torch.empty(self.nnz, dtype=_GRADV_DTYPE[self.store], device=_CUDA)
         C.csrk_spmv_adjoint(self.handle, self._check_vals(vals), _ptr(x) if grad_vals else None, _ptr(g), _ptr(gx),
                             _ptr(gv), nrhs, _stream())
         return gx, gv
@@ -210,11 +229,13 @@ class CsrkBatch:
     def spmv(self, xs, ys=None, vals=None):
         self._same_count(xs=xs, ys=ys, vals=vals)
         nrhs = 1 if xs[0].dim() == 1 else xs[0].shape[1]
+        for m, x in zip(self.mats, xs):
+            m._check_vec(x, "x", nrhs)
         if ys is None:
             ys = [torch.empty_like(x) for x in xs]
-        for m, x, y in zip(self.mats, xs, ys):
-            m._check_vec(x, "x", nrhs)
-            m._check_vec(y, "y", nrhs)
+        else:
+            for m, y in zip(self.mats, ys):
+                m._check_vec(y, "y", nrhs)
         vp = None if vals is None else [m._check_vals(v) for m, v in zip(self.mats, vals)]
         C.csrk_batch_spmv(self.handle, vp, [_ptr(x) for x in xs], [_ptr(y) for y in ys], nrhs, _stream())
         return ys
@@ -222,20 +243,21 @@ class CsrkBatch:
     def adjoint(self, xs, gs, vals=None, grad_x=True, grad_vals=True, out_x=None, out_vals=None):
         self._same_count(xs=xs if grad_vals else None, gs=gs, vals=vals, out_x=out_x, out_vals=out_vals)
         nrhs = 1 if gs[0].dim() == 1 else gs[0].shape[1]
-        gxs = None
-        gvs = None
-        if grad_x:
-            gxs = out_x if out_x is not None else [torch.empty_like(g) for g in gs]
-        if grad_vals:
-            gvs = out_vals if out_vals is not None else [
-                torch.empty(m.nnz, dtype=_GRADV_DTYPE[m.store], device="cuda") for m in self.mats]
+        gxs = out_x if grad_x else None
+        gvs = out_vals if grad_vals else None
         for i, m in enumerate(self.mats):
             m._check_vec(gs[i], "g", nrhs)
             if grad_vals:
                 m._check_vec(xs[i], "x", nrhs)
-                m._check_grad_vals(gvs[i])
-            if grad_x:
+                if gvs is not None:
+                    m._check_grad_vals(gvs[i])
+            if gxs is not None:
                 m._check_vec(gxs[i], "grad_x", nrhs)
+        if grad_x and gxs is None:
+            gxs = [torch.empty_like(g) for g in gs]
+        if grad_vals and gvs is None:
+            dt = _GRADV_DTYPE[self.store]
+            gvs = [torch.empty(m.nnz, dtype=dt, device=_CUDA) for m in self.mats]
         vp = None if vals is None else [m._check_vals(v) for m, v in zip(self.mats, vals)]
         C.csrk_batch_spmv_adjoint(self.handle, vp, [_ptr(x) for x in xs] if grad_vals else None,
                                   [_ptr(g) for g in gs],
