@@ -223,11 +223,19 @@ int32_t window_lanes(const csrk_matrix *h) {
 void launch_shape(csrk_matrix *h) {
     using namespace csrk::dev;
     const int32_t waves = has_long_rows(h) ? std::max(h->params.waves_per_wg, kLongRowWaves) : h->params.waves_per_wg;
-    const std::vector<int32_t> len = csrk::union_lengths(h->n, h->row_ptr, h->col_idx, h->trans);
-    h->win = csrk::launch_windows(h->sr_ptr, h->ssr_ptr, len, kWinRows, kWinEntries, kHeavyRow,
-                                  std::max(h->params.ssrs, waves));
-    if (!h->uni.ok)
-        h->win_uni = csrk::union_index(h->n, h->row_ptr, h->col_idx, h->win.win_ptr, h->trans, kUnionRows, kUnionWindow);
+    int32_t rows = 0;
+    for (size_t s = 0; s + 1 < h->sr_ptr.size(); ++s) rows = std::max(rows, h->sr_ptr[s + 1] - h->sr_ptr[s]);
+    if (rows <= kWinRows && h->max_sr_nnz <= kWinEntries && (h->trans.symmetric || h->uni.ok)) {
+        h->win.win_ptr = h->sr_ptr;  // every super-row is a window as it is
+        h->win.grp_ptr = h->ssr_ptr;
+    } else {
+        h->win = csrk::launch_windows(h->sr_ptr, h->ssr_ptr,
+                                      csrk::union_lengths(h->n, h->row_ptr, h->col_idx, h->trans), kWinRows,
+                                      kWinEntries, kHeavyRow, std::max(h->params.ssrs, waves));
+        if (!h->uni.ok)
+            h->win_uni =
+                csrk::union_index(h->n, h->row_ptr, h->col_idx, h->win.win_ptr, h->trans, kUnionRows, kUnionWindow);
+    }
     const csrk::UnionIndex &u = h->launch_union();
     h->max_union = h->max_win_rows = h->max_win_nnz = 0;
     for (size_t s = 0; s < u.sr_begin.size(); ++s) h->max_union = std::max(h->max_union, u.sr_end[s] - u.sr_begin[s]);
