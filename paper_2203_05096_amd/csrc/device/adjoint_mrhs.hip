@@ -7,7 +7,7 @@ namespace dev {
 
 namespace {
 
-template <typename VT, int RL, int VX, bool EXACT, bool IND, bool UNI, bool GX>
+template <typename VT, int RL, int VX, bool EXACT, bool IND, bool UNI, bool GX, bool KEEP>
 __global__ void __launch_bounds__(1024) k_adjoint_win_mrhs(WinArrays win, int32_t stride,
                                                            const int32_t *__restrict__ src,
                                                            const VT *__restrict__ vals,
@@ -30,7 +30,7 @@ __global__ void __launch_bounds__(1024) k_adjoint_win_mrhs(WinArrays win, int32_
         if (rec.rows() == 0) break;
         win_adjoint_mrhs<VT, RL, VX, EXACT, IND, UNI, GX>(rec, UNI ? win.urec[slot] : rec, win.rend, win.xend,
                                                    UNI ? win.ucols : win.cols, src, vals, x, g, gx, gv, nnz, nrhs,
-                                                   cap, lds, lane);
+                                                   cap, std::bool_constant<KEEP>{}, lds, lane);
     }
 }
 
@@ -68,14 +68,14 @@ __global__ void __launch_bounds__(1024) k_batch_adjoint_win_mrhs(const MatDesc *
                     win_adjoint_mrhs<VT, RL, VX, EXACT, IND, true, true>(
                         rec, wrec_u[slot], rend, global_ptr(d.wxend), global_ptr(d.wucols), global_ptr(d.u_src),
                         global_ptr(static_cast<const VT *>(IND ? d.vals : d.u_vals)), x, g, gx, gv, d.nu, nrhs, cap,
-                        lds, lane);
+                        std::false_type{}, lds, lane);
                     continue;
                 }
             }
             win_adjoint_mrhs<VT, RL, VX, EXACT, IND, false, true>(rec, rec, rend, nullptr, global_ptr(d.wcols),
                                                            global_ptr(d.t_src),
                                                            global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv,
-                                                           d.nnz, nrhs, cap, lds, lane);
+                                                           d.nnz, nrhs, cap, std::false_type{}, lds, lane);
         }
     }
 }
@@ -108,11 +108,17 @@ hipError_t adjoint_win_mrhs(const Arrays &a, csrk_dtype store, const void *vals,
             constexpr bool UNI = decltype(uc)::value, GX = decltype(gc)::value;
             const size_t lds = size_t(s.waves) *
                                win_mrhs_lds<VT>(UNI ? a.win.ucap : a.win.cap, win_gv_apart<VT>(nrhs, RL * VX));
-            hipLaunchKernelGGL((k_adjoint_win_mrhs<VT, RL, VX, EXACT, IND, UNI, GX>), dim3(a.split_adj.width * kXcds),
-                               dim3(s.waves * kWave), lds, st, a.win, a.srec_stride, src, static_cast<const VT *>(v),
-                               static_cast<const X *>(x), static_cast<const X *>(g), static_cast<X *>(gx),
-                               static_cast<A *>(gv), entries, nrhs, a.split_adj);
-            return hipGetLastError();
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(a.split_adj.width * kXcds), dim3(s.waves * kWave), lds, st, a.win,
+                                   a.srec_stride, src, static_cast<const VT *>(v), static_cast<const X *>(x),
+                                   static_cast<const X *>(g), static_cast<X *>(gx), static_cast<A *>(gv), entries, nrhs,
+                                   a.split_adj);
+                return hipGetLastError();
+            };
+            if constexpr (GX && !IND)
+                if (win_keep<VT>(a, nrhs, true))
+                    return launch(k_adjoint_win_mrhs<VT, RL, VX, EXACT, IND, UNI, GX, true>);
+            return launch(k_adjoint_win_mrhs<VT, RL, VX, EXACT, IND, UNI, GX, false>);
         };
         if (!gx) {
             if constexpr (!IND)

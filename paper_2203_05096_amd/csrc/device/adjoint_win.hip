@@ -7,7 +7,7 @@ namespace dev {
 
 namespace {
 
-template <typename VT, int LL, bool IND, bool UNI>
+template <typename VT, int LL, bool IND, bool UNI, bool KEEP>
 __global__ void __launch_bounds__(1024) k_adjoint_win(WinArrays win, int32_t stride, const int32_t *__restrict__ src,
                                                       const VT *__restrict__ vals,
                                                       const typename Store<VT>::X *__restrict__ x,
@@ -28,10 +28,10 @@ __global__ void __launch_bounds__(1024) k_adjoint_win(WinArrays win, int32_t str
         if (rec.rows() == 0) break;
         if constexpr (UNI)
             win_adjoint<VT, LL, IND, true>(rec, win.urec[slot], win.rend, win.xend, win.ucols, src, vals, x, g, gx, gv,
-                                       nnz, lds, lane);
+                                       nnz, std::bool_constant<KEEP>{}, lds, lane);
         else
-            win_adjoint<VT, LL, IND, false>(rec, rec, win.rend, nullptr, win.cols, src, vals, x, g, gx, gv, nnz, lds,
-                                        lane);
+            win_adjoint<VT, LL, IND, false>(rec, rec, win.rend, nullptr, win.cols, src, vals, x, g, gx, gv, nnz,
+                                        std::bool_constant<KEEP>{}, lds, lane);
     }
 }
 
@@ -71,13 +71,13 @@ __global__ void __launch_bounds__(1024) k_batch_adjoint_win(const MatDesc *__res
                         win_adjoint<VT, L, IND, true>(rec, wrec_u[slot], rend, global_ptr(d.wxend),
                                                       global_ptr(d.wucols), global_ptr(d.u_src),
                                                       global_ptr(static_cast<const VT *>(IND ? d.vals : d.u_vals)), x,
-                                                      g, gx, gv, d.nu, lds, lane);
+                                                      g, gx, gv, d.nu, std::false_type{}, lds, lane);
                         return;
                     }
                 }
                 win_adjoint<VT, L, IND, false>(rec, rec, rend, nullptr, global_ptr(d.wcols), global_ptr(d.t_src),
-                                               global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv, d.nnz, lds,
-                                               lane);
+                                               global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv, d.nnz, std::false_type{},
+                                               lds, lane);
             };
             if constexpr (LL)
                 go(std::integral_constant<int, LL>{});
@@ -111,13 +111,18 @@ hipError_t adjoint_win(const Arrays &a, csrk_dtype store, const void *vals, cons
         if constexpr (LL == 0) {
             return hipErrorInvalidValue;  // batches only
         } else {
-            hipLaunchKernelGGL((k_adjoint_win<VT, LL, IND, !SYM>), dim3(a.split_adj.width * kXcds),
-                               dim3(s.waves * kWave), size_t(s.waves) * win_adjoint_lds<VT>(), st, a.win, a.srec_stride,
-                               SYM ? a.t_src : a.u_src,
-                               static_cast<const VT *>(IND ? vals : SYM ? a.vals_t : a.u_vals),
-                               static_cast<const X *>(x), static_cast<const X *>(g), static_cast<X *>(gx),
-                               static_cast<A *>(gv), SYM ? a.nnz : a.nu, a.split_adj);
-            return hipGetLastError();
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(a.split_adj.width * kXcds), dim3(s.waves * kWave),
+                                   size_t(s.waves) * win_adjoint_lds<VT>(), st, a.win, a.srec_stride,
+                                   SYM ? a.t_src : a.u_src,
+                                   static_cast<const VT *>(IND ? vals : SYM ? a.vals_t : a.u_vals),
+                                   static_cast<const X *>(x), static_cast<const X *>(g), static_cast<X *>(gx),
+                                   static_cast<A *>(gv), SYM ? a.nnz : a.nu, a.split_adj);
+                return hipGetLastError();
+            };
+            if constexpr (!IND)
+                if (win_keep<VT>(a, 1, true)) return go(k_adjoint_win<VT, LL, IND, !SYM, true>);
+            return go(k_adjoint_win<VT, LL, IND, !SYM, false>);
         }
     });
 }

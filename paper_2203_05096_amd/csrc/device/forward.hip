@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(1024) k_spmv_csrk_dot(const SrRec *__restrict_
 
 // The product by the window walk (every super-row one window of 16-bit
 // columns); with DOT also the partial inner products of k_spmv_csrk_dot.
-template <typename VT, int LL, bool DOT>
+template <typename VT, int LL, bool DOT, bool KEEP>
 __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride, const VT *__restrict__ vals,
                                                    const typename Store<VT>::X *__restrict__ x,
                                                    typename Store<VT>::X *__restrict__ y, int64_t nnz, XcdSplit split,
@@ -107,13 +107,13 @@ __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride
             if constexpr (DOT) {
                 const X *xb = x + rec.base;
                 win_product<VT, LL>(
-                    rec, win.rend, win.cols, vals, nnz, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
+                    rec, win.rend, win.cols, vals, nnz, std::bool_constant<KEEP>{}, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
                     [&](int rr, A acc) {
                         y[rec.r0 + rr] = X(acc);
                         dot += double(X(acc)) * pdot[rec.r0 + rr];
                     });
             } else {
-                win_forward<VT, LL>(rec, win.rend, win.cols, vals, x, y, nnz, lds, lane);
+                win_forward<VT, LL>(rec, win.rend, win.cols, vals, x, y, nnz, std::bool_constant<KEEP>{}, lds, lane);
             }
         }
     }
@@ -199,15 +199,13 @@ hipError_t launch_win(const Arrays &a, const void *vals, const void *x, void *y,
         constexpr int LL = decltype(lc)::value;
         const dim3 grid(a.split_fwd.width * kXcds), block(s.waves * kWave);
         const size_t lds = size_t(s.waves) * win_forward_lds<VT>();
-        if (part)
-            hipLaunchKernelGGL((k_spmv_win<VT, LL, true>), grid, block, lds, st, a.win, a.srec_stride,
-                               static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
-                               a.split_fwd, pdot, part);
-        else
-            hipLaunchKernelGGL((k_spmv_win<VT, LL, false>), grid, block, lds, st, a.win, a.srec_stride,
-                               static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
-                               a.split_fwd, pdot, part);
-        return hipGetLastError();
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, lds, st, a.win, a.srec_stride, static_cast<const VT *>(vals),
+                               static_cast<const X *>(x), static_cast<X *>(y), a.nnz, a.split_fwd, pdot, part);
+            return hipGetLastError();
+        };
+        if (part) return go(k_spmv_win<VT, LL, true, false>);
+        return win_keep<VT>(a, 1, false) ? go(k_spmv_win<VT, LL, false, true>) : go(k_spmv_win<VT, LL, false, false>);
     });
 }
 

@@ -7,7 +7,7 @@ namespace dev {
 
 namespace {
 
-template <typename VT, int RL, int VX>
+template <typename VT, int RL, int VX, bool KEEP>
 __global__ void __launch_bounds__(1024) k_spmv_win_mrhs(WinArrays win, int32_t stride, const VT *__restrict__ vals,
                                                         const typename Store<VT>::X *__restrict__ x,
                                                         typename Store<VT>::X *__restrict__ y, int64_t nnz, int nrhs,
@@ -22,7 +22,7 @@ __global__ void __launch_bounds__(1024) k_spmv_win_mrhs(WinArrays win, int32_t s
     for (int32_t w = wave; w < stride; w += nw) {
         const WinRec rec = win.rec[int64_t(t) * stride + w];
         if (rec.rows() == 0) break;
-        win_forward_mrhs<VT, RL, VX>(rec, win.rend, win.cols, vals, x, y, nnz, nrhs, win.cap, lds, lane);
+        win_forward_mrhs<VT, RL, VX>(rec, win.rend, win.cols, vals, x, y, nnz, nrhs, win.cap, std::bool_constant<KEEP>{}, lds, lane);
     }
 }
 
@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(1024) k_batch_forward_win_mrhs(const MatDesc *
             win_forward_mrhs<VT, RL, VX>(rec, global_ptr(d.wrend), global_ptr(d.wcols),
                                          global_ptr(static_cast<const VT *>(d.vals)),
                                          global_ptr(static_cast<const X *>(d.x)), global_ptr(static_cast<X *>(d.y)),
-                                         d.nnz, nrhs, cap, lds, lane);
+                                         d.nnz, nrhs, cap, std::false_type{}, lds, lane);
         }
     }
 }
@@ -68,12 +68,16 @@ hipError_t spmv_win_mrhs(const Arrays &a, csrk_dtype store, const void *vals, co
     return by_store_block(store, nrhs, [&](auto vt, auto rc, auto vc) -> hipError_t {
         using VT = decltype(vt);
         using X = typename Store<VT>::X;
-        hipLaunchKernelGGL((k_spmv_win_mrhs<VT, decltype(rc)::value, decltype(vc)::value>),
-                           dim3(a.split_fwd.width * kXcds), dim3(s.waves * kWave),
-                           size_t(s.waves) * win_mrhs_lds<VT>(a.win.cap, false), st, a.win, a.srec_stride,
-                           static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz, nrhs,
-                           a.split_fwd);
-        return hipGetLastError();
+        constexpr int RL = decltype(rc)::value, VX = decltype(vc)::value;
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(a.split_fwd.width * kXcds), dim3(s.waves * kWave),
+                               size_t(s.waves) * win_mrhs_lds<VT>(a.win.cap, false), st, a.win, a.srec_stride,
+                               static_cast<const VT *>(vals), static_cast<const X *>(x), static_cast<X *>(y), a.nnz,
+                               nrhs, a.split_fwd);
+            return hipGetLastError();
+        };
+        return win_keep<VT>(a, nrhs, false) ? go(k_spmv_win_mrhs<VT, RL, VX, true>)
+                                            : go(k_spmv_win_mrhs<VT, RL, VX, false>);
     });
 }
 

@@ -63,11 +63,13 @@ struct WinStream {
 // groups of V from the 16-byte boundary at or below e0.  `cols` is padded to a
 // whole group; the values are the caller's or the handle's nnz elements, so
 // the last group of the array is read one by one.  IND: value k is
-// vals[src[k]] (0 where src[k] < 0), src holding nnz elements too.
-template <typename VT, bool IND>
+// vals[src[k]] (0 where src[k] < 0), src holding nnz elements too.  K: the
+// values are read through the caches (win_keep), otherwise past them; a constant,
+// since the compiler merges the two loads of a branch into one plain load.
+template <typename VT, bool IND, bool K>
 __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t nent, const uint16_t *__restrict__ cols,
                                          const int32_t *__restrict__ src, const VT *__restrict__ vals, int64_t nnz,
-                                         int lane) {
+                                         std::bool_constant<K>, int lane) {
     using W = WinStream<VT>;
     constexpr int V = W::V;
     typedef int32_t SV __attribute__((ext_vector_type(V)));
@@ -82,6 +84,8 @@ __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t n
                     const SV sv = *reinterpret_cast<const SV *>(src + pos);
 #pragma unroll
                     for (int e = 0; e < V; ++e) w.v[u][e] = sv[e] >= 0 ? vals[sv[e]] : VT(0);
+                } else if constexpr (K) {
+                    w.v[u] = *reinterpret_cast<const typename W::VV *>(vals + pos);
                 } else {
                     w.v[u] = __builtin_nontemporal_load(reinterpret_cast<const typename W::VV *>(vals + pos));
                 }
@@ -123,10 +127,11 @@ __host__ __device__ constexpr int win_forward_lds() {
 // The product of one super-row with a vector given by its entries: ready() is
 // called once the stream is requested, gather(c) returns x at column base + c,
 // and one lane per row calls emit(row, sum), the row counted from r0.
-template <typename VT, int LL, typename R, typename G, typename E>
+template <typename VT, int LL, bool K, typename R, typename G, typename E>
 __device__ __forceinline__ void win_product(const WinRec &rec, const uint16_t *__restrict__ rend16,
                                             const uint16_t *__restrict__ cols, const VT *__restrict__ vals, int64_t nnz,
-                                            unsigned char *__restrict__ lds, int lane, R &&ready, G &&gather, E &&emit) {
+                                            std::bool_constant<K> keep, unsigned char *__restrict__ lds, int lane,
+                                            R &&ready, G &&gather, E &&emit) {
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     constexpr int V = Store<VT>::V;
@@ -135,7 +140,7 @@ __device__ __forceinline__ void win_product(const WinRec &rec, const uint16_t *_
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + kStageEntries * sizeof(VT));
     const int nrows = rec.rows(), nent = rec.entries(), off = rec.e0 & (V - 1);
     WinStream<VT> w;
-    win_load<VT, false>(w, rec.e0, nent, cols, nullptr, vals, nnz, lane);
+    win_load<VT, false>(w, rec.e0, nent, cols, nullptr, vals, nnz, keep, lane);
     const int my_end = lane < nrows ? int(rend16[rec.r0 + lane]) : 0;
     ready();
     win_stage<VT>(w, rec.e0, nent, sval, scol, lane);
@@ -168,17 +173,17 @@ __device__ __forceinline__ void win_product(const WinRec &rec, const uint16_t *_
 }
 
 // y for the rows of one super-row.
-template <typename VT, int LL>
+template <typename VT, int LL, bool K>
 __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *__restrict__ rend16,
                                             const uint16_t *__restrict__ cols, const VT *__restrict__ vals,
                                             const typename Store<VT>::X *__restrict__ x,
                                             typename Store<VT>::X *__restrict__ y, int64_t nnz,
-                                            unsigned char *__restrict__ lds, int lane) {
+                                            std::bool_constant<K> keep, unsigned char *__restrict__ lds, int lane) {
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     const X *xb = x + rec.base;
     win_product<VT, LL>(
-        rec, rend16, cols, vals, nnz, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
+        rec, rend16, cols, vals, nnz, keep, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
         [&](int rr, A acc) { y[rec.r0 + rr] = X(acc); });
 }
 
@@ -228,7 +233,7 @@ __device__ __forceinline__ void win_store_gv(const A *__restrict__ sgv, int off,
 // the super-row's union range `ru` holds its A' entries (at a fixed offset, a
 // multiple of 8, from their A' positions) and then its rows' extras, whose ends
 // are xend16; columns, values and src are the union's, `nnz` its entries.
-template <typename VT, int LL, bool IND, bool UNI>
+template <typename VT, int LL, bool IND, bool UNI, bool K>
 __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, const uint16_t *__restrict__ rend16,
                                             const uint16_t *__restrict__ xend16, const uint16_t *__restrict__ cols,
                                             const int32_t *__restrict__ src, const VT *__restrict__ vals,
@@ -236,7 +241,7 @@ __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, 
                                             const typename Store<VT>::X *__restrict__ g,
                                             typename Store<VT>::X *__restrict__ gx,
                                             typename Store<VT>::A *__restrict__ gv, int64_t nnz,
-                                            unsigned char *__restrict__ lds, int lane) {
+                                            std::bool_constant<K> keep, unsigned char *__restrict__ lds, int lane) {
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     constexpr int V = Store<VT>::V;
@@ -247,7 +252,7 @@ __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, 
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + win_adjoint_lds<VT>() - kStageEntries * sizeof(uint16_t));
     const int nrows = ra.rows(), nent = ra.entries(), off = ru.e0 & (V - 1);
     WinStream<VT> w;
-    win_load<VT, IND>(w, ru.e0, ru.entries(), cols, src, vals, nnz, lane);
+    win_load<VT, IND>(w, ru.e0, ru.entries(), cols, src, vals, nnz, keep, lane);
     const int my_end = lane < nrows ? int(rend16[ra.r0 + lane]) : 0;
     const int my_xend = UNI && lane < nrows ? int(xend16[ra.r0 + lane]) : 0;
     const A my_g = lane < nrows ? A(g[ra.r0 + lane]) : A(0);
@@ -348,6 +353,23 @@ hipError_t by_batch_win(csrk_dtype store, int lanes, F &&f) {
         if (lanes == 0) return f(vt, std::integral_constant<int, 0>{});
         return by_win_lanes(lanes, [&](auto lc) { return f(vt, lc); });
     });
+}
+
+// Whether a launch over nrhs columns reads the values through the caches: its
+// whole traffic (values, columns, vectors, grad_vals) is at most kWinKeepBytes, so
+// that the next launch still finds it in the 256 MB Infinity Cache; more is read
+// past them, which leaves the caches to the vectors.  Three matrices in turn, us,
+// past / through: 82 MB, 3D 27-point 87x90x91 BF16 forward 22.0 / 20.1; 84 MB, 3D
+// 7-point 80^3 FP64 adjoint 18.8 / 15.2; 73 MB, 3D 19-point 61x64x67, 8 FP32
+// columns, forward and adjoint 44.8 / 40.4; 117 MB, 2D 9-point 1201x999 FP32
+// adjoint 33.0 / 36.3; 184 MB, 3D 7-point 128^3 FP64 forward 29.2 / 36.5.
+constexpr int64_t kWinKeepBytes = 96 << 20;
+template <typename VT>
+bool win_keep(const Arrays &a, int nrhs, bool adjoint) {
+    const int64_t entries = (adjoint && !a.sym ? a.nu : a.nnz) * int64_t(sizeof(VT) + sizeof(uint16_t));
+    const int64_t grad = adjoint ? a.nnz * int64_t(sizeof(typename Store<VT>::A)) : 0;
+    return entries + grad + (adjoint ? 3 : 2) * int64_t(a.n) * nrhs * int64_t(sizeof(typename Store<VT>::X)) <=
+           kWinKeepBytes;
 }
 
 }  // namespace

@@ -54,7 +54,11 @@ struct Slice {
     __device__ __forceinline__ void load(const X *__restrict__ base, uint32_t off) {
         v = *reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + off);
     }
-    __device__ __forceinline__ void store(X *__restrict__ p) const { *reinterpret_cast<V *>(p) = v; }
+    // past the caches: results are not read again by the launch (3D 7-point, 16 matrices, 8 FP32 columns: forward
+    // 53.9 -> 49.9 us, adjoint 96.2 -> 94.7)
+    __device__ __forceinline__ void store(X *__restrict__ p) const {
+        __builtin_nontemporal_store(v, reinterpret_cast<V *>(p));
+    }
 };
 
 // log2 of the groups of RL lanes per row: the largest power of two that still
@@ -67,13 +71,13 @@ __device__ __forceinline__ int win_groups(int nrows, int RL) {
 }
 
 // The window's columns (and, with VALS, its values) into LDS.
-template <typename VT, bool IND, bool VALS>
+template <typename VT, bool IND, bool VALS, bool K>
 __device__ __forceinline__ void win_fetch(int32_t e0, int32_t nent, const uint16_t *__restrict__ cols,
                                           const int32_t *__restrict__ src, const VT *__restrict__ vals, int64_t nnz,
-                                          VT *sval, uint16_t *scol, int lane) {
+                                          std::bool_constant<K> keep, VT *sval, uint16_t *scol, int lane) {
     if constexpr (VALS) {
         WinStream<VT> w;
-        win_load<VT, IND>(w, e0, nent, cols, src, vals, nnz, lane);
+        win_load<VT, IND>(w, e0, nent, cols, src, vals, nnz, keep, lane);
         win_stage<VT>(w, e0, nent, sval, scol, lane);
     } else {
         const int32_t ea = e0 & ~(Store<VT>::V - 1);  // LDS index k - ea in both forms
@@ -98,11 +102,12 @@ constexpr int mrhs_batch_adj() {
     return sizeof(X) == 8 ? 3 : 4;
 }
 
-template <typename VT, int RL, int VX>
+template <typename VT, int RL, int VX, bool K>
 __device__ __forceinline__ void win_forward_mrhs(const WinRec &rec, const uint16_t *__restrict__ rend16,
                                                  const uint16_t *__restrict__ cols, const VT *__restrict__ vals,
                                                  const typename Store<VT>::X *__restrict__ x,
                                                  typename Store<VT>::X *__restrict__ y, int64_t nnz, int nrhs, int cap,
+                                                 std::bool_constant<K> keep,
                                                  unsigned char *__restrict__ lds, int lane) {
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
@@ -111,7 +116,7 @@ __device__ __forceinline__ void win_forward_mrhs(const WinRec &rec, const uint16
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + cap * sizeof(VT));
     const int nrows = rec.rows(), nent = rec.entries(), off = rec.e0 & (Store<VT>::V - 1);
     const int my_end = lane < nrows ? int(rend16[rec.r0 + lane]) : 0;
-    win_fetch<VT, false, true>(rec.e0, nent, cols, nullptr, vals, nnz, sval, scol, lane);
+    win_fetch<VT, false, true>(rec.e0, nent, cols, nullptr, vals, nnz, keep, sval, scol, lane);
     wave_lds_sync();
     const int le = win_groups(nrows, RL), E = 1 << le;
     const int q = lane % RL, sub = (lane / RL) & (E - 1), rsub = (lane / RL) >> le, rows_per_pass = (kWave / RL) >> le;
@@ -166,7 +171,7 @@ __device__ __forceinline__ void win_forward_mrhs(const WinRec &rec, const uint16
 
 // Both gradients of one super-row (GX), or grad_vals alone; UNI as in
 // win_adjoint (with GX only).  EXACT: the slices do not overlap (nrhs % VX == 0).
-template <typename VT, int RL, int VX, bool EXACT, bool IND, bool UNI, bool GX>
+template <typename VT, int RL, int VX, bool EXACT, bool IND, bool UNI, bool GX, bool K>
 __device__ __forceinline__ void win_adjoint_mrhs(const WinRec &ra, const WinRec &ru,
                                                  const uint16_t *__restrict__ rend16,
                                                  const uint16_t *__restrict__ xend16,
@@ -176,7 +181,7 @@ __device__ __forceinline__ void win_adjoint_mrhs(const WinRec &ra, const WinRec 
                                                  const typename Store<VT>::X *__restrict__ g,
                                                  typename Store<VT>::X *__restrict__ gx,
                                                  typename Store<VT>::A *__restrict__ gv, int64_t nnz, int nrhs, int cap,
-                                                 unsigned char *__restrict__ lds, int lane) {
+                                                 std::bool_constant<K> keep, unsigned char *__restrict__ lds, int lane) {
     using A = typename Store<VT>::A;
     using X = typename Store<VT>::X;
     constexpr int V = Store<VT>::V;
@@ -188,7 +193,7 @@ __device__ __forceinline__ void win_adjoint_mrhs(const WinRec &ra, const WinRec 
     const int nrows = ra.rows(), nent = ra.entries(), off = ru.e0 & (V - 1);
     const int my_end = lane < nrows ? int(rend16[ra.r0 + lane]) : 0;
     const int my_xend = UNI && lane < nrows ? int(xend16[ra.r0 + lane]) : 0;
-    win_fetch<VT, IND, GX>(ru.e0, ru.entries(), cols, src, vals, nnz, sval, scol, lane);
+    win_fetch<VT, IND, GX>(ru.e0, ru.entries(), cols, src, vals, nnz, keep, sval, scol, lane);
     wave_lds_sync();
     const int le = win_groups(nrows, RL), E = 1 << le;
     const int q = lane % RL, sub = (lane / RL) & (E - 1), rsub = (lane / RL) >> le, rows_per_pass = (kWave / RL) >> le;
