@@ -75,8 +75,12 @@ typedef enum csrk_reorder { CSRK_REORDER_BANDK = 0, CSRK_REORDER_RCM = 1, CSRK_R
 
 /* Tuning parameters.  srs = rows per super-row (SRS), ssrs = super-rows per
  * super-super-row (SSRS) (Section 4.1).  lanes_per_row (1, 2, 4, ..., 64) is
- * the number of wavefront lanes that reduce one row; waves_per_wg (1..16) the
- * wavefronts per workgroup.  k is the number of CSR-k levels, 2..8 (Section
+ * the number of wavefront lanes that reduce one row (in the general walk; a
+ * matrix whose super-rows, or the pieces that launches cut them into, all fit
+ * one staging window with columns within 65536 of each other gives a row the
+ * lanes that its super-row leaves); waves_per_wg (1..16) the wavefronts per
+ * workgroup (at least 8 in a launch over one matrix with rows longer than
+ * CSRK_LONG_ROW).  k is the number of CSR-k levels, 2..8 (Section
  * 2.2 defines CSR-k for every k >= 2): k - 1 grouping levels above the rows.
  * k = 3 (CSR-3): super-rows and super-super-rows.  k = 2 (CSR-2): one
  * coarsening level, Band-k orders the coarse graph by reverse Cuthill-McKee;
@@ -286,7 +290,9 @@ csrk_status csrk_copy_device_vals(csrk_handle h, void *dst_dev, void *stream);
 
 /*
  * csrk_spmv — y' = A' x' (Section 1 statement of SpMV on the CSR-k arrays;
- * one super-super-row per workgroup, one super-row per wavefront, Section 3).
+ * one super-super-row per workgroup, one super-row per wavefront, Section 3;
+ * where a super-row has more than 64 rows or 504 entries, its windows of whole
+ * rows within both, grouped evenly).
  * vals_dev: NULL = the handle's values, else nnz values of the storage type
  * in CSR-k order (16-byte aligned).  x_dev, y_dev: n x nrhs row-major in
  * permuted space; FP64 for F64 storage, FP32 otherwise.  y must not alias x.
