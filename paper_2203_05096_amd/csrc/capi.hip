@@ -219,7 +219,11 @@ int32_t window_lanes(const csrk_matrix *h) {
 // carry.  Irregular matrices used to be walked super-row by super-row, one
 // wavefront each: super-rows of up to 2048 entries took four windows in turn.
 // An R-MAT graph of 2^18 rows (mean 8.7, longest row about 10,000 entries):
-// forward 30 us, adjoint 46 us then; see the launch rule at kLongRowWaves.
+// forward 30 us, adjoint 46 us then, 17.5 and 29.8 now.  What bounds it now is the
+// gathers, a cache line of its own each (2.3 M entries x 128 B from L2, twice that in
+// the adjoint): without any work on the long rows the same launches take 15.4 and
+// 28.6 us, and a long row's next window requested ahead changed nothing (2^20 rows:
+// forward 59.2 -> 65.4 us, for the registers).
 void launch_shape(csrk_matrix *h) {
     using namespace csrk::dev;
     const int32_t waves = has_long_rows(h) ? std::max(h->params.waves_per_wg, kLongRowWaves) : h->params.waves_per_wg;

@@ -76,8 +76,8 @@ __global__ void __launch_bounds__(1024) k_batch_adjoint_win(const MatDesc *__res
                     }
                 }
                 win_adjoint<VT, L, IND, false>(rec, rec, rend, nullptr, global_ptr(d.wcols), global_ptr(d.t_src),
-                                               global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv, d.nnz, std::false_type{},
-                                               lds, lane);
+                                               global_ptr(static_cast<const VT *>(d.vals)), x, g, gx, gv, d.nnz,
+                                               std::false_type{}, lds, lane);
             };
             if constexpr (LL)
                 go(std::integral_constant<int, LL>{});

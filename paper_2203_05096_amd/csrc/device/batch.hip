@@ -74,7 +74,8 @@ __global__ void __launch_bounds__(1024) k_batch_forward_win(const MatDesc *__res
                 win_forward<VT, decltype(lc)::value>(rec, global_ptr(d.wrend), global_ptr(d.wcols),
                                                      global_ptr(static_cast<const VT *>(d.vals)),
                                                      global_ptr(static_cast<const X *>(d.x)),
-                                                     global_ptr(static_cast<X *>(d.y)), d.nnz, std::false_type{}, lds, lane);
+                                                     global_ptr(static_cast<X *>(d.y)), d.nnz, std::false_type{}, lds,
+                                                     lane);
             };
             if constexpr (LL)
                 go(std::integral_constant<int, LL>{});

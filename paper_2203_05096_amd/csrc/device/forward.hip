@@ -107,7 +107,8 @@ __global__ void __launch_bounds__(1024) k_spmv_win(WinArrays win, int32_t stride
             if constexpr (DOT) {
                 const X *xb = x + rec.base;
                 win_product<VT, LL>(
-                    rec, win.rend, win.cols, vals, nnz, std::bool_constant<KEEP>{}, lds, lane, [] {}, [&](uint32_t c) { return xb[c]; },
+                    rec, win.rend, win.cols, vals, nnz, std::bool_constant<KEEP>{}, lds, lane, [] {},
+                    [&](uint32_t c) { return xb[c]; },
                     [&](int rr, A acc) {
                         y[rec.r0 + rr] = X(acc);
                         dot += double(X(acc)) * pdot[rec.r0 + rr];

@@ -22,7 +22,8 @@ __global__ void __launch_bounds__(1024) k_spmv_win_mrhs(WinArrays win, int32_t s
     for (int32_t w = wave; w < stride; w += nw) {
         const WinRec rec = win.rec[int64_t(t) * stride + w];
         if (rec.rows() == 0) break;
-        win_forward_mrhs<VT, RL, VX>(rec, win.rend, win.cols, vals, x, y, nnz, nrhs, win.cap, std::bool_constant<KEEP>{}, lds, lane);
+        win_forward_mrhs<VT, RL, VX>(rec, win.rend, win.cols, vals, x, y, nnz, nrhs, win.cap,
+                                     std::bool_constant<KEEP>{}, lds, lane);
     }
 }
 
