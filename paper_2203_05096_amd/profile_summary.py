@@ -99,8 +99,8 @@ def traffic(args):
         raise SystemExit("no calibration copy dispatches (run bench.py with --copy-calibration)")
     fs, ws = GIB / (cf * 1024), GIB / (cw * 1024)
     per = {}
-    for direction, prefixes in (("forward", ("k_batch_forward", "k_spmv_csrk<", "k_spmv_csrk_mrhs")),
-                                ("adjoint", ("k_batch_adjoint", "k_adjoint_csrk"))):
+    for direction, prefixes in (("forward", ("k_batch_forward", "k_spmv_win", "k_spmv_csrk<", "k_spmv_csrk_mrhs")),
+                                ("adjoint", ("k_batch_adjoint", "k_adjoint_win", "k_adjoint_csrk"))):
         names = [k for k in fetch if k.startswith(prefixes)]
         if not names:
             continue
