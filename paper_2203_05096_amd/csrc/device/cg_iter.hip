@@ -28,12 +28,37 @@ namespace {
 
 constexpr int kBlock = 256;
 
+// Threads per workgroup of the passes over the vectors.  Every workgroup reads the
+// whole list of parts, so many rows take few, large ones: at 128^3 rows 1024 of 256
+// threads read 134 MB of parts of p . q out of L2, 256 of 1024 a quarter of it (50
+// iterations, us, FP64: 3363 -> 3046; 97x91x88 1671 -> 1583).  Fewer rows take small
+// ones, which then reach more of the CUs (64^3 gives every CU one).
+constexpr int kWideBlock = 1024;
+constexpr int64_t kWideRows = 1 << 19;
+int cg_block(int64_t n) { return n > kWideRows ? kWideBlock : kBlock; }
+
+// part[first], part[first + step], ... below count, added in that order.  B are
+// requested at a time, the last batch filled up with zeros: each batch waits once
+// for L2.  50 iterations, us, eights with the rest one by one -> sixteens: 3D
+// 7-point 97x91x88 FP64 1774 -> 1671, 128^3 3396 -> 3363.
+template <int B>
+__device__ __forceinline__ double part_sum(const double *__restrict__ part, int count, int first, int step) {
+    double acc = 0;
+    for (int i = first; i < count; i += B * step) {
+        double v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = i + u * step < count ? part[i + u * step] : 0.0;
+#pragma unroll
+        for (int u = 0; u < B; ++u) acc += v[u];
+    }
+    return acc;
+}
+
 // part[0..count) added by one wavefront: lane l takes l, l + 64, ..., then the
 // lanes in a fixed order; the same bits in every lane of every wavefront.
+template <int B>
 __device__ __forceinline__ double wave_total(const double *__restrict__ part, int count, int lane) {
-    double acc = 0;
-#pragma unroll 4
-    for (int i = lane; i < count; i += kWave) acc += part[i];
+    double acc = part_sum<B>(part, count, lane, kWave);
 #pragma unroll
     for (int off = kWave / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
     return acc;
@@ -61,7 +86,7 @@ __global__ void __launch_bounds__(1024) k_cg_product(WinArrays win, int32_t stri
     auto scalars = [&]() {
         if (known) return;
         known = true;
-        const double rr = wave_total(rr_part, rr_parts, lane);
+        const double rr = wave_total<4>(rr_part, rr_parts, lane);
         if (blockIdx.x == 0 && threadIdx.x == 0) s[6 + (it & 1)] = rr;
         if (it > 0) {
             alpha = s[2];
@@ -109,13 +134,13 @@ __global__ void __launch_bounds__(1024) k_cg_product(WinArrays win, int32_t stri
 
 // r -= alpha q; rr_part[block] = its part of r . r.  The first elements are
 // requested before alpha is summed.
-template <typename TQ>
-__global__ void __launch_bounds__(kBlock) k_cg_residual(double *__restrict__ r, const TQ *__restrict__ q, int64_t n,
+template <typename TQ, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_cg_residual(double *__restrict__ r, const TQ *__restrict__ q, int64_t n,
                                                         const double *__restrict__ pq_part, int pq_parts,
                                                         double *__restrict__ s, int it, double *__restrict__ rr_part) {
     constexpr int W = 4;
-    __shared__ double sh[2][kBlock / kWave];
-    const int64_t step = int64_t(gridDim.x) * kBlock, first = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+    __shared__ double sh[2][BLOCK / kWave];
+    const int64_t step = int64_t(gridDim.x) * BLOCK, first = int64_t(blockIdx.x) * BLOCK + threadIdx.x;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     double rv[W], qv[W];
     auto load = [&](int64_t i) {
@@ -128,15 +153,13 @@ __global__ void __launch_bounds__(kBlock) k_cg_residual(double *__restrict__ r, 
     };
     load(first);
     const double rr = s[6 + (it & 1)];
-    double pq = 0;
-#pragma unroll 8
-    for (int i = threadIdx.x; i < pq_parts; i += kBlock) pq += pq_part[i];
+    double pq = part_sum<16>(pq_part, pq_parts, threadIdx.x, BLOCK);
 #pragma unroll
     for (int off = kWave / 2; off >= 1; off >>= 1) pq += __shfl_xor(pq, off);
     if (lane == 0) sh[0][wave] = pq;
     __syncthreads();
     pq = 0;
-    for (int w = 0; w < kBlock / kWave; ++w) pq += sh[0][w];
+    for (int w = 0; w < BLOCK / kWave; ++w) pq += sh[0][w];
     const double alpha = rr / pq;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         s[1] = pq;
@@ -160,7 +183,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_residual(double *__restrict__ r, 
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0;
-        for (int w = 0; w < kBlock / kWave; ++w) t += sh[1][w];
+        for (int w = 0; w < BLOCK / kWave; ++w) t += sh[1][w];
         rr_part[blockIdx.x] = t;
     }
 }
@@ -175,28 +198,48 @@ __global__ void __launch_bounds__(kBlock) k_cg_last(double *__restrict__ x, cons
 
 // Three launches: beta = r . r / its value before, x += alpha p, p = r + beta p,
 // and p_lo = p in the product's vector type when that is not FP64.
-__global__ void __launch_bounds__(kBlock) k_cg_update(double *__restrict__ x, double *__restrict__ p,
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_cg_update(double *__restrict__ x, double *__restrict__ p,
                                                       float *__restrict__ p_lo, const double *__restrict__ r, int64_t n,
                                                       const double *__restrict__ rr_part, int rr_parts,
                                                       double *__restrict__ s, int it) {
+    constexpr int W = 4;
+    const int64_t step = int64_t(gridDim.x) * BLOCK, first = int64_t(blockIdx.x) * BLOCK + threadIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
-    const double rr = wave_total(rr_part, rr_parts, lane);
+    double xv[W], pv[W], rv[W];
+    auto load = [&](int64_t i) {
+#pragma unroll
+        for (int u = 0; u < W; ++u) {
+            const bool in = i + u * step < n;
+            xv[u] = in ? x[i + u * step] : 0.0;
+            pv[u] = in ? p[i + u * step] : 0.0;
+            rv[u] = in ? r[i + u * step] : 0.0;
+        }
+    };
+    load(first);
+    const double rr = wave_total<16>(rr_part, rr_parts, lane);
     const double alpha = s[2], beta = rr / s[6 + (it & 1)];
     if (blockIdx.x == 0 && threadIdx.x == 0) s[6 + ((it + 1) & 1)] = rr;
-    for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += int64_t(gridDim.x) * kBlock) {
-        const double pi = p[i];
-        x[i] = __builtin_fma(alpha, pi, x[i]);
-        const double pn = __builtin_fma(beta, pi, r[i]);
-        p[i] = pn;
-        if (p_lo) p_lo[i] = float(pn);
+    for (int64_t i = first; i < n; i += W * step) {
+        if (i != first) load(i);
+#pragma unroll
+        for (int u = 0; u < W; ++u) {
+            const int64_t at = i + u * step;
+            if (at >= n) break;
+            x[at] = __builtin_fma(alpha, pv[u], xv[u]);
+            const double pn = __builtin_fma(beta, pv[u], rv[u]);
+            p[at] = pn;
+            if (p_lo) p_lo[at] = float(pn);
+        }
     }
 }
 
 }  // namespace
 
 int cg_iter_grid(int64_t n) {
-    const int64_t g = (n + 4 * kBlock - 1) / (4 * kBlock);  // one batch of loads per thread
-    return int(g < 1 ? 1 : (g > kCgGrid ? kCgGrid : g));
+    const int64_t per = 4 * cg_block(n), g = (n + per - 1) / per;  // one batch of loads per thread
+    const int64_t most = int64_t(kCgGrid) * kBlock / cg_block(n);
+    return int(g < 1 ? 1 : (g > most ? most : g));
 }
 
 namespace {
@@ -231,21 +274,28 @@ hipError_t product_two(const Arrays &a, csrk_dtype store, const void *vals, cons
 hipError_t cg_iteration(const Arrays &a, csrk_dtype store, const void *vals, const CgIter &w, int it, Shape s,
                         hipStream_t st) {
     const int parts = spmv_grid(a);
-    const dim3 grid(cg_iter_grid(a.n)), block(kBlock);
+    const dim3 grid(cg_iter_grid(a.n));
     if (!w.two && it == 0) hipLaunchKernelGGL(k_cg_first, dim3(1), dim3(1), 0, st, w.s);
     const void *in = store == CSRK_F64 ? static_cast<const void *>(w.p[0]) : static_cast<const void *>(w.p_lo);
     const hipError_t e = w.two ? product_two(a, store, vals, w, it, s, st)
                                : spmv_dot(a, store, vals, in, w.q, w.p[0], w.pq_part, s, st);
     if (e != hipSuccess) return e;
-    if (store == CSRK_F64)
-        hipLaunchKernelGGL((k_cg_residual<double>), grid, block, 0, st, w.r, static_cast<const double *>(w.q),
-                           int64_t(a.n), w.pq_part, parts, w.s, it, w.rr_part);
+    auto passes = [&](auto bc) {
+        constexpr int BLOCK = decltype(bc)::value;
+        if (store == CSRK_F64)
+            hipLaunchKernelGGL((k_cg_residual<double, BLOCK>), grid, dim3(BLOCK), 0, st, w.r,
+                               static_cast<const double *>(w.q), int64_t(a.n), w.pq_part, parts, w.s, it, w.rr_part);
+        else
+            hipLaunchKernelGGL((k_cg_residual<float, BLOCK>), grid, dim3(BLOCK), 0, st, w.r,
+                               static_cast<const float *>(w.q), int64_t(a.n), w.pq_part, parts, w.s, it, w.rr_part);
+        if (!w.two)
+            hipLaunchKernelGGL((k_cg_update<BLOCK>), grid, dim3(BLOCK), 0, st, w.x, w.p[0], w.p_lo, w.r, int64_t(a.n),
+                               w.rr_part, int(grid.x), w.s, it);
+    };
+    if (cg_block(a.n) == kBlock)
+        passes(std::integral_constant<int, kBlock>{});
     else
-        hipLaunchKernelGGL((k_cg_residual<float>), grid, block, 0, st, w.r, static_cast<const float *>(w.q),
-                           int64_t(a.n), w.pq_part, parts, w.s, it, w.rr_part);
-    if (!w.two)
-        hipLaunchKernelGGL(k_cg_update, grid, block, 0, st, w.x, w.p[0], w.p_lo, w.r, int64_t(a.n), w.rr_part,
-                           int(grid.x), w.s, it);
+        passes(std::integral_constant<int, kWideBlock>{});
     return hipGetLastError();
 }
 

@@ -230,3 +230,11 @@ def test_cg_launch_rules(side, band_rows, store):
     x, it, rel = M.cg(bd, x0=x, rtol=rtol, max_iter=500, check_every=1)  # from the solution: at most a few iterations
     assert it <= 7
     M.close()
+
+
+@pytest.mark.parametrize("rows", [1 << 19, (1 << 19) + 1, (1 << 20) + 4097])
+@pytest.mark.parametrize("store", ["f64", "f32"])
+def test_cg_large_workgroups(rows, store):
+    """The passes over the vectors at the last row count of the small workgroups, the first of the large ones, and one
+    that takes every large workgroup around a second time; checked as above."""
+    test_cg_launch_rules(0, rows, store)
