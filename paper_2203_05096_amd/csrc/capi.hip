@@ -709,7 +709,7 @@ csrk_status csrk_upload(csrk_handle h, csrk_dtype store) {
                 if (e == hipSuccess && !h->values_symmetric)
                     e = csrk::dev::transpose_values(arrays_of(h), store, h->d_vals, h->d_vals_t, nullptr);
                 if (e == hipSuccess && h->d_u_vals)
-                    e = csrk::dev::gather_values(h->d_u_src, h->nu, store, h->d_vals, h->d_u_vals, nullptr);
+                    e = csrk::dev::union_values(h->d_u_src, h->nu, store, h->d_vals, h->d_u_vals, nullptr);
                 hipError_t e2 = hipDeviceSynchronize();
                 (void)hipFree(tmp);
                 hip_check(e, "value conversion");

@@ -74,6 +74,40 @@ struct Store<uint16_t> {
     __device__ static float widen(uint16_t v) { return bf16_to_f32(v); }
 };
 
+// What a union entry (i, j) carries where A' has no (j, i): a NaN that `mirrored`
+// leaves on no stored value, so that a walk leaves such an entry out of grad_x
+// and still multiplies a stored zero (NaN against an infinite or NaN g_j).  The
+// same bits in FP32 and in BF16 once widened; in FP64 the high word decides.
+// Left out where the entry is used, its g_j gathered all the same.  Against zeros
+// in their place (one MI355X, us): adjoint, 2D 9-point 1201x999 with 10% dropped,
+// FP32, 32.8 -> 33.0; 16 3D 7-point matrices of sides 16 to 72 with 10% dropped,
+// 8 FP32 columns, 114.7 -> 116.2.
+constexpr uint32_t kNoMirror = 0x7fff0000u;
+
+template <typename VT>
+__device__ __forceinline__ VT no_mirror() {
+    if constexpr (sizeof(VT) == 8)
+        return __longlong_as_double((long long)(uint64_t(kNoMirror) << 32));
+    else if constexpr (sizeof(VT) == 4)
+        return __uint_as_float(kNoMirror);
+    else
+        return VT(kNoMirror >> 16);
+}
+
+// Whether v, a union entry's value widened, is a stored one.
+__device__ __forceinline__ bool has_mirror(double v) { return uint32_t(__double2hiint(v)) != kNoMirror; }
+__device__ __forceinline__ bool has_mirror(float v) { return __float_as_uint(v) != kNoMirror; }
+
+// A stored value as union entries carry it: a NaN of no_mirror's bits becomes another one.
+template <typename VT>
+__device__ __forceinline__ VT mirrored(VT v) {
+    if (has_mirror(Store<VT>::widen(v))) return v;
+    if constexpr (sizeof(VT) == 2)
+        return VT(0x7fc0);
+    else
+        return __builtin_nanf("");
+}
+
 // Super-super-row of block b under the work-balanced XCD ranges, or -1 for a
 // padding block.  b counts from the first SSR block, which the long-row blocks
 // in front of it (a multiple of 8 of them) leave on XCD 0.
@@ -172,16 +206,26 @@ __device__ __forceinline__ void stage_products(A *__restrict__ buf, const A (&p)
     }
 }
 
+// The value at position `at` of the caller's array; UNI: as union entries carry
+// it, where `at` is negative for an entry without a mirror.
+template <typename VT, bool UNI>
+__device__ __forceinline__ VT value_at(const VT *__restrict__ vals, int32_t at) {
+    if constexpr (UNI)
+        return at >= 0 ? mirrored(vals[at]) : no_mirror<VT>();
+    else
+        return vals[at];
+}
+
 // V consecutive column indices starting at pos (pos % V == 0) and the values
 // of those entries: vals[pos + e], or vals[src[pos + e]] when the values are
-// reached through an index map (IND; a negative map entry reads as 0).
-// Entries at or beyond nnz read as 0.
+// reached through an index map (IND; UNI: the union's, whose negative entries
+// read as no_mirror).  Entries at or beyond nnz read as 0.
 // The value stream is read with non-temporal loads: each value is used once
 // per product, and keeping it out of the caches leaves the Infinity Cache to
 // col_idx, row_ptr and the vectors, which the forward and the adjoint of a
 // step share (measured: the forward + adjoint step on a 128^3 7-point matrix
 // runs about 4% faster; loading col_idx the same way made it slower).
-template <typename VT, bool IND>
+template <typename VT, bool IND, bool UNI = false>
 __device__ __forceinline__ void load_vec(const VT *__restrict__ vals, const int32_t *__restrict__ cols,
                                          const int32_t *__restrict__ src, int64_t pos, int64_t nnz,
                                          typename Store<VT>::A (&v)[Store<VT>::V], int32_t (&c)[Store<VT>::V]) {
@@ -194,7 +238,7 @@ __device__ __forceinline__ void load_vec(const VT *__restrict__ vals, const int3
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 c[e] = cv[e];
-                v[e] = sv[e] >= 0 ? Store<VT>::widen(vals[sv[e]]) : typename Store<VT>::A(0);
+                v[e] = Store<VT>::widen(value_at<VT, UNI>(vals, sv[e]));
             }
         } else {
             typedef VT VV __attribute__((ext_vector_type(V)));
@@ -210,8 +254,10 @@ __device__ __forceinline__ void load_vec(const VT *__restrict__ vals, const int3
         for (int e = 0; e < V; ++e) {
             const bool ok = pos + e < nnz;
             c[e] = ok ? cols[pos + e] : 0;
-            const int64_t at = ok ? (IND ? int64_t(src[pos + e]) : pos + e) : -1;
-            v[e] = at >= 0 ? Store<VT>::widen(vals[at]) : typename Store<VT>::A(0);
+            if constexpr (IND)
+                v[e] = ok ? Store<VT>::widen(value_at<VT, UNI>(vals, src[pos + e])) : typename Store<VT>::A(0);
+            else
+                v[e] = ok ? Store<VT>::widen(vals[pos + e]) : typename Store<VT>::A(0);
         }
     }
 }
@@ -1538,9 +1584,9 @@ __device__ __forceinline__ void sr_adjoint_fused_rec(const SrRec &rec, const int
 // Both gradients of one super-row of a nonsymmetric pattern in one pass over
 // its union-pattern range (Arrays::u_col): the super-row's A' entries (at a
 // fixed offset `e` from their A' positions), then its rows' extras.  Each U
-// entry (i, j) carries a'_ji (0 where A' has no (j, i)), so row i of U times g
-// is grad_x[i]: it is summed over two segments, the row's A' part and its
-// extras.  grad_vals[k] = g_i x_j is written for the A' part only, at U
+// entry (i, j) carries a'_ji (no_mirror where A' has no (j, i)), so row i of U
+// times g is grad_x[i]: it is summed over two segments, the row's A' part and
+// its extras.  grad_vals[k] = g_i x_j is written for the A' part only, at U
 // position k + e.  `ra` is the super-row's record in A' (entries [e0, e1)),
 // `ru` its record in U; the host builds U only when every super-row has at
 // most 64 rows and fits one window (U entries <= kStageEntries - 8), which
@@ -1585,7 +1631,7 @@ __device__ __forceinline__ void sr_adjoint_union_rec(const SrRec &ra, const SrRe
     for (int u = 0; u < U; ++u) {
         const int64_t pos = base + int64_t(u) * kWave * V;
         if (pos < ce) {
-            load_vec<VT, IND>(vals, ucols, usrc, pos, nu, v[u], c[u]);
+            load_vec<VT, IND, true>(vals, ucols, usrc, pos, nu, v[u], c[u]);
         } else {
 #pragma unroll
             for (int q = 0; q < V; ++q) {
@@ -1627,7 +1673,7 @@ __device__ __forceinline__ void sr_adjoint_union_rec(const SrRec &ra, const SrRe
         for (int q = 0; q < V; ++q) {
             const int64_t k = pos + q;
             gvv[q] = (k >= cs && k < ca) ? gwin[rowid[k - cs]] * xs[u][q] : A(0);
-            pr[u][q] = v[u][q] * gs[u][q];
+            pr[u][q] = has_mirror(v[u][q]) ? v[u][q] * gs[u][q] : A(0);
         }
         if (pos >= cs && pos + V <= ca) {
             AV ov;
@@ -1983,7 +2029,7 @@ __device__ __forceinline__ void mrhs_adjoint_union_window(const SrRec &ra, const
     for (int u = 0; u < U; ++u) {
         const int64_t pos = base + int64_t(u) * kWave * V;
         if (pos < ce) {
-            load_vec<VT, IND>(vals, ucols, usrc, pos, nu, v[u], c[u]);
+            load_vec<VT, IND, true>(vals, ucols, usrc, pos, nu, v[u], c[u]);
         } else {
 #pragma unroll
             for (int t = 0; t < V; ++t) {
@@ -2040,11 +2086,12 @@ __device__ __forceinline__ void mrhs_adjoint_union_window(const SrRec &ra, const
                 }
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
+                    const bool has = has_mirror(a[t]);
                     A p = 0;
 #pragma unroll
                     for (int z = 0; z < VX; ++z) {
                         p += A(gi[z]) * A(xv[t][z]);
-                        acc[z] += a[t] * A(gj[t][z]);
+                        if (has) acc[z] += a[t] * A(gj[t][z]);
                     }
                     p = group_sum<RL>(p);
                     if (q == 0 && k0 + t < a1) sgv[k0 + t] = cb == 0 ? p : sgv[k0 + t] + p;

@@ -122,8 +122,8 @@ struct Arrays {
     // when every super-row fits one staging window; the single-right-hand-side
     // adjoint then takes both gradients in one pass over it.
     const int32_t *u_col = nullptr;
-    const int32_t *u_src = nullptr;  // position of a'_ji in A', -1 where A' has no (j, i) (value 0)
-    const void *u_vals = nullptr;    // the handle's values a'_ji in U order (0 where u_src is -1)
+    const int32_t *u_src = nullptr;  // position of a'_ji in A', -1 where A' has no (j, i)
+    const void *u_vals = nullptr;    // the handle's values a'_ji in U order (a marker where u_src is -1)
     const int32_t *erow_ptr = nullptr;  // extras of the rows before row i
     const SrRec *srec_u = nullptr;      // per (SSR, slot): rows [r0, r1), U entries [e0, e1)
     int64_t nu = 0;                     // U entries (with padding)
@@ -194,9 +194,9 @@ hipError_t adjoint_win_mrhs(const Arrays &a, csrk_dtype store, const void *vals,
                             void *gv, int nrhs, Shape s, hipStream_t st);
 // vals_t[p] = vals[t_src[p]]: the values in A'^T order.
 hipError_t transpose_values(const Arrays &a, csrk_dtype store, const void *vals, void *vals_t, hipStream_t st);
-// out[p] = vals[idx[p]] (0 where idx[p] < 0) for p < count, storage type `store`.
-hipError_t gather_values(const int32_t *idx, int64_t count, csrk_dtype store, const void *vals, void *out,
-                         hipStream_t st);
+// u_vals[p] = vals[u_src[p]] for p < nu, marked as without a mirror where u_src[p] < 0.
+hipError_t union_values(const int32_t *u_src, int64_t nu, csrk_dtype store, const void *vals, void *u_vals,
+                        hipStream_t st);
 // Fills a window layout from `count` super-row records: each slot's WinRec, its
 // entries' 16-bit column offsets and its rows' 16-bit ends (rp[r + 1] - rp[r0]).
 // *wide (one int32, cleared by the caller) becomes nonzero when some super-row's

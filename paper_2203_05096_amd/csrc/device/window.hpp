@@ -63,10 +63,10 @@ struct WinStream {
 // groups of V from the 16-byte boundary at or below e0.  `cols` is padded to a
 // whole group; the values are the caller's or the handle's nnz elements, so
 // the last group of the array is read one by one.  IND: value k is
-// vals[src[k]] (0 where src[k] < 0), src holding nnz elements too.  K: the
+// value_at(src[k]), src holding nnz elements too (UNI: the union's).  K: the
 // values are read through the caches (win_keep), otherwise past them; a constant,
 // since the compiler merges the two loads of a branch into one plain load.
-template <typename VT, bool IND, bool K>
+template <typename VT, bool IND, bool UNI, bool K>
 __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t nent, const uint16_t *__restrict__ cols,
                                          const int32_t *__restrict__ src, const VT *__restrict__ vals, int64_t nnz,
                                          std::bool_constant<K>, int lane) {
@@ -83,7 +83,7 @@ __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t n
                 if constexpr (IND) {
                     const SV sv = *reinterpret_cast<const SV *>(src + pos);
 #pragma unroll
-                    for (int e = 0; e < V; ++e) w.v[u][e] = sv[e] >= 0 ? vals[sv[e]] : VT(0);
+                    for (int e = 0; e < V; ++e) w.v[u][e] = value_at<VT, UNI>(vals, sv[e]);
                 } else if constexpr (K) {
                     w.v[u] = *reinterpret_cast<const typename W::VV *>(vals + pos);
                 } else {
@@ -92,8 +92,11 @@ __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t n
             } else {
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
-                    const int64_t at = pos + e < nnz ? (IND ? int64_t(src[pos + e]) : pos + e) : -1;
-                    w.v[u][e] = at >= 0 ? vals[at] : VT(0);
+                    const bool ok = pos + e < nnz;
+                    if constexpr (IND)
+                        w.v[u][e] = ok ? value_at<VT, UNI>(vals, src[pos + e]) : VT(0);
+                    else
+                        w.v[u][e] = ok ? vals[pos + e] : VT(0);
                 }
             }
         }
@@ -140,7 +143,7 @@ __device__ __forceinline__ void win_product(const WinRec &rec, const uint16_t *_
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + kStageEntries * sizeof(VT));
     const int nrows = rec.rows(), nent = rec.entries(), off = rec.e0 & (V - 1);
     WinStream<VT> w;
-    win_load<VT, false>(w, rec.e0, nent, cols, nullptr, vals, nnz, keep, lane);
+    win_load<VT, false, false>(w, rec.e0, nent, cols, nullptr, vals, nnz, keep, lane);
     const int my_end = lane < nrows ? int(rend16[rec.r0 + lane]) : 0;
     ready();
     win_stage<VT>(w, rec.e0, nent, sval, scol, lane);
@@ -231,8 +234,9 @@ __device__ __forceinline__ void win_store_gv(const A *__restrict__ sgv, int off,
 // Both gradients of one super-row.  UNI false: symmetric pattern, `ru` == `ra`
 // and values in A'^T order (vals) or the caller's through src (IND).  UNI true:
 // the super-row's union range `ru` holds its A' entries (at a fixed offset, a
-// multiple of 8, from their A' positions) and then its rows' extras, whose ends
-// are xend16; columns, values and src are the union's, `nnz` its entries.
+// multiple of 8, from their A' positions; no_mirror where A'^T has none) and then
+// its rows' extras, whose ends are xend16; columns, values and src are the
+// union's, `nnz` its entries.
 template <typename VT, int LL, bool IND, bool UNI, bool K>
 __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, const uint16_t *__restrict__ rend16,
                                             const uint16_t *__restrict__ xend16, const uint16_t *__restrict__ cols,
@@ -252,7 +256,7 @@ __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, 
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + win_adjoint_lds<VT>() - kStageEntries * sizeof(uint16_t));
     const int nrows = ra.rows(), nent = ra.entries(), off = ru.e0 & (V - 1);
     WinStream<VT> w;
-    win_load<VT, IND>(w, ru.e0, ru.entries(), cols, src, vals, nnz, keep, lane);
+    win_load<VT, IND, UNI>(w, ru.e0, ru.entries(), cols, src, vals, nnz, keep, lane);
     const int my_end = lane < nrows ? int(rend16[ra.r0 + lane]) : 0;
     const int my_xend = UNI && lane < nrows ? int(xend16[ra.r0 + lane]) : 0;
     const A my_g = lane < nrows ? A(g[ra.r0 + lane]) : A(0);
@@ -283,7 +287,8 @@ __device__ __forceinline__ void win_adjoint(const WinRec &ra, const WinRec &ru, 
 #pragma unroll
         for (int j = 0; j < B; ++j)
             if (k + j * LL < ke) {
-                acc += Store<VT>::widen(sval[k + j * LL]) * A(gw[j]);
+                const A a = Store<VT>::widen(sval[k + j * LL]);
+                if (!UNI || has_mirror(a)) acc += a * A(gw[j]);
                 sgv[k + j * LL] = gi * A(xv[j]);
             }
         k += B * LL;

@@ -71,13 +71,13 @@ __device__ __forceinline__ int win_groups(int nrows, int RL) {
 }
 
 // The window's columns (and, with VALS, its values) into LDS.
-template <typename VT, bool IND, bool VALS, bool K>
+template <typename VT, bool IND, bool UNI, bool VALS, bool K>
 __device__ __forceinline__ void win_fetch(int32_t e0, int32_t nent, const uint16_t *__restrict__ cols,
                                           const int32_t *__restrict__ src, const VT *__restrict__ vals, int64_t nnz,
                                           std::bool_constant<K> keep, VT *sval, uint16_t *scol, int lane) {
     if constexpr (VALS) {
         WinStream<VT> w;
-        win_load<VT, IND>(w, e0, nent, cols, src, vals, nnz, keep, lane);
+        win_load<VT, IND, UNI>(w, e0, nent, cols, src, vals, nnz, keep, lane);
         win_stage<VT>(w, e0, nent, sval, scol, lane);
     } else {
         const int32_t ea = e0 & ~(Store<VT>::V - 1);  // LDS index k - ea in both forms
@@ -116,7 +116,7 @@ __device__ __forceinline__ void win_forward_mrhs(const WinRec &rec, const uint16
     uint16_t *scol = reinterpret_cast<uint16_t *>(lds + cap * sizeof(VT));
     const int nrows = rec.rows(), nent = rec.entries(), off = rec.e0 & (Store<VT>::V - 1);
     const int my_end = lane < nrows ? int(rend16[rec.r0 + lane]) : 0;
-    win_fetch<VT, false, true>(rec.e0, nent, cols, nullptr, vals, nnz, keep, sval, scol, lane);
+    win_fetch<VT, false, false, true>(rec.e0, nent, cols, nullptr, vals, nnz, keep, sval, scol, lane);
     wave_lds_sync();
     const int le = win_groups(nrows, RL), E = 1 << le;
     const int q = lane % RL, sub = (lane / RL) & (E - 1), rsub = (lane / RL) >> le, rows_per_pass = (kWave / RL) >> le;
@@ -193,7 +193,7 @@ __device__ __forceinline__ void win_adjoint_mrhs(const WinRec &ra, const WinRec 
     const int nrows = ra.rows(), nent = ra.entries(), off = ru.e0 & (V - 1);
     const int my_end = lane < nrows ? int(rend16[ra.r0 + lane]) : 0;
     const int my_xend = UNI && lane < nrows ? int(xend16[ra.r0 + lane]) : 0;
-    win_fetch<VT, IND, GX>(ru.e0, ru.entries(), cols, src, vals, nnz, keep, sval, scol, lane);
+    win_fetch<VT, IND, UNI, GX>(ru.e0, ru.entries(), cols, src, vals, nnz, keep, sval, scol, lane);
     wave_lds_sync();
     const int le = win_groups(nrows, RL), E = 1 << le;
     const int q = lane % RL, sub = (lane / RL) & (E - 1), rsub = (lane / RL) >> le, rows_per_pass = (kWave / RL) >> le;
@@ -242,8 +242,10 @@ __device__ __forceinline__ void win_adjoint_mrhs(const WinRec &ra, const WinRec 
                     const bool ok = k + j * E < ke;
                     if constexpr (GX) {  // before grad_vals can take the value's place
                         const A v = Store<VT>::widen(sval[ok ? k + j * E : off]), a = ok ? v : A(0);
+                        if (!UNI || has_mirror(a)) {
 #pragma unroll
-                        for (int e = 0; e < VX; ++e) acc[e] += a * A(gw[j].v[e]);
+                            for (int e = 0; e < VX; ++e) acc[e] += a * A(gw[j].v[e]);
+                        }
                     }
                     A p = 0;
 #pragma unroll
