@@ -121,11 +121,27 @@ typedef struct csrk_info {
                                  reads the forward's values instead of a transposed copy */
     csrk_params params;
     int32_t adjoint_union;    /* 1 when uploaded with a nonsymmetric pattern whose union
-                                 pattern (A' + A'^T) fits the staging windows: the
-                                 adjoint (one or several right-hand sides) then takes both
-                                 gradients in one pass over the union instead of a pass
-                                 over A' and one over A'^T */
+                                 pattern (A' + A'^T) fits the staging windows super-row by
+                                 super-row (csrk_copy_union): the adjoint then takes both
+                                 gradients in one pass over that union.  0 says nothing of
+                                 the launches: super-rows that do not fit are cut into
+                                 windows, whose own union the adjoint takes in one pass if
+                                 it fits (csrk_walk.adjoint_passes) */
 } csrk_info;
+
+/* The launches that a handle's calls take (csrk_get_walk). */
+typedef struct csrk_walk {
+    int32_t windows;          /* units of rows that one wavefront takes: the super-rows, or the
+                                 pieces that launches cut them into */
+    int32_t product_window;   /* 1: products go by the window walk (every unit one staging window
+                                 of 16-bit columns), which does not read lanes_per_row */
+    int32_t adjoint_window;   /* 1: so do adjoints with both outputs */
+    int32_t lanes;            /* lanes per row of the window walk with one right-hand side, 0
+                                 without it */
+    int32_t adjoint_passes;   /* both outputs, one right-hand side: 1 = one pass over A' (symmetric
+                                 pattern) or over the union pattern, 2 = A' and then A'^T */
+    int32_t cg_launches;      /* launches of a CG iteration */
+} csrk_walk;
 
 typedef struct csrk_matrix *csrk_handle;
 typedef struct csrk_batch_s *csrk_batch;
@@ -228,6 +244,10 @@ csrk_status csrk_set_launch(csrk_handle h, int32_t lanes_per_row, int32_t waves_
 /* Statistics and parameters of a handle. */
 csrk_status csrk_get_info(csrk_handle h, csrk_info *out);
 
+/* The launches that an uploaded handle's calls take: for tuners and tests.
+ * Errors: CSRK_ERR_ARG (null argument), CSRK_ERR_UNSUPPORTED (host-only handle). */
+csrk_status csrk_get_walk(csrk_handle h, csrk_walk *out);
+
 /*
  * csrk_level_ptr — the pointer array of grouping level `level` (Section 2.2,
  * Fig. 1): level 1 = sr_ptr (rows per super-row), level 2 = ssr_ptr
@@ -244,7 +264,9 @@ csrk_status csrk_level_ptr(csrk_handle h, int32_t level, int32_t *count, int32_t
  * one-pass adjoint (built on the host with the structure; see adjoint_union
  * in csrk_info).  *nu receives the number of union entries, padding included
  * (0 when the pattern is symmetric or some super-row has more than 64 rows or
- * more than 504 union entries: then the adjoint walks A' and A'^T).  Super-row
+ * more than 504 union entries: the adjoint then walks the union of the windows
+ * that launches cut super-rows into, which is not copied here, or, where some
+ * row's own union entries exceed 504, A' and A'^T).  Super-row
  * s owns union entries [sr_begin[s], sr_end[s]): its A' entries in A' order
  * (u_col = their columns), then its rows' extras, the columns j with (j, i) in
  * A' but (i, j) not, row by row by increasing column; each super-row's extras

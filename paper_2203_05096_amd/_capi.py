@@ -47,6 +47,14 @@ class csrk_info(ctypes.Structure):
         return d
 
 
+class csrk_walk(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("windows", "product_window", "adjoint_window", "lanes", "adjoint_passes",
+                                              "cg_launches")]
+
+    def as_dict(self):
+        return {f: int(getattr(self, f)) for f, _ in self._fields_}
+
+
 class CsrkError(RuntimeError):
     def __init__(self, status: int, where: str, detail: str):
         self.status = status
@@ -82,6 +90,7 @@ _SIGS = {
                     ctypes.POINTER(csrk_params), ctypes.POINTER(_h)], ctypes.c_int),
     "csrk_set_launch": ([_h, ctypes.c_int32, ctypes.c_int32], ctypes.c_int),
     "csrk_get_info": ([_h, ctypes.POINTER(csrk_info)], ctypes.c_int),
+    "csrk_get_walk": ([_h, ctypes.POINTER(csrk_walk)], ctypes.c_int),
     "csrk_copy_structure": ([_h, _i32p, _i32p, _i32p, _f64p, _i64p, _i32p, _i32p], ctypes.c_int),
     "csrk_copy_union": ([_h, ctypes.POINTER(ctypes.c_int64), _vp, _vp, _vp, _vp, _vp], ctypes.c_int),
     "csrk_level_ptr": ([_h, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), _vp], ctypes.c_int),
@@ -253,6 +262,12 @@ def csrk_get_info(h: int) -> dict:
     i = csrk_info()
     _check(lib().csrk_get_info(h, ctypes.byref(i)), "csrk_get_info")
     return i.as_dict()
+
+
+def csrk_get_walk(h: int) -> dict:
+    w = csrk_walk()
+    _check(lib().csrk_get_walk(h, ctypes.byref(w)), "csrk_get_walk")
+    return w.as_dict()
 
 
 def csrk_copy_structure(h: int) -> dict:

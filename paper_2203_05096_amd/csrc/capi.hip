@@ -1056,6 +1056,24 @@ unsigned char *scratch_on(int device) {
 
 }  // namespace
 
+csrk_status csrk_get_walk(csrk_handle h, csrk_walk *out) {
+    return guard([&] {
+        if (!out) throw Error{CSRK_ERR_ARG, "null argument"};
+        need_device(h);
+        const csrk::dev::Arrays a = arrays_of(h);
+        csrk_walk w{};
+        w.windows = static_cast<int32_t>(h->win.win_ptr.size()) - 1;
+        w.product_window = a.win.rec ? 1 : 0;
+        w.adjoint_window = a.win.rec && (a.sym || a.win.urec) ? 1 : 0;
+        w.lanes = a.win.rec ? a.win.lanes : 0;
+        const bool one = a.sym || w.adjoint_window || (a.srec_u && !adapt_windows(a, h->params.lanes_per_row));
+        w.adjoint_passes = one ? 1 : 2;
+        w.cg_launches = cg_two_launches(h) ? 2 : 3;
+        *out = w;
+        return CSRK_OK;
+    });
+}
+
 csrk_status csrk_cg(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int32_t max_iter,
                     int32_t check_every, void *stream, int32_t *iters_out, double *rel_resid_out) {
     return guard([&] {

@@ -2236,11 +2236,6 @@ hipError_t by_vx(int vx, F &&f) {
 // Lanes per row for a multi-right-hand-side kernel with VX columns per lane.
 inline int rhs_lanes(int nrhs, int vx) { return pow2_at_least((nrhs + vx - 1) / vx); }
 
-// Whether windows of few rows get more lanes per row (window_row_sums): only
-// for matrices with rows far longer than L lanes per row is meant for, so that
-// regular matrices run the plain reduction.
-inline bool adapt_windows(const Arrays &a, int L) { return a.max_row > 16 * L; }
-
 // Calls f(std::bool_constant<ADAPT>); the adaptive reduction is instantiated
 // for up to 4 lanes per row (wider groups already suit long rows).
 template <int L, typename F>

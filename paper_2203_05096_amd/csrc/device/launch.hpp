@@ -130,6 +130,11 @@ struct Arrays {
     WinArrays win;  // 16-bit form of A' for the window walk
 };
 
+// Whether windows of few rows get more lanes per row (window_row_sums): only
+// for matrices with rows far longer than L lanes per row is meant for, so that
+// regular matrices run the plain reduction.
+inline bool adapt_windows(const Arrays &a, int L) { return a.max_row > 16 * L; }
+
 // Per-matrix record of a batched launch (device-resident table).
 struct MatDesc {
     const int32_t *ssr_ptr;

@@ -1,0 +1,174 @@
+"""Which walk a matrix gets, at the edges of each rule, and the walks that the other tests' matrices no longer reach:
+blocks of right-hand sides over columns too far apart for 16 bits, A' and then A'^T, batches whose matrices differ."""
+
+import numpy as np
+import pytest
+
+from tests.gpu_util import check_forward, params, say, to_dev
+from tests.test_gpu_nonfinite import heavy_band
+from tests.test_gpu_window import CASES, DT, band, symmetrised, wide
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import adjoint as OA  # noqa: E402
+from oracle import precision as OP  # noqa: E402
+from paper_2203_05096_amd import _capi as C  # noqa: E402
+from paper_2203_05096_amd.matrix import CsrkBatch, CsrkMatrix  # noqa: E402
+
+LANES = 2
+
+
+def build(A, srs, store="f64", waves=2):
+    A.vals = OP.stored_values(A.vals, store)
+    return CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store,
+                               params=params(srs, 3, lanes=LANES, waves=waves, reorder="none"))
+
+
+# a row of 33 entries where a window of 40 rows leaves it one lane (32 at most); rows past 504 entries
+GENERAL = {"beyond", "heavy"}
+ROW_LANES = {"lanes16": 16, "one_row": 16, "rows96": 1}  # the most that still walk a window's rows at once
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_walk_of_edge_matrices(name):
+    make, srs = CASES[name]
+    for A in (make(), symmetrised(make())):
+        M = build(A, srs)
+        w = C.csrk_get_walk(M.handle)
+        say("walk", name, A.name, w)
+        if A.name == "sym":
+            longest = int(np.diff(A.row_ptr).max())
+            assert w["product_window"] == (1 if longest <= 32 * max(w["lanes"], 1) else 0)
+            assert w["adjoint_passes"] == 1
+        else:
+            assert w["product_window"] == (name not in GENERAL)
+            # one pass over A' + A'^T, unless a row outgrows a window, or the lanes of the general walk
+            assert w["adjoint_passes"] == (2 if name in GENERAL else 1)
+            if name in ROW_LANES:
+                assert w["lanes"] == ROW_LANES[name]
+        assert w["adjoint_window"] == w["product_window"] and (w["lanes"] > 0) == bool(w["product_window"])
+        M.close()
+
+
+def test_walk_windows():
+    """504 entries stay one window, more are cut; a handle that is not uploaded has no walk."""
+    full = symmetrised(band(640, 0.0))
+    for rows, windows in ((64, 20), (56, 12)):
+        # bands of nine: 64 rows hold 576 entries (cut in two), 56 rows 504 (one window)
+        M = build(full, rows)
+        sr = M.structure()["sr_ptr"]
+        assert np.array_equal(sr, np.minimum(np.arange(len(sr)) * rows, 640))
+        assert C.csrk_get_walk(M.handle)["windows"] == windows
+        M.close()
+    h = C.csrk_build_host(full.row_ptr, full.col_idx, full.vals, params(64, 3))
+    with pytest.raises(C.CsrkError) as e:
+        C.csrk_get_walk(h)
+    C.csrk_destroy(h)
+    assert e.value.name == "CSRK_ERR_UNSUPPORTED"
+
+
+def span(A, srs):
+    """The widest super-row: how far its last column lies from its first."""
+    sr = np.repeat(np.arange(A.n) // srs, np.diff(A.row_ptr))
+    lo, hi = np.full(A.n // srs + 1, A.n), np.zeros(A.n // srs + 1, dtype=np.int64)
+    np.minimum.at(lo, sr, A.col_idx)
+    np.maximum.at(hi, sr, A.col_idx)
+    return int((hi - lo).max())
+
+
+@pytest.mark.parametrize("sym", [False, True])
+def test_walk_column_span(sym):
+    """Columns of a window within 65536 of each other are kept in 16 bits: those of A' for the product, those of
+    A' + A'^T for the adjoint."""
+    seen = set()
+    for gap in (65500, 65519, 65520, 65521, 65535, 65536):
+        A = wide(70001, 16, gap)
+        U = symmetrised(A)
+        A = U if sym else A
+        M = build(A, 16)
+        w = C.csrk_get_walk(M.handle)
+        assert w["windows"] == (A.n + 15) // 16
+        due = span(A, 16) <= 65535, span(U, 16) <= 65535
+        assert (w["product_window"], w["adjoint_window"], w["adjoint_passes"]) == (*due, 1), gap
+        seen.add((due, span(A, 16), span(U, 16)))
+        M.close()
+    assert {d for d, _, _ in seen} >= ({(True, True), (False, False)} | (set() if sym else {(True, False)}))
+    assert sym or {a for _, a, _ in seen} >= {65535, 65536}
+
+
+def close(out, ref, scale, beta, what):
+    assert np.all(np.abs(out.double().cpu().numpy() - ref) <= beta * scale), what
+
+
+def check(Ms, As, nrhs, caller):
+    """Products and both gradients, alone and in one batch, within the bounds of their sums in FP64 or FP32."""
+    store = Ms[0].store
+    rng = np.random.default_rng(nrhs)
+    shape = (lambda A: (A.n,) if nrhs == 1 else (A.n, nrhs))
+    xs, gs = ([rng.uniform(-1, 1, shape(A)).astype(np.float32).astype(np.float64) for A in As] for _ in range(2))
+    xd, gd = [to_dev(x, DT[store]) for x in xs], [to_dev(g, DT[store]) for g in gs]
+    vals = [M.values() if caller else None for M in Ms]
+    B = CsrkBatch(Ms)
+    many = vals if caller else None
+    yb, (bx, bv) = B.spmv(xd, vals=many), B.adjoint(xd, gd, vals=many)
+    for i, (M, A) in enumerate(zip(Ms, As)):
+        y, (gx, gv) = M.spmv(xd[i], vals=vals[i]), M.adjoint(xd[i], gd[i], vals=vals[i])
+        torch.cuda.synchronize()
+        c = np.maximum(np.bincount(A.col_idx, minlength=A.n), 1)
+        c = c if nrhs == 1 else c[:, None]
+        f64 = store == "f64"
+        for o in (y, yb[i]):
+            check_forward(o.double().cpu().numpy(), A, xs[i], np.arange(A.n), store, False, label=A.name)
+        for o in (gx, bx[i]):
+            close(o, OA.grad_x(A.row_ptr, A.col_idx, A.vals, gs[i]),
+                  OA.grad_x(A.row_ptr, A.col_idx, np.abs(A.vals), np.abs(gs[i])),
+                  1e-12 if f64 else OP.gamma(c, 2.0 ** -24), (A.name, "grad_x"))
+        for o in (gv, bv[i]):
+            close(o, OA.grad_vals(A.row_ptr, A.col_idx, xs[i], gs[i]),
+                  OA.grad_vals(A.row_ptr, A.col_idx, np.abs(xs[i]), np.abs(gs[i])),
+                  1e-12 if f64 else OP.gamma(nrhs, 2.0 ** -24), (A.name, "grad_vals"))
+    B.close()
+
+
+@pytest.mark.parametrize("caller", [False, True])
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("nrhs", [1, 2, 5, 8])
+@pytest.mark.parametrize("name", ["wide", "wide sym", "two passes"])
+def test_general_walk(name, nrhs, store, caller):
+    say("general walk", name, nrhs, store, caller)
+    if name == "two passes":
+        A = heavy_band()
+        A.vals = np.random.default_rng(2).uniform(-1, 1, A.nnz)
+        M = build(A, 30, store)
+    else:
+        A = wide(70001, 16, 65536)
+        A = symmetrised(A) if name == "wide sym" else A
+        M = build(A, 16, store)
+    w = C.csrk_get_walk(M.handle)
+    assert w["product_window"] == 0 and w["adjoint_passes"] == (2 if name == "two passes" else 1)
+    check([M, M], [A, A], nrhs, caller)
+    M.close()
+
+
+@pytest.mark.parametrize("caller", [False, True])
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("nrhs", [1, 4, 5])
+@pytest.mark.parametrize("mix", ["lanes", "patterns", "lanes and patterns"])
+def test_batch_of_different_windows(mix, nrhs, store, caller):
+    """One launch over matrices of different lanes per row, and over symmetric and nonsymmetric patterns."""
+    say("batch mix", mix, nrhs, store, caller)
+    if mix == "lanes":
+        As, srs = [symmetrised(band(333, 0.1)) for _ in range(3)], (40, 17, 5)
+    elif mix == "patterns":
+        As, srs = [symmetrised(band(333, 0.1)), band(777, 0.3), symmetrised(band(64, 0.2))], (24, 24, 24)
+    else:
+        As, srs = [band(333, 0.1), symmetrised(band(777, 0.3)), band(65, 0.2), CASES["tiny"][0]()], (4, 9, 30, 64)
+    Ms = [build(A, s, store) for A, s in zip(As, srs)]
+    ws = [C.csrk_get_walk(M.handle) for M in Ms]
+    assert all(w["product_window"] and w["adjoint_window"] for w in ws)
+    assert (len({w["lanes"] for w in ws}) > 1) == ("lanes" in mix)
+    check(Ms, As, nrhs, caller)
+    for M in Ms:
+        M.close()
