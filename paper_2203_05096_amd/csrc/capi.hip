@@ -53,7 +53,7 @@ struct csrk_matrix {
     bool on_device = false;
     csrk_dtype store = CSRK_F64;
     int device = -1;
-    int32_t *d_row_ptr = nullptr, *d_col_idx = nullptr, *d_sr_ptr = nullptr, *d_ssr_ptr = nullptr, *d_perm = nullptr;
+    int32_t *d_row_ptr = nullptr, *d_col_idx = nullptr, *d_perm = nullptr;
     int32_t *d_t_row_ptr = nullptr, *d_t_col = nullptr, *d_t_src = nullptr;  // t_row_ptr/t_col only if nonsymmetric
     void *d_vals = nullptr;
     void *d_vals_t = nullptr;  // stored values in A'^T order, for the adjoint
@@ -156,12 +156,12 @@ void free_device(csrk_matrix *h) {
     if (!h->on_device) return;
     DeviceScope ds(h->device);
     h->cg_mem.free();
-    for (void *p : {(void *)h->d_row_ptr, (void *)h->d_col_idx, (void *)h->d_sr_ptr, (void *)h->d_ssr_ptr,
-                    (void *)h->d_perm, (void *)h->d_t_row_ptr, (void *)h->d_t_col, (void *)h->d_t_src, h->d_vals,
-                    h->d_vals_t == h->d_vals ? nullptr : h->d_vals_t, (void *)h->d_long, (void *)h->d_t_long,
-                    (void *)h->d_srec, (void *)h->d_srec_t, (void *)h->d_u_col, (void *)h->d_u_src,
-                    (void *)h->d_erow_ptr, h->d_u_vals, (void *)h->d_srec_u, (void *)h->d_wrec, (void *)h->d_wcols,
-                    (void *)h->d_wrend, (void *)h->d_wrec_u, (void *)h->d_wucols, (void *)h->d_wxend})
+    for (void *p : {(void *)h->d_row_ptr, (void *)h->d_col_idx, (void *)h->d_perm, (void *)h->d_t_row_ptr,
+                    (void *)h->d_t_col, (void *)h->d_t_src, h->d_vals, h->d_vals_t == h->d_vals ? nullptr : h->d_vals_t,
+                    (void *)h->d_long, (void *)h->d_t_long, (void *)h->d_srec, (void *)h->d_srec_t, (void *)h->d_u_col,
+                    (void *)h->d_u_src, (void *)h->d_erow_ptr, h->d_u_vals, (void *)h->d_srec_u, (void *)h->d_wrec,
+                    (void *)h->d_wcols, (void *)h->d_wrend, (void *)h->d_wrec_u, (void *)h->d_wucols,
+                    (void *)h->d_wxend})
         if (p) (void)hipFree(p);
     h->d_wrec = h->d_wrec_u = nullptr;
     h->d_wcols = h->d_wrend = h->d_wucols = h->d_wxend = nullptr;
@@ -169,7 +169,7 @@ void free_device(csrk_matrix *h) {
     h->d_u_vals = nullptr;
     h->d_srec_u = nullptr;
     h->nu = 0;
-    h->d_row_ptr = h->d_col_idx = h->d_sr_ptr = h->d_ssr_ptr = h->d_perm = nullptr;
+    h->d_row_ptr = h->d_col_idx = h->d_perm = nullptr;
     h->d_t_row_ptr = h->d_t_col = h->d_t_src = nullptr;
     h->d_long = h->d_t_long = nullptr;
     h->d_srec = h->d_srec_t = nullptr;
@@ -336,12 +336,9 @@ csrk::dev::Arrays arrays_of(const csrk_matrix *h) {
     csrk::dev::Arrays a;
     a.n = h->n;
     a.nnz = h->nnz;
-    a.nsr = static_cast<int32_t>(h->sr_ptr.size()) - 1;
-    a.nssr = static_cast<int32_t>(h->win.grp_ptr.size()) - 1;
+    a.ngroups = static_cast<int32_t>(h->win.grp_ptr.size()) - 1;
     a.row_ptr = h->d_row_ptr;
     a.col_idx = h->d_col_idx;
-    a.sr_ptr = h->d_sr_ptr;
-    a.ssr_ptr = h->d_ssr_ptr;
     a.perm = h->d_perm;
     const bool sym = h->trans.symmetric;
     a.t_row_ptr = sym ? h->d_row_ptr : h->d_t_row_ptr;
@@ -634,8 +631,6 @@ csrk_status csrk_upload(csrk_handle h, csrk_dtype store) {
         try {
             h->d_row_ptr = upload_array(h->row_ptr, "row_ptr");
             h->d_col_idx = upload_array(h->col_idx, "col_idx");
-            h->d_sr_ptr = upload_array(h->sr_ptr, "sr_ptr");
-            h->d_ssr_ptr = upload_array(h->ssr_ptr, "ssr_ptr");
             h->d_perm = upload_array(h->perm, "perm");
             h->d_t_src = upload_array(h->trans.t_src, "transposed map");
             if (!h->trans.symmetric) {
@@ -1306,8 +1301,6 @@ csrk::dev::MatDesc *upload_descs(csrk_batch b, int which, const void *const *val
         const csrk_matrix *h = b->handles[i];
         csrk::dev::MatDesc &m = d[i];
         std::memset(&m, 0, sizeof(m));
-        m.ssr_ptr = h->d_ssr_ptr;
-        m.sr_ptr = h->d_sr_ptr;
         m.row_ptr = h->d_row_ptr;
         m.col_idx = h->d_col_idx;
         const csrk::dev::Arrays a = arrays_of(h);
@@ -1322,7 +1315,6 @@ csrk::dev::MatDesc *upload_descs(csrk_batch b, int which, const void *const *val
         m.gv = gv ? gv[i] : nullptr;
         m.nnz = h->nnz;
         m.n = h->n;
-        m.nssr = a.nssr;
         m.sym = h->trans.symmetric ? 1 : 0;
         m.wcols = h->d_wcols;
         m.wrend = h->d_wrend;

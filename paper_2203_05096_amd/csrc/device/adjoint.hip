@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(1024) k_adjoint_csrk_mrhs(
 
 hipError_t adjoint(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
                    void *gv, int nrhs, Shape s, hipStream_t st) {
-    if (a.nssr == 0) return hipSuccess;
+    if (a.ngroups == 0) return hipSuccess;
     if (nrhs == 1 && gx && gv && a.win.rec && (a.sym || a.win.urec))
         return adjoint_win(a, store, vals, x, g, gx, gv, s, st);
     if (nrhs > 1 && gv && a.win.rec && win_block(store, nrhs) && (!gx || a.sym || a.win.urec))

@@ -101,7 +101,7 @@ hipError_t by_adj_win(csrk_dtype store, int lanes, bool ind, bool sym, F &&f) {
 
 hipError_t adjoint_win(const Arrays &a, csrk_dtype store, const void *vals, const void *x, const void *g, void *gx,
                        void *gv, Shape s, hipStream_t st) {
-    if (a.nssr == 0) return hipSuccess;
+    if (a.ngroups == 0) return hipSuccess;
     return by_adj_win(store, a.win.lanes, vals != nullptr, a.sym, [&](auto vt, auto lc, auto ic, auto sc) -> hipError_t {
         using VT = decltype(vt);
         using X = typename Store<VT>::X;

@@ -214,7 +214,7 @@ hipError_t launch_win(const Arrays &a, const void *vals, const void *x, void *y,
 
 hipError_t spmv(const Arrays &a, csrk_dtype store, const void *vals, const void *x, void *y, int nrhs, Shape s,
                 hipStream_t st) {
-    if (a.nssr == 0) return hipSuccess;
+    if (a.ngroups == 0) return hipSuccess;
     const int block = s.waves * kWave;
     if (nrhs > 1 && a.win.rec && win_block(store, nrhs)) return spmv_win_mrhs(a, store, vals, x, y, nrhs, s, st);
     return by_dtype(store, [&](auto vt) -> hipError_t {
@@ -257,7 +257,7 @@ int spmv_grid(const Arrays &a) {
 
 hipError_t spmv_dot(const Arrays &a, csrk_dtype store, const void *vals, const void *x, void *y, const double *pdot,
                     double *part, Shape s, hipStream_t st) {
-    if (a.nssr == 0) return hipSuccess;
+    if (a.ngroups == 0) return hipSuccess;
     const int block = s.waves * kWave;
     return by_dtype(store, [&](auto vt) -> hipError_t {
         using VT = decltype(vt);

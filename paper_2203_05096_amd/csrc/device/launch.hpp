@@ -89,12 +89,9 @@ constexpr int64_t kWinBlockBytes = 65536;
 struct Arrays {
     int32_t n = 0;
     int64_t nnz = 0;
-    int32_t nsr = 0;
-    int32_t nssr = 0;
+    int32_t ngroups = 0;  // groups of windows, one workgroup each (the super-super-rows where none is cut)
     const int32_t *row_ptr = nullptr;
     const int32_t *col_idx = nullptr;
-    const int32_t *sr_ptr = nullptr;
-    const int32_t *ssr_ptr = nullptr;
     const int32_t *perm = nullptr;
     // A'^T: row j lists column j of A' by increasing row (t_col) with each
     // entry's position in A' (t_src).  For a symmetric pattern t_row_ptr and
@@ -113,9 +110,9 @@ struct Arrays {
     XcdSplit split_fwd;  // by the forward's work (rows of A')
     XcdSplit split_adj;  // by the adjoint's work (rows of A' and of A'^T)
     int32_t max_row = 0;  // longest row of A' or of A'^T (nonzeros)
-    const SrRec *srec = nullptr;    // nssr * srec_stride super-row records
+    const SrRec *srec = nullptr;    // ngroups * srec_stride window records
     const SrRec *srec_t = nullptr;  // the same rows of A'^T (entries of t_row_ptr); == srec if symmetric
-    int32_t srec_stride = 0;        // most super-rows in one super-super-row
+    int32_t srec_stride = 0;        // most windows in one group
     // Union pattern of a nonsymmetric A' (host union_index): per super-row its
     // A' entries, then its rows' extras (entries of A'^T missing from A'),
     // each U entry (i, j) carrying a'_ji.  Present (srec_u != nullptr) only
@@ -137,8 +134,6 @@ inline bool adapt_windows(const Arrays &a, int L) { return a.max_row > 16 * L; }
 
 // Per-matrix record of a batched launch (device-resident table).
 struct MatDesc {
-    const int32_t *ssr_ptr;
-    const int32_t *sr_ptr;
     const int32_t *row_ptr;
     const int32_t *col_idx;
     const int32_t *t_row_ptr;
@@ -152,7 +147,7 @@ struct MatDesc {
     void *gv;
     int64_t nnz;
     int32_t n;
-    int32_t nssr;
+    int32_t wlanes;
     int32_t sym;
     int32_t uni;  // the matrix has a union-pattern index (Arrays::u_col ...): the adjoint takes one pass
     const int32_t *u_col;
@@ -164,8 +159,6 @@ struct MatDesc {
     const uint16_t *wrend;
     const uint16_t *wucols;  // their union's, where the pattern is nonsymmetric
     const uint16_t *wxend;
-    int32_t wlanes;
-    int32_t pad;
 };
 
 // Kernel-shape knobs: lanes per row in the reduction, wavefronts per workgroup.
