@@ -971,8 +971,8 @@ void cg_run(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int3
     const double target = rtol * (bnorm > 0 ? bnorm : 1.0);
     double rr = host_s[0];
     int32_t it = 0;
-    bool done = std::sqrt(rr) <= target;
-    while (!done && it < max_iter) {
+    bool done = std::sqrt(rr) <= target, broke = false;
+    while (!done && !broke && it < max_iter) {
         hip_check(csrk::dev::cg_iteration(a, h->store, h->d_vals, iter, it, shp, st), "cg iteration");
         ++it;
         if (it % check_every == 0 || it == max_iter) {
@@ -983,17 +983,19 @@ void cg_run(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int3
             hip_check(hipStreamSynchronize(st), "cg sync");
             if (report) std::copy(report, report + 2, host_s);
             rr = host_s[0];
-            if (!(host_s[1] > 0) || !std::isfinite(rr))
-                throw Error{CSRK_ERR_UNSUPPORTED,
-                            "CG breakdown (p'Ap <= 0 or a non-finite residual): the matrix is not symmetric "
-                            "positive definite in the stored precision"};
+            broke = !(host_s[1] > 0) || !std::isfinite(rr);
             done = std::sqrt(rr) <= target;
         }
     }
+    // x holds every iteration's update when the call returns, after a breakdown too
     if (w.two && it > 0) hip_check(csrk::dev::cg_last(iter, it, n, st), "cg x update");
+    hip_check(hipStreamSynchronize(st), "cg sync");
+    if (broke)
+        throw Error{CSRK_ERR_UNSUPPORTED,
+                    "CG breakdown (p'Ap <= 0 or a non-finite residual): the matrix is not symmetric "
+                    "positive definite in the stored precision"};
     if (iters_out) *iters_out = it;
     if (rel_resid_out) *rel_resid_out = std::sqrt(rr) / (bnorm > 0 ? bnorm : 1.0);
-    hip_check(hipStreamSynchronize(st), "cg sync");
 }
 
 // Work memory of one csrk_cg call: taken from the handle, or allocated, and on
