@@ -882,14 +882,30 @@ size_t round256(size_t b) { return (std::max<size_t>(b, 16) + 255) / 256 * 256; 
 // The residual's partial sums, behind the bytes that cg_work_layout counts.
 constexpr size_t kCgPartBytes = size_t(csrk::dev::kCgGrid) * 8;
 
-// Rows up to which a solve takes two launches an iteration, where the matrix has
-// the window layout: beyond, gathering p and r for every entry costs more than a
-// launch.  3D 7-point FP64, us for 50 iterations, two launches / three / the five
-// before: 24x25x26 627 / 751 / 998; 64^3 833 / 967 / 1383; 80^3 1532 / 1402 / 1900;
-// 120^3 3685 / 2972 / 3448.
+// Entries up to which a solve takes two launches an iteration, where the matrix
+// has the window layout: they gather p and r (16 bytes) for every entry, against
+// one value of p (8, or 4 with FP32/BF16 storage) and a launch and passes over r
+// and p more with three.  us an iteration, two launches / three / the five that
+// were there first (one MI355X, 50 iterations, best of three processes):
+//                                   FP64                  FP32
+//   3D 27-point 37^3, 1.3 M entries 13.9 / 16.2 / 20.6    14.8 / 16.7 / 20.1
+//   3D 7-point 64^3, 1.8 M          15.7 / 17.8 / 26.9    16.7 / 17.3 / 25.1
+//   2D 5-point 620^2, 1.9 M         18.6 / 19.5 / 27.1    18.3 / 20.2 / 27.9
+//   3D 19-point 48^3, 2.0 M         18.2 / 17.0 / 25.0    18.7 / 17.8 / 23.7
+//   2D 9-point 512^2, 2.4 M         18.5 / 20.2 / 28.2    18.2 / 18.9 / 27.9
+//   3D 7-point 73^3, 2.7 M          21.3 / 21.8 / 30.8    19.9 / 19.9 / 28.4
+//   3D 27-point 48^3, 2.9 M         19.3 / 19.4 / 26.8    18.1 / 18.3 / 25.2
+//   2D 9-point 620^2, 3.5 M         26.5 / 25.3 / 34.6    21.8 / 21.7 / 31.2
+//   3D 27-point 58^3, 5.1 M         27.9 / 24.8 / 35.5    26.0 / 22.8 / 32.9
+//   3D 27-point 73^3, 10 M          50.0 / 40.0 / 51.1    46.5 / 35.5 / 44.4
+// Rows are bounded too: the second p must not take a matrix that csrk_cg_noalloc's
+// array held past it, and with fewer than 5 entries a row nothing is measured.
+constexpr int32_t kCgTwoEntries = 3 << 20;
 constexpr int32_t kCgTwoRows = 3 << 17;
 
-bool cg_two_launches(const csrk_matrix *h) { return h->n > 0 && h->d_wrec && h->n <= kCgTwoRows; }
+bool cg_two_launches(const csrk_matrix *h) {
+    return h->n > 0 && h->d_wrec && h->nnz <= kCgTwoEntries && h->n <= kCgTwoRows;
+}
 
 // Bytes of CgWork for this handle without the residual's partial sums, and the
 // pointers inside base (which holds kCgPartBytes more).

@@ -64,7 +64,9 @@ __device__ __forceinline__ double wave_total(const double *__restrict__ part, in
     return acc;
 }
 
-template <typename VT, int LL, bool KEEP>
+// The matrix is read through the caches: 3 M entries, the most that come here, and
+// the vectors stay in the Infinity Cache from one iteration to the next.
+template <typename VT, int LL>
 __global__ void __launch_bounds__(1024) k_cg_product(WinArrays win, int32_t stride, const VT *__restrict__ vals,
                                                      const double *__restrict__ r, const double *__restrict__ p_old,
                                                      double *__restrict__ p, double *__restrict__ x,
@@ -101,7 +103,7 @@ __global__ void __launch_bounds__(1024) k_cg_product(WinArrays win, int32_t stri
             const int rr = lane / LL;
             double pi = 0;
             win_product<VT, LL>(
-                rec, win.rend, win.cols, vals, nnz, std::bool_constant<KEEP>{}, lds, lane,
+                rec, win.rend, win.cols, vals, nnz, std::true_type{}, lds, lane,
                 [&]() {
                     const bool own = rr < rec.rows() && lane % LL == 0;
                     const int64_t i = rec.r0 + rr;
@@ -253,18 +255,13 @@ hipError_t product_two(const Arrays &a, csrk_dtype store, const void *vals, cons
         using VT = decltype(vt);
         using X = typename Store<VT>::X;
         return by_win_lanes(a.win.lanes, [&](auto lc) -> hipError_t {
-            auto go = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(spmv_grid(a)), dim3(s.waves * kWave),
-                                   size_t(s.waves) * win_forward_lds<VT>(), st, a.win, a.srec_stride,
-                                   static_cast<const VT *>(vals), static_cast<const double *>(w.r),
-                                   static_cast<const double *>(it == 0 ? w.r : w.p[(it + 1) & 1]), w.p[it & 1], w.x,
-                                   static_cast<X *>(w.q), a.nnz, a.split_fwd, static_cast<const double *>(w.rr_part),
-                                   it == 0 ? w.rr_parts0 : cg_iter_grid(a.n), w.s, it, w.pq_part);
-                return hipGetLastError();
-            };
-            // the matrix is read again in every iteration, and so are five vectors
-            return win_keep<VT>(a, 2, true) ? go(k_cg_product<VT, decltype(lc)::value, true>)
-                                            : go(k_cg_product<VT, decltype(lc)::value, false>);
+            hipLaunchKernelGGL((k_cg_product<VT, decltype(lc)::value>), dim3(spmv_grid(a)), dim3(s.waves * kWave),
+                               size_t(s.waves) * win_forward_lds<VT>(), st, a.win, a.srec_stride,
+                               static_cast<const VT *>(vals), static_cast<const double *>(w.r),
+                               static_cast<const double *>(it == 0 ? w.r : w.p[(it + 1) & 1]), w.p[it & 1], w.x,
+                               static_cast<X *>(w.q), a.nnz, a.split_fwd, static_cast<const double *>(w.rr_part),
+                               it == 0 ? w.rr_parts0 : cg_iter_grid(a.n), w.s, it, w.pq_part);
+            return hipGetLastError();
         });
     });
 }

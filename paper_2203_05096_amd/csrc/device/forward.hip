@@ -205,6 +205,8 @@ hipError_t launch_win(const Arrays &a, const void *vals, const void *x, void *y,
                                static_cast<const X *>(x), static_cast<X *>(y), a.nnz, a.split_fwd, pdot, part);
             return hipGetLastError();
         };
+        // CG's product, past the caches at any size (three launches an iteration, us, past / through: 3D 7-point
+        // 73^3 FP64 21.8 / 21.1, 2D 9-point 620^2 25.3 / 24.8, 3D 27-point 73^3 40.0 / 36.7)
         if (part) return go(k_spmv_win<VT, LL, true, false>);
         return win_keep<VT>(a, 1, false) ? go(k_spmv_win<VT, LL, false, true>) : go(k_spmv_win<VT, LL, false, false>);
     });

@@ -4,6 +4,7 @@ blocks of right-hand sides over columns too far apart for 16 bits, A' and then A
 import numpy as np
 import pytest
 
+from gen import CsrInput
 from tests.gpu_util import check_forward, params, say, to_dev
 from tests.test_gpu_nonfinite import heavy_band
 from tests.test_gpu_window import CASES, DT, band, symmetrised, wide
@@ -14,6 +15,7 @@ torch = pytest.importorskip("torch")
 
 from oracle import adjoint as OA  # noqa: E402
 from oracle import precision as OP  # noqa: E402
+from oracle import spmv as OS  # noqa: E402
 from paper_2203_05096_amd import _capi as C  # noqa: E402
 from paper_2203_05096_amd.matrix import CsrkBatch, CsrkMatrix  # noqa: E402
 
@@ -172,3 +174,36 @@ def test_batch_of_different_windows(mix, nrhs, store, caller):
     check(Ms, As, nrhs, caller)
     for M in Ms:
         M.close()
+
+
+def repeated(n, entries):
+    """A symmetric band of `entries` (odd) a row: -1 off the diagonal, a dominant diagonal."""
+    h = entries // 2
+    cols = np.arange(n)[:, None] + np.arange(-h, h + 1)
+    ok = (cols >= 0) & (cols < n)
+    rp = np.concatenate([[0], np.cumsum(ok.sum(1))]).astype(np.int32)
+    ci = cols[ok].astype(np.int32)
+    vals = np.where(ci == np.repeat(np.arange(n), np.diff(rp)), entries + 1.0, -1.0)
+    return CsrInput("band", n, rp, ci, vals, {})
+
+
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("n,entries,launches", [(100000, 31, 2), (105000, 31, 3), (393216, 5, 2), (393217, 5, 3),
+                                                (393000, 9, 3)])
+def test_cg_launches_by_entries_and_rows(n, entries, launches, store):
+    """Two launches an iteration up to 3 * 2^20 entries and 3 * 2^17 rows: many entries in few rows take three.  The
+    solve is checked by the residual of the stored matrix (exact values): the recurrence drifts from it by rounding
+    alone in FP64 (2x the tolerance), by the FP32 products otherwise (100x)."""
+    say("cg launches", n, entries, store)
+    A = repeated(n, entries)
+    M = CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store)
+    assert C.csrk_get_walk(M.handle)["cg_launches"] == launches
+    perm = M.structure()["perm"]
+    b, rtol = np.random.default_rng(4).uniform(-1, 1, n), 1e-6
+    x, it, rel = M.cg(to_dev(b[perm], torch.float64), rtol=rtol, max_iter=500, check_every=5)
+    assert 0 < it < 500 and rel <= rtol
+    xin = np.empty(n)
+    xin[perm] = x.cpu().numpy()
+    res = np.linalg.norm(b - OS.spmv(A.row_ptr, A.col_idx, A.vals, xin)) / np.linalg.norm(b)
+    assert res <= (2 if store == "f64" else 100) * rtol, res
+    M.close()
