@@ -357,16 +357,22 @@ csrk_status csrk_spmv_host(csrk_handle h, const double *x, double *y, int32_t nt
  * *rel_resid_out (both may be NULL) receive the iteration count and
  * ||r||_2 / ||b||_2.  Works in one device block holding 3 or 4 work vectors
  * and one FP64 partial sum per workgroup of the product (p'Ap is summed by the
- * product's own workgroups); the handle keeps it for its next call, and with it
- * 16 bytes of mapped host memory, until csrk_destroy or csrk_upload (a call that
- * finds it in use by another allocates its own).  Synchronises `stream` before
- * returning.  Errors: CSRK_ERR_ARG (null
+ * product's own workgroups).  A block of at most CSRK_CG_NOALLOC_BYTES, and 16
+ * bytes of mapped host memory, stay with the handle for its next call, until
+ * csrk_cg_release, csrk_destroy or csrk_upload (a call that finds it in use by
+ * another allocates its own); a larger block is freed before the call returns.
+ * Synchronises `stream` before returning.  Errors: CSRK_ERR_ARG (null
  * vectors, rtol <= 0, max_iter < 0, check_every < 1), CSRK_ERR_UNSUPPORTED on
  * a breakdown (p'A p <= 0: the stored matrix is not positive definite),
  * CSRK_ERR_ALLOC, CSRK_ERR_DEVICE.
  */
 csrk_status csrk_cg(csrk_handle h, const double *b_dev, double *x_dev, double rtol, int32_t max_iter,
                     int32_t check_every, void *stream, int32_t *iters_out, double *rel_resid_out);
+
+/* csrk_cg_release — frees the work memory that csrk_cg calls left with the
+ * handle (a call under way keeps its own).  Errors: CSRK_ERR_ARG (null handle),
+ * CSRK_ERR_DEVICE. */
+csrk_status csrk_cg_release(csrk_handle h);
 
 /*
  * csrk_cg_noalloc — csrk_cg for callers that cannot allocate device memory

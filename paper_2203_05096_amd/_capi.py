@@ -79,6 +79,7 @@ _SIGS = {
                  ctypes.POINTER(ctypes.c_double)], ctypes.c_int),
     "csrk_cg_noalloc": ([_h, _vp, _vp, ctypes.c_double, ctypes.c_int32, ctypes.c_int32, _vp,
                          ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_double)], ctypes.c_int),
+    "csrk_cg_release": ([_h], ctypes.c_int),
     "csrk_cg_noalloc_bytes": ([_h, _i64p], ctypes.c_int),
     "csrk_build_host": ([ctypes.c_int32, ctypes.c_int64, _i32p, _i32p, _vp, ctypes.c_int,
                          ctypes.POINTER(csrk_params), ctypes.POINTER(_h)], ctypes.c_int),
@@ -351,6 +352,10 @@ def csrk_cg_noalloc(h: int, b_dev, x_dev, rtol: float, max_iter: int, check_ever
     _check(lib().csrk_cg_noalloc(h, b_dev, x_dev, float(rtol), int(max_iter), int(check_every), stream,
                                  ctypes.byref(it), ctypes.byref(rr)), "csrk_cg_noalloc")
     return it.value, rr.value
+
+
+def csrk_cg_release(h: int):
+    _check(lib().csrk_cg_release(h), "csrk_cg_release")
 
 
 def csrk_cg_noalloc_bytes(h: int) -> int:

@@ -129,6 +129,10 @@ class CsrkMatrix:
         it, rel = C.csrk_cg(self.handle, _ptr(b), _ptr(x), rtol, max_iter, check_every, _stream())
         return x, it, rel
 
+    def cg_release(self):
+        """Frees the work memory that the matrix keeps between cg calls."""
+        C.csrk_cg_release(self.handle)
+
     def spmv_plain(self, x, y=None, vals=None):
         """Same product with the plain CSR kernel (no super-row levels)."""
         nrhs = self._check_vec(x, "x")

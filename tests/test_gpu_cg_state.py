@@ -47,3 +47,46 @@ def test_cg_breakdown_leaves_the_updated_x(n, noalloc):
         x[perm] = xd.cpu().numpy()
         assert np.max(np.abs(x - ref)) <= 1e-12 * np.max(np.abs(ref))
     M.close()
+
+
+def test_cg_memory_a_handle_keeps():
+    """A handle keeps the work vectors of its last solve up to CSRK_CG_NOALLOC_BYTES, gives them back when asked and
+    takes new ones for the next; a larger solve's are freed when the call returns."""
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    page = 2 << 20  # what the allocator rounds a block to
+    for n in (4099, 3000000, 2000000, 300000):  # the first one loads the kernels
+        rp, ci, vals = tridiagonal(n, 4.0, -1.0)
+        M, M2 = (CsrkMatrix.from_csr(rp, ci, vals, store="f64") for _ in range(2))
+        M.cg_release()  # nothing kept yet
+        b = torch.ones(n, dtype=torch.float64, device="cuda")
+        xs = [torch.zeros(n, dtype=torch.float64, device="cuda") for _ in range(3)]
+
+        def solve(x, M=M):
+            return C.csrk_cg(M.handle, b.data_ptr(), x.data_ptr(), 1e-9, 50, 5, stream())
+        need = C.csrk_cg_noalloc_bytes(M.handle)
+        start = free()
+        first = solve(xs[0])
+        held = start - free()
+        again, at_rest = solve(xs[1]), start - free()
+        M.cg_release()
+        # the runtime keeps small blocks that are freed for the next that asks: another handle's solve takes this one
+        other, reused = solve(xs[2], M2), start - free()
+        M2.cg_release()
+        say("cg memory", n, need, held, at_rest, reused)
+        if n > 4099:
+            if need > C.CG_NOALLOC_BYTES:
+                assert held <= page and at_rest <= page
+            else:
+                assert need - page <= held <= need + 2 * page and abs(at_rest - held) <= page
+            assert reused <= held + page
+        assert first == again == other and torch.equal(xs[0], xs[1]) and torch.equal(xs[0], xs[2])
+        xs[2].zero_()
+        assert solve(xs[2]) == first and torch.equal(xs[0], xs[2])  # with new work memory
+        M.close()
+        M2.close()
+    with pytest.raises(C.CsrkError) as e:
+        C.csrk_cg_release(None)
+    assert e.value.name == "CSRK_ERR_ARG"
