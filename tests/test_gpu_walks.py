@@ -207,3 +207,36 @@ def test_cg_launches_by_entries_and_rows(n, entries, launches, store):
     res = np.linalg.norm(b - OS.spmv(A.row_ptr, A.col_idx, A.vals, xin)) / np.linalg.norm(b)
     assert res <= (2 if store == "f64" else 100) * rtol, res
     M.close()
+
+
+@pytest.mark.parametrize("sym", [True, False])
+@pytest.mark.parametrize("store,nrhs,n", [("f32", 130, 110000), ("f64", 8, 600000), ("bf16", 16, 800000),
+                                          ("f32", 5, 1600000)])
+def test_block_launches_past_the_caches(store, nrhs, n, sym):
+    """Blocks whose launches move more than 96 MB read the handle's values past the caches: both directions, exact and
+    overlapping slices, one and several chunks of columns, symmetric patterns and unions."""
+    say("large block", store, nrhs, n, sym)
+    rng = np.random.default_rng(nrhs)
+    cols = np.arange(n)[:, None] + np.arange(-2, 3)
+    keep = (cols >= 0) & (cols < n) & (sym | (rng.random(cols.shape) >= 0.1) | (cols == np.arange(n)[:, None]))
+    rp = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int32)
+    A = CsrInput("large", n, rp, cols[keep].astype(np.int32), np.round(rng.uniform(-1, 1, keep.sum()) * 64) / 64, {})
+    vb, xb = {"f64": (8, 8), "f32": (4, 4), "bf16": (2, 4)}[store]
+    assert A.nnz * (vb + 2) + 2 * n * nrhs * xb > 96 << 20
+    M = CsrkMatrix.from_csr(A.row_ptr, A.col_idx, A.vals, store=store, nrhs=nrhs, params=params(32, 4, reorder="none"))
+    w = C.csrk_get_walk(M.handle)
+    assert w["product_window"] and w["adjoint_window"]
+    x, g = (rng.uniform(-1, 1, (n, nrhs)).astype(np.float32).astype(np.float64) for _ in range(2))
+    xd, gd = to_dev(x, DT[store]), to_dev(g, DT[store])
+    y, (gx, gv) = M.spmv(xd), M.adjoint(xd, gd)
+    _, only = M.adjoint(xd, gd, grad_x=False)
+    torch.cuda.synchronize()
+    check_forward(y.double().cpu().numpy(), A, x, np.arange(n), store, False, label="large block")
+    f64 = store == "f64"
+    c = np.maximum(np.bincount(A.col_idx, minlength=n), 1)[:, None]
+    close(gx, OA.grad_x(A.row_ptr, A.col_idx, A.vals, g), OA.grad_x(A.row_ptr, A.col_idx, np.abs(A.vals), np.abs(g)),
+          1e-12 if f64 else OP.gamma(c, 2.0 ** -24), "grad_x")
+    ref, scale = OA.grad_vals(A.row_ptr, A.col_idx, x, g), OA.grad_vals(A.row_ptr, A.col_idx, np.abs(x), np.abs(g))
+    for o in (gv, only):
+        close(o, ref, scale, 1e-12 if f64 else OP.gamma(nrhs, 2.0 ** -24), "grad_vals")
+    M.close()
