@@ -114,12 +114,20 @@ def time_step(M: CsrkMatrix, x, g, y, gx, gv, reps: int = 20, warmup: int = 5) -
     return a.elapsed_time(b) * 1e3 / reps
 
 
+def reads_lanes(M: CsrkMatrix, nrhs: int, objective: str) -> bool:
+    """Whether the objective's launches depend on lanes_per_row: blocks of right-hand sides and the window walk
+    choose their lanes themselves."""
+    w = C.csrk_get_walk(M.handle)
+    return nrhs == 1 and not (w["product_window"] and (objective == "forward" or w["adjoint_window"]))
+
+
 def sweep(A, store: str = "f64", srs_list=SRS_SWEEP, ssrs_list=SSRS_SWEEP, lanes_list=LANES_SWEEP,
           waves_list=WAVES_SWEEP, reorder: str = "bandk", nrhs: int = 1, reps: int = 40, seed: int = 0,
           name: str | None = None, threads: int = 8, objective: str = "forward", on_trial=None) -> SweepResult:
     """Times every combination on matrix A (an object with row_ptr, col_idx, vals).  objective is
     "forward" (the paper's) or "step" (forward + adjoint); waves_list None ties the waves per
-    workgroup to SSRS.  on_trial(M, x, y, trial), if given, is called after each timing with the
+    workgroup to SSRS.  Launches that do not read the lanes per row are timed once for all of
+    lanes_list (the first then counts as the best).  on_trial(M, x, y, trial), if given, is called after each timing with the
     matrix and the permuted-space input and output of its last timed product (a caller's check
     that every candidate computes the same product)."""
     n, nnz = len(A.row_ptr) - 1, int(A.row_ptr[-1])
@@ -146,10 +154,15 @@ def sweep(A, store: str = "f64", srs_list=SRS_SWEEP, ssrs_list=SSRS_SWEEP, lanes
         for (srs, ssrs), h in (r for i in range(0, len(combos), threads) for r in ex.map(build, combos[i:i + threads])):
             C.csrk_upload(h, store)
             M = CsrkMatrix(h, store)
+            same = not reads_lanes(M, nrhs, objective)
+            timed = {}  # by waves: the one timing of launches that differ in lanes only
             for lanes, waves in itertools.product(lanes_list, [min(ssrs, 16)] if waves_list is None else waves_list):
                 C.csrk_set_launch(M.handle, lanes, waves)
-                us = time_forward(M, x, y, reps) if objective == "forward" else \
-                    time_step(M, x, gvec, y, gx, gv, reps)
+                if same and waves in timed:
+                    us = timed[waves]
+                else:
+                    us = timed[waves] = time_forward(M, x, y, reps) if objective == "forward" else \
+                        time_step(M, x, gvec, y, gx, gv, reps)
                 res.trials.append(Trial(srs, ssrs, lanes, waves, reorder, us))
                 if on_trial is not None:
                     torch.cuda.synchronize()
@@ -238,13 +251,17 @@ def load(path: str) -> list:
     return out
 
 
+_LAUNCH_NOTE = ("Launches that choose their lanes per row themselves (the window walk, blocks of right-hand sides) share one "
+                "timing over all lanes; super-rows of more than 64 rows or 504 entries are cut into windows by the launch.")
+
+
 def markdown(groups: dict, consts: dict, command: str) -> str:
     """A summary table per storage type: best shape, model shape, ratio."""
     a_r, b_r = consts["srs"]
     a_s, b_s = consts["ssrs"]
     lines = [f"Fit (Section 4.1 form, each size regressed on ln r separately, over all sweeps below): "
              f"SRS = {a_r:.2f} - {b_r:.2f} ln r; SSRS = {a_s:.3f} - ({b_s:.4f}) ln r, rounded half up, then "
-             f"snapped to the nearest power of two.", "", "Command:", "", "    " + command, ""]
+             f"snapped to the nearest power of two.", "", _LAUNCH_NOTE, "", "Command:", "", "    " + command, ""]
     for store, results in groups.items():
         lines += [f"### {store}", "",
                   "| matrix | rdensity | best (SRS, SSRS, lanes) | best us | model (SRS, SSRS, lanes) | model us |"
@@ -284,7 +301,7 @@ def grid_markdown(res: SweepResult, picks: dict, command: str) -> str:
     lines = [f"Matrix {res.name}: n = {res.n:,}, nnz = {res.nnz:,}, rdensity {res.rdensity:.3f}.", "",
              "Command:", "", "    " + command, "",
              f"{'Forward' if res.objective == 'forward' else 'Forward + adjoint'} kernel time in us per (SRS, SSRS) "
-             "cell, the best over lanes per row; waves per workgroup = min(SSRS, 16):", "",
+             "cell, the best over lanes per row; waves per workgroup = min(SSRS, 16):", "", _LAUNCH_NOTE, "",
              "| SRS \\ SSRS | " + " | ".join(str(v) for v in ssrs_l) + " |",
              "|---|" + "---|" * len(ssrs_l)]
     for srs in srs_l:

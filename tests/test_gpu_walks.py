@@ -240,3 +240,20 @@ def test_block_launches_past_the_caches(store, nrhs, n, sym):
     for o in (gv, only):
         close(o, ref, scale, 1e-12 if f64 else OP.gamma(nrhs, 2.0 ** -24), "grad_vals")
     M.close()
+
+
+@pytest.mark.parametrize("objective", ["forward", "step"])
+def test_sweep_times_equal_launches_once(objective):
+    """Trials that differ in lanes per row only, where the launch does not read them, are one launch and one timing:
+    window walks and blocks of right-hand sides.  The general walk's lanes are each timed."""
+    from paper_2203_05096_amd import autotune as T
+    general = wide(70001, 16, 65536)
+    for A, nrhs, same in ((band(3000, 0.1), 1, True), (general, 4, True), (general, 1, False)):
+        say("sweep lanes", A.name, nrhs, objective)
+        res = T.sweep(A, "f64", srs_list=(16, 32), ssrs_list=(2,), lanes_list=(1, 2, 4), nrhs=nrhs, reps=20, threads=2,
+                      reorder="none", objective=objective)
+        assert len(res.trials) == 6
+        for srs in (16, 32):
+            times = {t.us for t in res.trials if t.srs == srs}
+            assert len(times) == 1 if same else len(times) > 1
+        assert not same or res.best.lanes == 1
