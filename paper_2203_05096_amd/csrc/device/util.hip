@@ -12,11 +12,11 @@ namespace {
 
 // ------------------------------------------------------------------ utilities
 
-// out[p] = value_at(idx[p]) for p < count.
+// out[p] = in[idx[p]] for p < count, UNI: as union entries carry it.
 template <typename T, bool UNI>
 __global__ void k_gather(const int32_t *__restrict__ idx, const T *__restrict__ in, T *__restrict__ out, int64_t count) {
     for (int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < count; p += int64_t(gridDim.x) * blockDim.x)
-        out[p] = value_at<T, UNI>(in, idx[p]);
+        out[p] = value_of<T, UNI>(fetch_at<T, UNI>(in, idx[p]), idx[p]);
 }
 
 template <bool UNI>

@@ -63,7 +63,7 @@ struct WinStream {
 // groups of V from the 16-byte boundary at or below e0.  `cols` is padded to a
 // whole group; the values are the caller's or the handle's nnz elements, so
 // the last group of the array is read one by one.  IND: value k is
-// value_at(src[k]), src holding nnz elements too (UNI: the union's).  K: the
+// the caller's at src[k], src holding nnz elements too (UNI: the union's).  K: the
 // values are read through the caches (win_keep), otherwise past them; a constant,
 // since the compiler merges the two loads of a branch into one plain load.
 template <typename VT, bool IND, bool UNI, bool K>
@@ -74,6 +74,7 @@ __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t n
     constexpr int V = W::V;
     typedef int32_t SV __attribute__((ext_vector_type(V)));
     const int32_t ea = e0 & ~(V - 1), ce = e0 + nent;
+    SV sv[IND ? W::U : 1];
 #pragma unroll
     for (int u = 0; u < W::U; ++u) {
         const int64_t pos = int64_t(ea) + (u * kWave + lane) * V;
@@ -81,9 +82,9 @@ __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t n
             w.c[u] = *reinterpret_cast<const typename W::CC *>(cols + pos);
             if (pos + V <= nnz) {
                 if constexpr (IND) {
-                    const SV sv = *reinterpret_cast<const SV *>(src + pos);
+                    sv[u] = *reinterpret_cast<const SV *>(src + pos);
 #pragma unroll
-                    for (int e = 0; e < V; ++e) w.v[u][e] = value_at<VT, UNI>(vals, sv[e]);
+                    for (int e = 0; e < V; ++e) w.v[u][e] = fetch_at<VT, UNI>(vals, sv[u][e]);
                 } else if constexpr (K) {
                     w.v[u] = *reinterpret_cast<const typename W::VV *>(vals + pos);
                 } else {
@@ -93,13 +94,22 @@ __device__ __forceinline__ void win_load(WinStream<VT> &w, int32_t e0, int32_t n
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
                     const bool ok = pos + e < nnz;
-                    if constexpr (IND)
-                        w.v[u][e] = ok ? value_at<VT, UNI>(vals, src[pos + e]) : VT(0);
-                    else
+                    if constexpr (IND) {
+                        sv[u][e] = ok ? src[pos + e] : 0;
+                        w.v[u][e] = ok ? fetch_at<VT, UNI>(vals, sv[u][e]) : VT(0);
+                    } else {
                         w.v[u][e] = ok ? vals[pos + e] : VT(0);
+                    }
                 }
             }
         }
+    }
+    if constexpr (IND && UNI) {
+#pragma unroll
+        for (int u = 0; u < W::U; ++u)
+            if (int64_t(ea) + (u * kWave + lane) * V < ce)
+#pragma unroll
+                for (int e = 0; e < V; ++e) w.v[u][e] = value_of<VT, UNI>(w.v[u][e], sv[u][e]);
     }
 }
 
