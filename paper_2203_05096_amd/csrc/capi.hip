@@ -194,8 +194,26 @@ T *upload_array(const std::vector<T> &v, const char *what) {
 // Rows of more entries than this stand alone in a window of a cut super-row:
 // its other rows would wait for the lanes that sum it.
 constexpr int32_t kHeavyRow = 256;
+// Union entries, in entries of A', up to which super-rows are cut into windows that
+// hold them as well, so that the adjoint takes one pass over the union.  Beyond, A'
+// alone fills the windows, and the adjoint takes a union that fits them all the same
+// or two passes.  Windows for the union / for A', us, adjoint, adjoint with the
+// caller's values:
+//   3D 27-point 47x45x41, 10% dropped, FP32  11.7 / 14.7  17.4 / 17.4
+//   3D 19-point 40x57x43, 10% dropped, FP32   9.4 / 11.1  13.3 / 13.6
+//   3D 27-point 47x45x41, 30% dropped, FP32  10.5 / 11.8  15.6 / 14.4
+//   3D 19-point 40x57x43, 30% dropped, FP32   9.2 / 8.6   12.2 / 11.0   FP64 13.2 / 11.7  17.9 / 14.8
+//   2D 9-point 501x403, 30% dropped, FP64    13.4 / 12.6  16.7 / 14.2
+//   100,000 rows, upper band of 31, FP64     25.9 / 19.7  32.0 / 23.4   product 10.7 / 8.6
+//   50,000 rows of 40, no mirrors, FP64      24.7 / 20.5  37.3 / 25.4   product 12.3 / 8.7
+constexpr double kUnionCut = 1.2;
+
 // Wavefronts per workgroup, at least, for a matrix with long rows: one
-// workgroup computes each, and the longest is what the launch waits for.
+// workgroup computes each, and the longest is what the launch waits for.  The
+// launch's groups then hold at least as many windows, cut or not: a group of two
+// super-rows leaves six of eight wavefronts idle and their LDS taken (300,000 rows
+// of 7 columns near the diagonal and two dense ones, FP32, us, groups of two / of
+// eight: product 9.6 / 8.1, grad_x alone 12.6 / 8.9, grad_vals alone 11.7 / 8.1).
 constexpr int32_t kLongRowWaves = 8;
 
 bool has_long_rows(const csrk_matrix *h) { return h->max_row_any > csrk::dev::kLongRow; }
@@ -251,9 +269,15 @@ void launch_shape(csrk_matrix *h) {
         h->win.win_ptr = h->sr_ptr;  // every super-row is a window as it is
         h->win.grp_ptr = h->ssr_ptr;
     } else {
-        h->win = csrk::launch_windows(h->sr_ptr, h->ssr_ptr,
-                                      csrk::union_lengths(h->n, h->row_ptr, h->col_idx, h->trans), kWinRows,
-                                      kWinEntries, kHeavyRow, std::max(h->params.ssrs, waves));
+        std::vector<int32_t> len(size_t(h->n));
+        for (int32_t i = 0; i < h->n; ++i) len[size_t(i)] = h->row_ptr[size_t(i) + 1] - h->row_ptr[size_t(i)];
+        if (!h->trans.symmetric) {
+            std::vector<int32_t> both = csrk::union_lengths(h->n, h->row_ptr, h->col_idx, h->trans);
+            const int64_t total = std::accumulate(both.begin(), both.end(), int64_t(0));
+            if (h->uni.ok || double(total) <= kUnionCut * double(h->nnz)) len = std::move(both);
+        }
+        h->win = csrk::launch_windows(h->sr_ptr, h->ssr_ptr, len, kWinRows, kWinEntries, kHeavyRow,
+                                      std::max(h->params.ssrs, waves), has_long_rows(h));
         if (!h->uni.ok)
             h->win_uni =
                 csrk::union_index(h->n, h->row_ptr, h->col_idx, h->win.win_ptr, h->trans, kUnionRows, kUnionWindow);
@@ -267,7 +291,7 @@ void launch_shape(csrk_matrix *h) {
         h->max_win_nnz = std::max(h->max_win_nnz, h->row_ptr[size_t(r1)] - h->row_ptr[size_t(r0)]);
     }
     h->win_lanes = window_lanes(h);
-    h->interleave = h->win_lanes == 0 && h->win.grp_ptr != h->ssr_ptr && columns_spread(h);
+    h->interleave = h->win_lanes == 0 && h->win.cut && columns_spread(h);
 }
 
 // Where group t's records stand in the tables: in order, or (interleave) so

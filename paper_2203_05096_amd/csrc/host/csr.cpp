@@ -201,10 +201,9 @@ std::vector<int32_t> union_lengths(int32_t n, const std::vector<int32_t> &row_pt
 
 Windows launch_windows(const std::vector<int32_t> &sr_ptr, const std::vector<int32_t> &ssr_ptr,
                        const std::vector<int32_t> &len, int32_t max_rows, int32_t max_entries, int32_t heavy,
-                       int32_t group) {
+                       int32_t group, bool regroup) {
     Windows w;
     w.win_ptr.push_back(0);
-    bool cut = false;
     for (size_t s = 0; s + 1 < sr_ptr.size(); ++s) {
         const int32_t r0 = sr_ptr[s], r1 = sr_ptr[s + 1];
         int64_t total = 0;
@@ -213,7 +212,7 @@ Windows launch_windows(const std::vector<int32_t> &sr_ptr, const std::vector<int
             w.win_ptr.push_back(r1);
             continue;
         }
-        cut = true;
+        w.cut = true;
         const int32_t pieces = (r1 - r0 + max_rows - 1) / max_rows, rows = (r1 - r0 + pieces - 1) / pieces;
         int64_t sum = 0;
         bool alone = false;  // the open window holds a heavy row
@@ -228,7 +227,7 @@ Windows launch_windows(const std::vector<int32_t> &sr_ptr, const std::vector<int
         }
         w.win_ptr.push_back(r1);
     }
-    if (!cut) {
+    if (!w.cut && !regroup) {
         w.grp_ptr = ssr_ptr;
         return w;
     }

@@ -203,15 +203,16 @@ void check_params(const csrk_params &p);
 // about equal rows, in which a row of more than `heavy` entries stands alone
 // (also one of more than max_entries); the windows are then grouped `group` at a
 // time in order (grp_ptr), whatever super-super-row they come from, so that no
-// workgroup gets more of them than another.  len[i]: entries that row i counts
-// for.
+// workgroup gets more of them than another; with `regroup` also where none is
+// cut.  len[i]: entries that row i counts for.
 struct Windows {
     std::vector<int32_t> win_ptr;  // rows before window w
     std::vector<int32_t> grp_ptr;  // windows before group t
+    bool cut = false;              // some super-row is cut
 };
 Windows launch_windows(const std::vector<int32_t> &sr_ptr, const std::vector<int32_t> &ssr_ptr,
                        const std::vector<int32_t> &len, int32_t max_rows, int32_t max_entries, int32_t heavy,
-                       int32_t group);
+                       int32_t group, bool regroup);
 
 // Entries per row of the union pattern A' + A'^T (A's own for a symmetric one).
 std::vector<int32_t> union_lengths(int32_t n, const std::vector<int32_t> &row_ptr, const std::vector<int32_t> &col_idx,

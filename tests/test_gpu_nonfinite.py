@@ -33,7 +33,7 @@ def heavy_band():
 
 CASES = {
     "union": (lambda: band(407, 0.2), 24),  # super-rows that fit their window
-    "cut": (lambda: band(407, 0.2), 200),  # cut into windows that do
+    "cut": (lambda: band(407, 0.1), 200),  # cut into windows that do
     "wide": (lambda: wide(70001, 16, 65536), 16),  # columns too far apart for 16 bits
     "two passes": (heavy_band, 30),
     "symmetric": (lambda: symmetrised(band(407, 0.2)), 24),

@@ -28,30 +28,69 @@ def build(A, srs, store="f64", waves=2):
                                params=params(srs, 3, lanes=LANES, waves=waves, reorder="none"))
 
 
-# a row of 33 entries where a window of 40 rows leaves it one lane (32 at most); rows past 504 entries
-GENERAL = {"beyond", "heavy"}
-ROW_LANES = {"lanes16": 16, "one_row": 16, "rows96": 1}  # the most that still walk a window's rows at once
+def union_lengths(A):
+    """Entries per row of A + A^T."""
+    import scipy.sparse as sp
+    P = sp.csr_matrix((np.ones(A.nnz), A.col_idx, A.row_ptr), shape=(A.n, A.n))
+    return np.diff((P + P.T).tocsr().indptr)
 
 
-@pytest.mark.parametrize("name", list(CASES))
+def cut(sr, length):
+    """The launch's windows: super-rows of at most 64 rows and 504 entries, others cut into about equal rows within
+    both, a row of more than 256 entries alone."""
+    out = [0]
+    for r0, r1 in zip(sr[:-1], sr[1:]):
+        if r1 - r0 <= 64 and length[r0:r1].sum() <= 504:
+            out.append(r1)
+            continue
+        pieces = -(-(r1 - r0) // 64)
+        rows, total, alone = -(-(r1 - r0) // pieces), 0, False
+        for i in range(r0, r1):
+            if i > out[-1] and (alone or length[i] > 256 or i - out[-1] == rows or total + length[i] > 504):
+                out.append(i)
+                total = 0
+            total += length[i]
+            alone = length[i] > 256
+        out.append(r1)
+    return np.array(out)
+
+
+def due(A, M):
+    """The walk that the rules give the matrix (rows in their own order, columns within 16 bits)."""
+    sr = M.structure()["sr_ptr"].astype(np.int64)
+    own, both = np.diff(A.row_ptr), union_lengths(A)
+    sym = both.sum() == own.sum()
+    sums = (lambda ptr, length: np.add.reduceat(np.append(length, 0), ptr[:-1]) * (np.diff(ptr) > 0))
+    fits = (lambda ptr: np.diff(ptr).max() <= 64 and sums(ptr, both).max() <= 504)
+    win = cut(sr, both if fits(sr) or both.sum() <= 1.2 * own.sum() else own)
+    longest = max(own.max(), np.bincount(A.col_idx, minlength=A.n).max())
+    lanes = 1
+    while lanes < 16 and np.diff(win).max() * lanes * 2 <= 64:
+        lanes *= 2
+    window = sums(win, own).max() <= 504 and longest <= 32 * lanes
+    union = fits(win)
+    one = sym or (union and (window or longest <= 16 * LANES))
+    return {"windows": len(win) - 1, "product_window": int(window), "adjoint_window": int(window and (sym or union)),
+            "lanes": lanes if window else 0, "adjoint_passes": 1 if one else 2}
+
+
+@pytest.mark.parametrize("name", list(CASES) + ["band"])
 def test_walk_of_edge_matrices(name):
-    make, srs = CASES[name]
-    for A in (make(), symmetrised(make())):
-        M = build(A, srs)
-        w = C.csrk_get_walk(M.handle)
-        say("walk", name, A.name, w)
-        if A.name == "sym":
-            longest = int(np.diff(A.row_ptr).max())
-            assert w["product_window"] == (1 if longest <= 32 * max(w["lanes"], 1) else 0)
-            assert w["adjoint_passes"] == 1
-        else:
-            assert w["product_window"] == (name not in GENERAL)
-            # one pass over A' + A'^T, unless a row outgrows a window, or the lanes of the general walk
-            assert w["adjoint_passes"] == (2 if name in GENERAL else 1)
-            if name in ROW_LANES:
-                assert w["lanes"] == ROW_LANES[name]
-        assert w["adjoint_window"] == w["product_window"] and (w["lanes"] > 0) == bool(w["product_window"])
-        M.close()
+    """Every field against the rules written out, for the edge matrices and bands with more and more dropped."""
+    seen = []
+    makes = [CASES[name]] if name in CASES else \
+        [(lambda d=d: band(1203, d), srs) for d in (0.02, 0.1, 0.3, 0.5, 0.9) for srs in (40, 50, 200)]
+    for make, srs in makes:
+        for A in (make(), symmetrised(make())):
+            M = build(A, srs)
+            w = C.csrk_get_walk(M.handle)
+            say("walk", name, A.name, w)
+            want = due(A, M)
+            assert {k: w[k] for k in want} == want
+            seen.append((w["product_window"], w["adjoint_passes"]))
+            M.close()
+    assert name not in ("beyond", "heavy") or (0, 2) in seen
+    assert name not in ("one_row", "lanes16") or seen[0][0] == 1
 
 
 def test_walk_windows():
@@ -150,6 +189,29 @@ def test_general_walk(name, nrhs, store, caller):
         M = build(A, 16, store)
     w = C.csrk_get_walk(M.handle)
     assert w["product_window"] == 0 and w["adjoint_passes"] == (2 if name == "two passes" else 1)
+    check([M, M], [A, A], nrhs, caller)
+    M.close()
+
+
+@pytest.mark.parametrize("caller", [False, True])
+@pytest.mark.parametrize("store", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("nrhs", [1, 3, 8])
+@pytest.mark.parametrize("name", ["extras", "extras of long rows", "cut"])
+def test_union_windows(name, nrhs, store, caller):
+    """The window walk over unions: patterns without a mirror, whose rows have as many extras as entries (around one
+    and several batches of them), and super-rows cut into windows for their union."""
+    say("union windows", name, nrhs, store, caller)
+    if name == "cut":
+        A, srs = band(1203, 0.1), 200
+    else:
+        lengths, srs = ([1, 2, 3, 4, 5, 9, 10, 11, 13] * 50, 16) if name == "extras" else ([60, 17, 33, 64, 40, 1] * 50, 3)
+        rows = [np.arange(i, min(i + m, len(lengths))) for i, m in enumerate(lengths)]  # an upper triangle
+        rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+        A = CsrInput(name, len(rows), rp, np.concatenate(rows).astype(np.int32), np.zeros(rp[-1]), {})
+        A.vals = np.random.default_rng(6).uniform(-1, 1, A.nnz)
+    M = build(A, srs, store)
+    w = C.csrk_get_walk(M.handle)
+    assert w["adjoint_window"] == 1 and M.info["adjoint_union"] == (name != "cut")
     check([M, M], [A, A], nrhs, caller)
     M.close()
 
