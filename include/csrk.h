@@ -265,8 +265,8 @@ csrk_status csrk_level_ptr(csrk_handle h, int32_t level, int32_t *count, int32_t
  * in csrk_info).  *nu receives the number of union entries, padding included
  * (0 when the pattern is symmetric or some super-row has more than 64 rows or
  * more than 504 union entries: the adjoint then walks the union of the windows
- * that launches cut super-rows into, which is not copied here, or, where some
- * row's own union entries exceed 504, A' and A'^T).  Super-row
+ * that launches cut super-rows into, which is not copied here, where it fits
+ * them, otherwise A' and A'^T; csrk_get_walk says which).  Super-row
  * s owns union entries [sr_begin[s], sr_end[s]): its A' entries in A' order
  * (u_col = their columns), then its rows' extras, the columns j with (j, i) in
  * A' but (i, j) not, row by row by increasing column; each super-row's extras

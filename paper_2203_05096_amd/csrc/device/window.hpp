@@ -206,12 +206,12 @@ __device__ __forceinline__ void win_forward(const WinRec &rec, const uint16_t *_
 // gather x_j and g_j of its entries, add a_ji g_j to grad_x[i] in registers
 // and leave grad_vals = g_i x_j in LDS (over the value just used where the two
 // have one size), from where they go out as 16-byte stores; stored straight by
-// the row lanes they cost 58 instead of 39 us on the 3D 7-point matrix below.
+// the row lanes they cost the 3D 7-point matrix below half as much time again.
 // Bound by HBM: per entry it reads 2 bytes of columns and a value and writes a
-// grad_vals, near the rate of a plain copy (entry-order gathers, 32-bit
-// columns and a map from entries to rows in LDS before; us before -> after):
-// 3D 7-point 101x97x113 FP64 47.6 -> 38.9, 27-point 75x80x77 FP32 47.3 -> 31.5,
-// BF16 48.0 -> 30.4, FP64 64.3 -> 51.9.
+// grad_vals, near the rate of a plain copy (entry-order gathers, 32-bit columns and
+// a map from entries to rows in LDS before; three matrices in turn, us before ->
+// after): 3D 7-point 101x97x113 FP64 41.0 -> 34.3, 27-point 75x80x77 FP32 43.5 ->
+// 31.7, BF16 43.2 -> 29.5, FP64 57.0 -> 46.9.
 
 // LDS bytes per wavefront: values (overwritten by grad_vals of the same size),
 // grad_vals where values are smaller, and column offsets.
@@ -378,6 +378,9 @@ hipError_t by_batch_win(csrk_dtype store, int lanes, F &&f) {
 // 7-point 80^3 FP64 adjoint 18.8 / 15.2; 73 MB, 3D 19-point 61x64x67, 8 FP32
 // columns, forward and adjoint 44.8 / 40.4; 117 MB, 2D 9-point 1201x999 FP32
 // adjoint 33.0 / 36.3; 184 MB, 3D 7-point 128^3 FP64 forward 29.2 / 36.5.
+// Batched launches read past them at any size: 16 3D 7-point matrices, 8 FP32
+// columns, 83 MB, forward 29.7 / 28.7, 118 MB, adjoint 56.2 / 54.8; one column, 205
+// MB, FP64 forward 30.6 / 36.7, 330 MB, adjoint 60.7 / 64.7; the same below 80 MB.
 constexpr int64_t kWinKeepBytes = 96 << 20;
 template <typename VT>
 bool win_keep(const Arrays &a, int nrhs, bool adjoint) {

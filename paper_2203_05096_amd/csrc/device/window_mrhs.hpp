@@ -10,13 +10,13 @@
 // (equal results, written twice; counted once in grad_vals).  gfx950 loads and
 // stores 16 bytes from any 4-byte boundary.
 //
-// What bounds it: the latency of its chain of loads (record, stream, batches of
-// gathers) at the wavefronts that its registers leave resident.  One MI355X,
-// three matrices used in turn, us, forward / adjoint, general walk -> window
-// walk: 3D 7-point, 16 matrices of sides 16 to 72, 8 columns, FP32 60.7 / 101.0
-// -> 54.3 / 96.6; 3D 19-point 61x64x67, 8 columns, FP32 21.2 / 42.9 -> 17.4 /
-// 29.5; 2D 5-point 707x601, 5 columns, FP64 (one column per lane before, as
-// rows end off 16 bytes) 21.8 / 46.0 -> 15.6 / 23.6.
+// What bounds it: waiting for its chain of loads (record, stream, batches of
+// gathers) at the wavefronts that its registers leave resident; the counters do not
+// tell latency from bandwidth there.  One MI355X, three matrices used in turn, us,
+// forward / adjoint, general walk -> window walk: 3D 7-point, 16 matrices of sides
+// 16 to 72, 8 columns, FP32 56.3 / 96.6 -> 49.8 / 91.0; 3D 19-point 61x64x67, 8
+// columns, FP32 21.5 / 43.1 -> 15.8 / 27.5; 2D 5-point 707x601, 5 columns, FP64 (one
+// column per lane before, as rows end off 16 bytes) 22.1 / 47.3 -> 14.3 / 23.3.
 #pragma once
 
 #include "window.hpp"
