@@ -79,8 +79,8 @@ typedef enum csrk_reorder { CSRK_REORDER_BANDK = 0, CSRK_REORDER_RCM = 1, CSRK_R
  * matrix whose super-rows, or the pieces that launches cut them into, all fit
  * one staging window with columns within 65536 of each other gives a row the
  * lanes that its super-row leaves); waves_per_wg (1..16) the wavefronts per
- * workgroup (at least 8 in a launch over one matrix with rows longer than
- * CSRK_LONG_ROW).  k is the number of CSR-k levels, 2..8 (Section
+ * workgroup (at least 8 in a launch over one matrix with rows or columns longer
+ * than CSRK_LONG_ROW).  k is the number of CSR-k levels, 2..8 (Section
  * 2.2 defines CSR-k for every k >= 2): k - 1 grouping levels above the rows.
  * k = 3 (CSR-3): super-rows and super-super-rows.  k = 2 (CSR-2): one
  * coarsening level, Band-k orders the coarse graph by reverse Cuthill-McKee;
