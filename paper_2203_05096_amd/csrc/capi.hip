@@ -206,7 +206,11 @@ constexpr int32_t kHeavyRow = 256;
 //   2D 9-point 501x403, 30% dropped, FP64    13.4 / 12.6  16.7 / 14.2
 //   100,000 rows, upper band of 31, FP64     25.9 / 19.7  32.0 / 23.4   product 10.7 / 8.6
 //   50,000 rows of 40, no mirrors, FP64      24.7 / 20.5  37.3 / 25.4   product 12.3 / 8.7
-constexpr double kUnionCut = 1.2;
+// Small matrices, whose launches wait for two passes in turn, take more extras:
+//   3D 27-point 31x30x33, 30% dropped, 0.6 M entries, FP64  7.7 / 9.4  10.1 / 10.3  FP32 6.8 / 7.9  8.1 / 7.9
+//   3D 19-point 41x39x43, 30% dropped, 0.9 M entries, FP64  9.9 / 9.9  13.2 / 12.0  FP32 7.3 / 7.2  9.9 / 9.1
+constexpr double kUnionCut = 1.2, kUnionCutSmall = 1.4;
+constexpr int64_t kUnionSmall = 1 << 20;
 
 // Wavefronts per workgroup, at least, for a matrix with long rows: one
 // workgroup computes each, and the longest is what the launch waits for.  The
@@ -274,7 +278,8 @@ void launch_shape(csrk_matrix *h) {
         if (!h->trans.symmetric) {
             std::vector<int32_t> both = csrk::union_lengths(h->n, h->row_ptr, h->col_idx, h->trans);
             const int64_t total = std::accumulate(both.begin(), both.end(), int64_t(0));
-            if (h->uni.ok || double(total) <= kUnionCut * double(h->nnz)) len = std::move(both);
+            const double most = h->nnz <= kUnionSmall ? kUnionCutSmall : kUnionCut;
+            if (h->uni.ok || double(total) <= most * double(h->nnz)) len = std::move(both);
         }
         h->win = csrk::launch_windows(h->sr_ptr, h->ssr_ptr, len, kWinRows, kWinEntries, kHeavyRow,
                                       std::max(h->params.ssrs, waves), has_long_rows(h));

@@ -62,7 +62,8 @@ def due(A, M):
     sym = both.sum() == own.sum()
     sums = (lambda ptr, length: np.add.reduceat(np.append(length, 0), ptr[:-1]) * (np.diff(ptr) > 0))
     fits = (lambda ptr: np.diff(ptr).max() <= 64 and sums(ptr, both).max() <= 504)
-    win = cut(sr, both if fits(sr) or both.sum() <= 1.2 * own.sum() else own)
+    most = 1.4 if A.nnz <= 1 << 20 else 1.2
+    win = cut(sr, both if fits(sr) or both.sum() <= most * own.sum() else own)
     longest = max(own.max(), np.bincount(A.col_idx, minlength=A.n).max())
     lanes = 1
     while lanes < 16 and np.diff(win).max() * lanes * 2 <= 64:
@@ -91,6 +92,21 @@ def test_walk_of_edge_matrices(name):
             M.close()
     assert name not in ("beyond", "heavy") or (0, 2) in seen
     assert name not in ("one_row", "lanes16") or seen[0][0] == 1
+
+
+@pytest.mark.parametrize("n,drop", [(140000, 0.3), (190000, 0.3), (190000, 0.1), (140000, 0.6)])
+def test_walk_by_extras_and_entries(n, drop):
+    """Super-rows are cut for the union up to 1.4 times the entries in small matrices, 1.2 times in others; with 60%
+    dropped, the union fits the super-rows all the same."""
+    cols = np.arange(n)[:, None] + np.arange(-4, 5)
+    keep = (cols >= 0) & (cols < n) & ((np.random.default_rng(9).random(cols.shape) >= drop) | (cols == np.arange(n)[:, None]))
+    rp = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int32)
+    A = CsrInput("band", n, rp, cols[keep].astype(np.int32), np.ones(keep.sum()), {})
+    M = build(A, 64)
+    w, want = C.csrk_get_walk(M.handle), due(A, M)
+    assert {k: w[k] for k in want} == want
+    assert want["adjoint_passes"] == (2 if (n, drop) == (190000, 0.3) else 1)
+    M.close()
 
 
 def test_walk_windows():
